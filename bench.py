@@ -44,7 +44,6 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 VALU_LANE_OPS_PEAK = 256 * 4 * 16 * 2.4e9   # vector lane-operations per second (MI355X)
-MF_FLAG = 1024                                  # build-variant flag: pair tests on the matrix cores
 
 
 def log(*a):
@@ -177,10 +176,7 @@ def run_windows(H, torch, cfg, X0, V0, SIG, L, prec, steps, warmup, windows, eve
 
 def build_kernel_name(d: int, variant: int) -> str:
     """The list-build kernel a build variant launches (n_cell >= 3)."""
-    g = variant & ~MF_FLAG
-    if g >= 64:
-        return "k_build<%d,%d lanes>" % (d, g)
-    return "k_build_t<%d,%d%s>" % (d, g, ",matrix-core tests" if variant & MF_FLAG else "")
+    return "k_build_mf<%d,%d>" % (d, variant)
 
 
 def window_record(cfg, prec_mixed, win, meta, steps):
@@ -605,8 +601,8 @@ def main():
     # vector prefilter's cost, ceil(d/2) packed int16 dot products and a
     # compare, one VALU lane-operation each; the peak is 256 CUs x 4 SIMDs x
     # 16 lanes x 2.4 GHz lane-operations per second.  (Row culling skips most
-    # candidates before any test, and the matrix-core variant runs the tests
-    # it does make as f16 products, so this is a rate, not the kernel's own
+    # candidates before any test, and the tests it does make run as f16
+    # matrix products, so this is a rate, not the kernel's own
     # VALU use.)
     roof_build = None
     if f.get("build_ms") and f.get("build_candidates"):

@@ -16,11 +16,12 @@ struct DKernels {
   void (*disp_restart)(SysDev* s, int grid, hipStream_t st);
   void (*bin)(const KArgs& a, int grid, hipStream_t st);
   void (*cellsort)(bool mix, const KArgs& a, int grid, hipStream_t st);
-  // reach: stencil radius in subcells (1: subcells of side >= r_l,max, 3^d
-  // stencil; 2: half-size subcells, 5^d stencil); blk: workgroup size of the
-  // home-atom-lane build (64/128/256), or 1, 2, 4 waves per subcell of the
-  // candidate-lane build.  Each launch serves the systems of its own reach.
-  void (*build)(int reach, bool wrap, int blk, const KArgs& a, int grid, hipStream_t st);
+  // list build of the systems of n_cell >= 3 on one stencil radius (reach 1:
+  // subcells of side >= r_l,max, 3^d stencil; 2: half-size subcells, 5^d
+  // stencil) and of one form (BuildMode), with G = 1, 2 or 4 waves per subcell
+  void (*build)(int reach, int mode, int G, const KArgs& a, int grid, hipStream_t st);
+  // list build of the systems of n_cell <= 2, over atom tiles
+  void (*build_wrap)(const KArgs& a, int grid, hipStream_t st);
   // the force kernels serve the systems of one precision form (mix) and one
   // potential class (morse: the Morse form; otherwise WCA and harmonic)
   void (*force)(bool mix, int lpa, bool morse, const KArgs& a, int grid, int fire, hipStream_t st);

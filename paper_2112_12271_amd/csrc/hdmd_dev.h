@@ -15,12 +15,10 @@
 //             source and destination of the permutation at a rebuild.
 //   f         forces [d][npad] (FP64 or FP32), written by the force kernels.
 //   xref      positions at the last build [d][npad] FP64 (rebuild trigger).
-//   qc        offsets from the subcell centre quantised to int8 in units of
-//             L_sc/250, packed four per int32 (prefilter of the list build
-//             when n_cell >= 3); qc16 the same as int16 pairs with |q|^2 in
-//             the last word read, or, when n_cell <= 2, 16-bit coordinates
-//             wrapping at L; ycell the offsets in FP32 (home-lane build when
-//             n_cell <= 2).
+//   qc16      the list build's record of each atom: the f16 slots of its offset
+//             from the subcell centre quantised in units of L_sc/250 (32
+//             bytes), or, for n_cell <= 2, of its place on the circle along
+//             each axis (32 bytes; 48 for d >= 8).
 //   nl, nlen  Verlet rows in ELL form, column-major nl[k*npad + i], i.e. entry
 //             k of every row is contiguous so a wave reads it coalesced.
 // Atoms are stored in subcell order (canonical: by subcell, then caller id),
@@ -44,11 +42,18 @@ constexpr int kPart = 11;       // doubles per wave in the partial-sum array
 // non-Gaussian alpha_2, overlap f_ov
 constexpr int kThermoCols = 10;
 constexpr int kMaxSlots = 1024;
-constexpr int kQCap = 16;       // per-lane prefilter queue of the build
 constexpr int kSwapBatch = 256;   // SWAP attempts per batch (a multiple of 64)
 constexpr int kPotMorse = 2;     // hdmd_system.potential of the Morse form
-constexpr int kQScale = 250;    // int8 quantisation: subcell side = 250 units
-constexpr int kBuildMF = 1024;  // build-variant flag: candidate-lane build, pair tests on the matrix cores
+constexpr int kQScale = 250;    // quantisation of the list build: subcell side = 250 units
+
+// forms of the matrix-core list build (kernels.h)
+enum BuildMode : int32_t { BUILD_SPARSE = 0, BUILD_DENSE = 1 };
+// The form a system's build takes (BuildMode), the same alone and in a batch:
+// the blocks of 16 candidates are mostly full from 16 atoms per subcell on.
+__host__ __device__ inline int build_mode(int reach, int64_t n, int64_t ncells) {
+  return reach == 2 || n > 16 * ncells ? BUILD_DENSE : BUILD_SPARSE;
+}
+
 
 enum Mode : int32_t { MODE_NONE = 0, MODE_FIRE = 1, MODE_MD = 2, MODE_STATIC = 3 };
 enum Slot : int32_t { SLOT_EMPTY = 0, SLOT_RUNNING = 1, SLOT_DONE = 2 };
@@ -76,9 +81,11 @@ struct FireCtl {
 struct SysDev {
   // ---- static, written by the host
   int32_t d, potential, precision, n;
-  int32_t npad, ncell, radix, ncells;
-  int32_t nstencil, width, nchunks, ntiles;
-  int32_t mode, wrap, nwaves;
+  int32_t npad, ncell, ncells;
+  int32_t width, nchunks, ntiles;
+  int32_t mode, nwaves;
+  int32_t wrap;   // 1: n_cell <= 2 on subcells of side >= r_l,max
+  int32_t bmode;  // form of the list build (BuildMode)
   int32_t reach;  // stencil radius in subcells: 1 (side >= r_l,max), 2 (half-size subcells)
   int32_t lpa;    // lanes per atom of the force kernels (1, 2 or 4)
   int32_t pad0;
@@ -89,10 +96,7 @@ struct SysDev {
   double qmarg;          // sqrt(d)/2 with slack: half the quantisation error bound
   double morse_a;        // Morse stiffness (potential 2)
   double tau_t, temp_t;  // Berendsen time constant (0: NVE) and target temperature
-  float rl2f, lscf, Lf, pad3;
-  int32_t tq, tcull;     // int8 prefilter threshold; row-culling threshold
-                         // (squared quantised units)
-  int32_t ysort, pad5;   // 1: subcells ordered by last-axis offset, then caller id
+  int32_t ysort;         // 1: subcells ordered by last-axis offset, then caller id
   double* x[2];
   int32_t* q[2];
   void* v[2];
@@ -101,12 +105,7 @@ struct SysDev {
   double* xref;
   double* disp[2];  // unwrapped displacement since the run's start up to the
                     // last build, [d][npad] (MD; permuted with the atoms)
-  float* ycell;
-  int32_t* qc;
-  int32_t* qc16;  // int16 offsets or wrapped 16-bit coordinates, [npad][8];
-                  // n_cell >= 3: words 0.. the offsets as int16 pairs, word
-                  // 3 (d <= 6) or 7 the home term |q|^2 - T, word 5 the
-                  // row-cull threshold, word 6 the threshold share T
+  int32_t* qc16;  // list-build records
   int32_t* cell_of;
   int32_t* rank;
   int32_t* cell_count;
@@ -156,7 +155,7 @@ struct Table {
 
 // Kernel arguments: either one system (tile = blockIdx) or a batch table.
 // part selects a sub-range of the cell tiles: 0 all, 1 systems with
-// n_cell >= 3, 2 systems with n_cell <= 2 (the two list-build variants).
+// n_cell >= 3, 2 systems with n_cell <= 2 (crowded subcells).
 struct KArgs {
   SysDev* single;
   Table* tab;
@@ -229,10 +228,53 @@ __device__ inline bool fetch_sys(const KArgs& a, int t, SysDev*& s) {
   return true;
 }
 
-__device__ inline bool running(const SysDev* s) { return s->status == SLOT_RUNNING; }
+// P: a descriptor pointer, generic or in the constant address space (cSys)
+template <typename P>
+__device__ inline bool running(P s) {
+  return s->status == SLOT_RUNNING;
+}
 
-__device__ inline bool need_rebuild(const SysDev* s) {
-  return s->force_rebuild != 0 || __longlong_as_double((long long)s->maxdisp2) > s->halfskin2;
+template <typename P>
+__device__ inline bool need_rebuild(P s) {
+  return (s->force_rebuild != 0) | (__longlong_as_double((long long)s->maxdisp2) > s->halfskin2);
+}
+
+// Descriptors and tables read through the constant address space: scalar
+// loads, whose values the compiler knows to be the same in every lane.  Only
+// for fields that the running kernel does not write.
+typedef const __attribute__((address_space(4))) SysDev cSys;
+typedef const __attribute__((address_space(4))) Table cTable;
+typedef const __attribute__((address_space(4))) int2 cint2;
+
+__device__ inline bool fetch_atom_tile_u(const KArgs& a, int t, SysDev*& s, int& tile) {
+  if (a.single) {
+    s = a.single;
+    tile = t;
+    return t < ((cSys*)a.single)->ntiles;
+  }
+  cTable* tab = (cTable*)a.tab;
+  if (t >= tab->n_atom[a.cls]) return false;
+  cint2* e = (cint2*)tab->atom_tiles[a.cls] + t;
+  s = tab->sys[e->x];
+  tile = e->y;
+  return true;
+}
+
+__device__ inline bool fetch_cell_tile_u(const KArgs& a, int t, SysDev*& s, int& cell) {
+  if (a.single) {
+    s = a.single;
+    cell = t;
+    return t < ((cSys*)a.single)->ncells;
+  }
+  cTable* tab = (cTable*)a.tab;
+  int lo = 0, hi = tab->n_cell[a.cls];
+  if (a.part == 1) hi = tab->n_cell_nowrap[a.cls];
+  else if (a.part == 2) lo = tab->n_cell_nowrap[a.cls];
+  if (t >= hi - lo) return false;
+  cint2* e = (cint2*)tab->cell_tiles[a.cls] + lo + t;
+  s = tab->sys[e->x];
+  cell = e->y;
+  return true;
 }
 
 // Subcell start (exclusive prefix of occupancies), split in chunk-local part
@@ -275,11 +317,9 @@ struct Dims {
   static constexpr int SQ = (D + 1) & ~1;                     // FP64 sigma slot (in ints)
   static constexpr int DQ = D <= 2 ? 4 : (D <= 6 ? 8 : 16);  // fixed-point record stride (ints)
   static constexpr int NQ = (SQ + 2 + 3) / 4;                 // int4 loads per record
-  static constexpr int DY = (D + 3) & ~3;                     // FP32 offset stride
-  static constexpr int QW = (D + 3) / 4;                      // int8x4 words of the offsets
 };
 
-// int8 offset from the subcell centre in units of L_sc / 250; |y| <= L_sc/2
+// offset from the subcell centre in units of L_sc / 250; |y| <= L_sc/2
 // up to binning rounding, so |q| <= 125 and the clamp never bites.
 __device__ inline int quant8(double y, double qinv) {
   int q = (int)rint(y * qinv);
@@ -291,7 +331,7 @@ __device__ inline double last_centre(const SysDev* s, int c) {
   return ((double)(c % s->ncell) + 0.5) * s->lsc - s->hL;
 }
 
-// An atom's share T of the candidate-lane prefilter threshold (squared
+// An atom's share T of the list build's prefilter threshold (squared
 // quantised units): a = (c sigma + s)/2, alpha = a/Delta + sqrt(d)/2 (with
 // slack), T = floor(2 alpha^2) + 1; non-decreasing in sigma.
 __device__ inline int thresh_share(const SysDev* s, double sg) {

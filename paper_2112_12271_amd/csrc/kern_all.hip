@@ -151,60 +151,67 @@ __global__ __launch_bounds__(kTile) void k_force_all(KArgs a, int fire) {
 // Verlet-list build of every rebuilding system with d <= kBuildAllMaxD (the
 // d = 9, 10 bodies need more registers than four waves per SIMD allow, so
 // those classes keep launches of their own): a subcell of an n_cell >= 3
-// system is one wave's work (four such per workgroup), a subcell of an
-// n_cell <= 2 system (crowded: it holds the atoms of 1/2^d of the box) is
-// split over the four waves of a workgroup.  One launch per stencil radius
-// present (RAD 1: subcells of side >= r_l,max; RAD 2: half-size subcells),
-// each passing over the subcells of the other radius.
+// system is one wave's work (four such per workgroup), and so is an atom
+// tile of an n_cell <= 2 system.  One launch per stencil radius present (RAD
+// 1: subcells of side >= r_l,max; RAD 2: half-size subcells), each passing
+// over the subcells of the other radius.
 template <int RAD>
-__global__ __launch_bounds__(256) void k_build_all(KArgs a) {
-  __shared__ unsigned long long msk_all[4][8 * 128];
-  __shared__ int cand_all[4][8 * 64];
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int nnw = a.tab->n_cell_nowrap[0], ntot = a.tab->n_cell[0];
-  const int unw = (nnw + 3) / 4;
-  const int units = unw + (ntot - nnw);
-  const int2* tiles = a.tab->cell_tiles[0];
-  const int g = gridDim.x;
-  for (int base = xcd_tile(blockIdx.x, g); base < units; base += 256 * g) {
-    unsigned long long mk[4];
-    {
-      // unit u: subcells 4u..4u+3 of the n_cell >= 3 part, or one wrapped subcell
-      const int u = base + (int)threadIdx.x * g;
-      bool act = false;
-      int2 e;
-      if (u < unw) {
-        for (int q = 0; q < 4; q++) act |= tile_rebuilds(a.tab, tiles, 4 * u + q, nnw, e, kBuildAllMaxD);
-      } else if (u < units) {
-        act = tile_rebuilds(a.tab, tiles, nnw + (u - unw), ntot, e, kBuildAllMaxD);
+__global__ __launch_bounds__(256, 4) void k_build_all(KArgs a) {
+  __shared__ BuildLds<RAD> lds[4];
+  static_assert(sizeof(WrapLds) <= sizeof(BuildLds<RAD>), "one LDS area serves both builds");
+  cTable* tab = (cTable*)a.tab;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int nnw = tab->n_cell_nowrap[0];
+  cint2* tiles = (cint2*)tab->cell_tiles[0];
+  // this wave's tiles are strided by the waves of the launch
+  const int g = gridDim.x * 4, me = xcd_tile(blockIdx.x, gridDim.x) * 4 + wv;
+  for (int base = me; base < nnw; base += 64 * g) {
+    int2 e;
+    unsigned long long mk = __ballot(
+        tile_rebuilds(a.tab, a.tab->cell_tiles[0], base + lane * g, nnw, e, kBuildAllMaxD));
+    while (mk) {
+      const int idx = base + __builtin_ctzll(mk) * g;
+      mk &= mk - 1;
+      SysDev* s = tab->sys[tiles[idx].x];
+      cSys* c = (cSys*)s;
+      const int hc = tiles[idx].y;
+      if (c->reach != RAD) continue;
+      const int mode = c->bmode;
+      switch (c->d) {
+#define HDMD_CASE(DD)                                                                              \
+  case DD:                                                                                         \
+    if (RAD == 1 && mode == BUILD_SPARSE)                                                          \
+      build_mf_tile<DD, RAD, RAD == 1 ? BUILD_SPARSE : BUILD_DENSE>(s, hc, 0, 1, &lds[wv]);        \
+    else build_mf_tile<DD, RAD, BUILD_DENSE>(s, hc, 0, 1, &lds[wv]);                               \
+    break;
+        HDMD_BUILD_D(HDMD_CASE)
+#undef HDMD_CASE
       }
-      if (!block_ballots(act, reinterpret_cast<unsigned long long*>(cand_all[0]), mk)) continue;
     }
-    for (int q = 0; q < 4; q++) {
-      unsigned long long mq = mk[q];
-      while (mq) {
-        const int u = base + (64 * q + __builtin_ctzll(mq)) * g;
-        mq &= mq - 1;
-        const bool wr = u >= unw;
-        const int idx = wr ? nnw + (u - unw) : 4 * u + wv;
-        if (idx >= ntot || (!wr && idx >= nnw)) continue;
-        const int2 e = tiles[idx];
-        SysDev* s = uniform_ptr(a.tab->sys[uniform_int(e.x)]);
-        const int hc = uniform_int(e.y);
-        if (!running(s) || !need_rebuild(s) || uniform_int(s->reach) != RAD) continue;
-        switch (s->d) {
-#define HDMD_CASE(DD)                                                             \
-  case DD:                                                                        \
-    if (RAD == 2) build_t_tile<DD, 1, false, 2>(s, hc, 0, msk_all[wv], cand_all[wv]); \
-    else if (wr) build_t_tile<DD, 4, true>(s, hc, wv, msk_all[wv], cand_all[wv]); \
-    else build_t_tile<DD, 1, false>(s, hc, 0, msk_all[wv], cand_all[wv]);         \
+  }
+  if constexpr (RAD == 1) {
+    const int nat = tab->n_atom[0];
+    cint2* at = (cint2*)tab->atom_tiles[0];
+    for (int base = me; base < nat; base += 64 * g) {
+      int2 e = make_int2(0, 0);
+      bool act = tile_rebuilds(a.tab, a.tab->atom_tiles[0], base + lane * g, nat, e, kBuildAllMaxD);
+      if (act) act = a.tab->sys[e.x]->wrap != 0;
+      unsigned long long mk = __ballot(act);
+      while (mk) {
+        const int idx = base + __builtin_ctzll(mk) * g;
+        mk &= mk - 1;
+        SysDev* s = tab->sys[at[idx].x];
+        const int tile = at[idx].y;
+        switch (((cSys*)s)->d) {
+#define HDMD_CASE(DD)                                                         \
+  case DD:                                                                    \
+    build_wrap_tile<DD>(s, tile, reinterpret_cast<WrapLds*>(&lds[wv]));       \
     break;
           HDMD_BUILD_D(HDMD_CASE)
 #undef HDMD_CASE
         }
       }
     }
-    __syncthreads();  // the LDS exchange area is free again
   }
 }
 

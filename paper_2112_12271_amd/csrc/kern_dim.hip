@@ -34,48 +34,24 @@ void l_cellsort(bool mix, const KArgs& a, int grid, hipStream_t st) {
   if (mix) k_cellsort<D, float><<<grid, 256, 0, st>>>(a);
   else k_cellsort<D, double><<<grid, 256, 0, st>>>(a);
 }
-void l_build(int reach, bool wrap, int blk, const KArgs& a, int grid, hipStream_t st) {
-  if ((blk & kBuildMF) && !wrap) {
-    // candidate-lane build with the pair tests on the matrix cores
-    blk &= ~kBuildMF;
-    if (reach == 2) {
-      if (blk == 1) k_build_t<D, 1, false, 2, true><<<grid, 64, 0, st>>>(a);
-      else if (blk == 2) k_build_t<D, 2, false, 2, true><<<grid, 128, 0, st>>>(a);
-      else k_build_t<D, 4, false, 2, true><<<grid, 256, 0, st>>>(a);
-    } else {
-      if (blk == 1) k_build_t<D, 1, false, 1, true><<<grid, 64, 0, st>>>(a);
-      else if (blk == 2) k_build_t<D, 2, false, 1, true><<<grid, 128, 0, st>>>(a);
-      else k_build_t<D, 4, false, 1, true><<<grid, 256, 0, st>>>(a);
-    }
-    return;
-  }
-  blk &= ~kBuildMF;  // wrapped systems: the vector form
+void l_build(int reach, int mode, int G, const KArgs& a, int grid, hipStream_t st) {
   if (reach == 2) {
-    // half-size subcells, 5^d stencil (never wrapped)
-    if (blk == 1) k_build_t<D, 1, false, 2><<<grid, 64, 0, st>>>(a);
-    else if (blk == 2) k_build_t<D, 2, false, 2><<<grid, 128, 0, st>>>(a);
-    else if (blk == 4 || blk == 8 || blk == 16) k_build_t<D, 4, false, 2><<<grid, 256, 0, st>>>(a);
-    else if (blk <= 64) k_build<D, false, 64><<<grid, 64, 0, st>>>(a);
-    else if (blk <= 128) k_build<D, false, 128><<<grid, 128, 0, st>>>(a);
-    else k_build<D, false, 256><<<grid, 256, 0, st>>>(a);
-  } else if (wrap) {
-    // crowded subcells (n_cell <= 2): up to 16 waves share one
-    if (blk == 1) k_build_t<D, 1, true><<<grid, 64, 0, st>>>(a);
-    else if (blk == 2) k_build_t<D, 2, true><<<grid, 128, 0, st>>>(a);
-    else if (blk == 4) k_build_t<D, 4, true><<<grid, 256, 0, st>>>(a);
-    else if (blk == 8) k_build_t<D, 8, true><<<grid, 512, 0, st>>>(a);
-    else if (blk == 16) k_build_t<D, 16, true><<<grid, 1024, 0, st>>>(a);
-    else if (blk <= 64) k_build<D, true, 64><<<grid, 64, 0, st>>>(a);
-    else if (blk <= 128) k_build<D, true, 128><<<grid, 128, 0, st>>>(a);
-    else k_build<D, true, 256><<<grid, 256, 0, st>>>(a);
+    // half-size subcells, 5^d stencil
+    if (G <= 1) k_build_mf<D, 1, 2, BUILD_DENSE><<<grid, 64, 0, st>>>(a);
+    else if (G == 2) k_build_mf<D, 2, 2, BUILD_DENSE><<<grid, 128, 0, st>>>(a);
+    else k_build_mf<D, 4, 2, BUILD_DENSE><<<grid, 256, 0, st>>>(a);
+  } else if (mode == BUILD_DENSE) {
+    if (G <= 1) k_build_mf<D, 1, 1, BUILD_DENSE><<<grid, 64, 0, st>>>(a);
+    else if (G == 2) k_build_mf<D, 2, 1, BUILD_DENSE><<<grid, 128, 0, st>>>(a);
+    else k_build_mf<D, 4, 1, BUILD_DENSE><<<grid, 256, 0, st>>>(a);
   } else {
-    if (blk == 1) k_build_t<D, 1, false><<<grid, 64, 0, st>>>(a);
-    else if (blk == 2) k_build_t<D, 2, false><<<grid, 128, 0, st>>>(a);
-    else if (blk == 4 || blk == 8 || blk == 16) k_build_t<D, 4, false><<<grid, 256, 0, st>>>(a);
-    else if (blk <= 64) k_build<D, false, 64><<<grid, 64, 0, st>>>(a);
-    else if (blk <= 128) k_build<D, false, 128><<<grid, 128, 0, st>>>(a);
-    else k_build<D, false, 256><<<grid, 256, 0, st>>>(a);
+    if (G <= 1) k_build_mf<D, 1, 1, BUILD_SPARSE><<<grid, 64, 0, st>>>(a);
+    else if (G == 2) k_build_mf<D, 2, 1, BUILD_SPARSE><<<grid, 128, 0, st>>>(a);
+    else k_build_mf<D, 4, 1, BUILD_SPARSE><<<grid, 256, 0, st>>>(a);
   }
+}
+void l_build_wrap(const KArgs& a, int grid, hipStream_t st) {
+  k_build_wrap<D><<<grid, 64, 0, st>>>(a);
 }
 template <bool MIX, int LPA, bool MORSE = false>
 void force_lpa(const KArgs& a, int grid, int fire, hipStream_t st) {
@@ -134,7 +110,7 @@ void l_swap_settle(SysDev* s, hipStream_t st, long long* ctl, const int32_t* off
   k_swap_settle<D><<<1, 1024, 0, st>>>(s, ctl, off_in, off_out, n_att, pairs, u, T, slot_of, de,
                                        conf, acc, diam);
 }
-const DKernels table = {l_load, l_unload, l_same_state, l_disp_restart, l_bin, l_cellsort, l_build, l_force, l_step,
+const DKernels table = {l_load, l_unload, l_same_state, l_disp_restart, l_bin, l_cellsort, l_build, l_build_wrap, l_force, l_step,
                         l_fire_update, l_vanhove, l_swap_de, l_swap_settle};
 }  // namespace
 

@@ -5,7 +5,7 @@
 //  k_scatter     counting-sort placement by subcell            (common.hip)
 //  k_cellsort    per-subcell sort by caller id, permutation of every per-atom
 //                array, reference positions, prefilter offsets
-//  k_build       Verlet rows over the 3^d linked subcells      (Sec. II.C, Fig. 1)
+//  k_build_mf, k_build_wrap  Verlet rows over the linked subcells (Sec. II.C, Fig. 1)
 //  k_force       pair forces and energy (+ FIRE reductions)    (Sec. II.B)
 //  k_step        fused velocity-Verlet step + rebuild trigger (Sec. II.B/II.C)
 //  k_fire_update semi-implicit Euler FIRE update
@@ -257,7 +257,61 @@ __device__ inline void bitonic_sort(int* keys, int* vals, int cnt) {
   }
 }
 
-__device__ inline int sext8(int w, int k) { return (int)(signed char)((w >> (8 * k)) & 0xff); }
+typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
+__device__ inline unsigned h2u(hv2 v) { return __builtin_bit_cast(unsigned, v); }
+__device__ inline hv2 u2h(unsigned v) { return __builtin_bit_cast(hv2, v); }
+
+// The candidate slots of an atom (see the list build below) from its int8 offsets and C.
+template <int D>
+__device__ inline void cand_record(const int (&q)[D], int C, unsigned (&w)[8]) {
+  _Float16 sl[16];
+#pragma unroll
+  for (int k = 0; k < 16; k++) sl[k] = (_Float16)0;
+  sl[0] = (_Float16)(short)(2 * q[D - 1]);
+  sl[1] = (_Float16)2048;
+  sl[2] = sl[3] = (_Float16)1;
+#pragma unroll
+  for (int k = 0; k < D - 1; k++) sl[4 + k] = (_Float16)(short)(2 * q[k]);
+  sl[D + 3] = (_Float16)(short)(C >> 11);
+  sl[D + 4] = (_Float16)(short)(C & 2047);
+#pragma unroll
+  for (int t = 0; t < 8; t++) w[t] = h2u(hv2{sl[2 * t], sl[2 * t + 1]});
+}
+
+typedef _Float16 hv8 __attribute__((ext_vector_type(8)));
+template <int D>
+struct WrapRec {
+  static constexpr int SLOTS = 2 * D + 2 <= 16 ? 16 : 24;
+  static constexpr int WORDS = SLOTS / 2;            // record words
+  static constexpr int LW = SLOTS == 16 ? 2 : 4;     // words per lane and operand
+};
+
+// f16 rounding: every cos and sin is off by at most 2^-12 + 2^-24, so the sum
+// of 2 d products by less than 2 d * 2 * 2^-12 * (|cos| + |sin|)/2 <= 1.42 d
+// 2^-11, and each share by 2^-11 d (|t| < 2 d); the margin of a share covers
+// half of the first and its own, doubled.
+__host__ __device__ constexpr double wrap_margin(int d) { return d * (1.42 / 2048.0 + 2.0 / 2048.0); }
+
+template <int D>
+__device__ inline void wrap_record(const SysDev* s, const double (&x)[D], double sg, int32_t* out) {
+  typedef WrapRec<D> R;
+  _Float16 sl[R::SLOTS];
+#pragma unroll
+  for (int k = 0; k < R::SLOTS; k++) sl[k] = (_Float16)0;
+  const double two_pi = 6.283185307179586;
+#pragma unroll
+  for (int k = 0; k < D; k++) {
+    const float th = (float)(x[k] / s->L * two_pi);
+    sl[2 * k] = (_Float16)cosf(th);
+    sl[2 * k + 1] = (_Float16)sinf(th);
+  }
+  const double a = two_pi / s->L * 0.5 * (s->cutoff * sg + s->skin);
+  sl[2 * D] = (_Float16)1;
+  // a share below the f16 range passes every pair, as -2 d does
+  sl[2 * D + 1] = (_Float16)(float)fmax(0.5 * D - a * a - wrap_margin(D), -2.0 * D);
+#pragma unroll
+  for (int t = 0; t < R::WORDS; t++) out[t] = (int)h2u(hv2{sl[2 * t], sl[2 * t + 1]});
+}
 
 // One subcell of a system that rebuilds (a block of 256 threads): its atoms
 // sorted by their keys (caller id, or, with ysort, the quantised offset along
@@ -265,7 +319,6 @@ __device__ inline int sext8(int w, int k) { return (int)(signed char)((w >> (8 *
 // subcell order.
 template <int D, typename VT>
 __device__ inline void cellsort_tile(SysDev* s, int c, int* sk, int* sv) {
-  constexpr int DY = Dims<D>::DY, QW = Dims<D>::QW;
   constexpr bool MIX = sizeof(VT) == 4;
   const int s0 = cell_start(s, c), cnt = cell_start(s, c + 1) - s0;
   if (threadIdx.x == 0) {
@@ -320,62 +373,21 @@ __device__ inline void cellsort_tile(SysDev* s, int c, int* sk, int* sv) {
       if (md) dout[(size_t)k * npad + dst] = din[(size_t)k * npad + src];
     }
     if (wrap) {
-      float y[DY];
-#pragma unroll
-      for (int k = 0; k < DY; k++) y[k] = k < D ? (float)(x[k] - cen[k]) : 0.0f;
-      float4* yp = reinterpret_cast<float4*>(s->ycell + (size_t)dst * DY);
-#pragma unroll
-      for (int k = 0; k < DY / 4; k++) yp[k] = make_float4(y[4 * k], y[4 * k + 1], y[4 * k + 2], y[4 * k + 3]);
-      // 16-bit coordinates u = (x + L/2) 2^16 / L, wrapping at L: the 16-bit
-      // difference u_j - u_i is the minimum-image displacement in L/2^16
-      // units (candidate-lane build with n_cell <= 2)
-      const double ws16 = 65536.0 / s->L;
-      int p16[8];
-#pragma unroll
-      for (int k = 0; k < 8; k++) p16[k] = 0;
-#pragma unroll
-      for (int k = 0; k < D; k++) {
-        const int u = (int)((long long)rint((x[k] + s->hL) * ws16) & 0xffff);
-        p16[k / 2] |= u << (16 * (k % 2));
-      }
-      int4* pp = reinterpret_cast<int4*>(s->qc16 + (size_t)dst * 8);
-      pp[0] = make_int4(p16[0], p16[1], p16[2], p16[3]);
-      pp[1] = make_int4(p16[4], p16[5], p16[6], p16[7]);
+      // slots on the circle (list build of n_cell <= 2)
+      wrap_record<D>(s, x, sg, s->qc16 + (size_t)dst * WrapRec<D>::WORDS);
     } else {
-      int w[QW];
-#pragma unroll
-      for (int k = 0; k < QW; k++) w[k] = 0;
-#pragma unroll
-      for (int k = 0; k < D; k++)
-        w[k / 4] |= (quant8(x[k] - cen[k], s->qinv) & 0xff) << (8 * (k % 4));
-#pragma unroll
-      for (int k = 0; k < QW; k++) s->qc[(size_t)dst * 4 + k] = w[k];
-      // the same offsets as int16 pairs for the candidate-lane build, with
-      // the atom's share of the pair threshold.  A pair is within its list
-      // radius r_ij = a_i + a_j, a = (c sigma + s)/2, only if
-      // |q_j - q_i| < alpha_i + alpha_j, alpha = a/Delta + sqrt(d)/2 (each
-      // axis is off by at most one unit), and (alpha_i + alpha_j)^2 <=
-      // 2 alpha_i^2 + 2 alpha_j^2 < T_i + T_j with T = floor(2 alpha^2) + 1:
-      // one integer per atom, so the test stays one sum of products.  The
-      // row cull takes the atom's reach a_i + r_l,max/2 instead of r_l,max.
-      int p16[8], B = 0;
-#pragma unroll
-      for (int k = 0; k < 8; k++) p16[k] = 0;
+      // the candidate slots of the matrix-core build
+      int qv[D], Q = 0;
 #pragma unroll
       for (int k = 0; k < D; k++) {
-        const int qv = sext8(w[k / 4], k % 4);
-        p16[k / 2] |= (qv & 0xffff) << (16 * (k % 2));
-        B += qv * qv;
+        qv[k] = quant8(x[k] - cen[k], s->qinv);
+        Q += qv[k] * qv[k];
       }
-      const int T = thresh_share(s, sg);
-      const double ai = 0.5 * (s->cutoff * sg + s->skin);
-      const double reach = (ai + 0.5 * s->rlmax) * s->qinv;
-      p16[(D + 1) / 2 < 4 ? 3 : 7] = B - T;
-      p16[5] = (int)ceil(reach * reach);
-      p16[6] = T;
+      unsigned w[8];
+      cand_record<D>(qv, thresh_share(s, sg) - Q, w);
       int4* pp = reinterpret_cast<int4*>(s->qc16 + (size_t)dst * 8);
-      pp[0] = make_int4(p16[0], p16[1], p16[2], p16[3]);
-      pp[1] = make_int4(p16[4], p16[5], p16[6], p16[7]);
+      pp[0] = make_int4((int)w[0], (int)w[1], (int)w[2], (int)w[3]);
+      pp[1] = make_int4((int)w[4], (int)w[5], (int)w[6], (int)w[7]);
     }
     s->oid[pn][dst] = s->ysort ? keys[q] & ((1 << 23) - 1) : keys[q];
   }
@@ -401,334 +413,49 @@ __global__ __launch_bounds__(256) void k_cellsort(KArgs a) {
 // ---------------------------------------------------------------------------
 // Verlet-list build over the linked subcells (Sec. II.C, Fig. 1)
 //
-// One workgroup per home subcell; its atoms are the lanes (in chunks of BLK).
-// The linked subcells are decoded on the fly from a mixed-radix counter
-// (offsets -1/0/+1 per axis, -2..+2 on half-size subcells, or the
-// deduplicated {0,+1} / {0} when n_cell is 2 / 1).  Each linked subcell's atoms are staged in LDS and every lane tests
-// every staged atom with a conservative prefilter; survivors go to a per-lane
-// LDS queue and are re-tested exactly in FP64 with the per-pair radius -- the
-// operation sequence of the list definition -- before being appended to the
-// row.  Row order: linked-subcell order, then slot order (deterministic).
+// Systems of n_cell >= 3 (and half-size subcells, at least 5 per axis): the
+// matrix-core build.  Every atom's offset from its subcell centre is
+// quantised to q = y/Delta (Delta = L_sc/250, |q| <= 125), so an atom of the
+// subcell o away sits at q_j + 250 o.  A pair is within its list radius
+// r_ij = a_i + a_j, a = (c sigma + s)/2, only if |q_j + 250 o - q_i| <
+// alpha_i + alpha_j, alpha = a/Delta + sqrt(d)/2 (each axis is off by at most
+// one unit), and (alpha_i + alpha_j)^2 <= 2 alpha_i^2 + 2 alpha_j^2 < T_i +
+// T_j with T = floor(2 alpha^2) + 1: with q'_i = q_i - 250 o,
+//   |q_j - q'_i|^2 < T_i + T_j  <=>  S_ij = q'_i.(2 q_j) + C_j - B'_i > 0,
+//   C_j = T_j - |q_j|^2,  B'_i = |q'_i|^2 - T_i.
+// S is one entry of a product over 16 f16 slots:
+//   candidate [2q_j,d-1, 2048, 1, 1, 2q_j,0 .. 2q_j,d-2, floor(C_j/2048), C_j mod 2048, 0 ..]
+//   home      [-q'_i,d-1, floor(B'_i/2048), B'_i mod 2048, 1/2, -q'_i,0 .. -q'_i,d-2, -2048, -1, 0 ..]
+// gives 1/2 - S_ij, negative exactly when the pair survives.  Every slot is
+// an integer of magnitude <= 2048 or 1/2 (exact in f16: |2q| <= 254, |q'| <=
+// 127 + 250 reach, -2^18 < C < 2^18, |B'| < 2^22) and every partial sum is a
+// multiple of 1/2 below 2^23 in magnitude, so the f32 accumulation is exact
+// in any order.  The subcell shift sits on the home side only: the candidate
+// slots are a record of the atom's own, written once by the subcell sort in
+// the layout the matrix instruction reads, and the build loads them straight
+// into its operands (no conversion, no shuffle); the home slots are remade
+// per row of linked subcells, for the home atoms that can reach it.
+// Survivors are listed 64 lanes at a time as (home atom, candidate) codes
+// and re-tested exactly in FP64 with the per-pair radius -- the operation
+// sequence of the list definition -- one per lane; the passing ones are
+// appended to their rows.
 //
-// Prefilter, not wrapped (n_cell >= 3, or half-size subcells, at least 5 per
-// axis): the image shift of a linked subcell is its offset times the subcell
-// side for every pair within the list radius, so with
-// offsets y from the subcell centres quantised to q = y/Delta (Delta =
-// L_sc/250, shift D = 250 o exactly), |r - Delta |q_j + D - q_i|| <= Delta
-// sqrt(d) and
-//   |q_j + D - q_i|^2 = A_j + C_i - 2 q_i.q_j,  A_j = |q_j + D|^2,
-//   C_i = |q_i|^2 - 2 q_i.D,
-// where q_i.q_j is two or three packed int8 dot products (v_dot4_i32_i8);
-// a pair survives when that is below ((r_l,max + Delta sqrt(d)) / Delta)^2.
-// Prefilter, n_cell <= 2: FP32 offsets with the per-axis minimum image
-// min(|u|, L - |u|), against the largest list radius enlarged by 1e-4.
-// ---------------------------------------------------------------------------
-template <int D>
-__device__ inline void decode_linked(int q, int radix, int reach, int nc, const int (&ci)[D],
-                                     int (&o)[D], int (&cj)[D]) {
-  // radix 2 reach + 1: offsets -reach..+reach; fewer subcells per axis than
-  // that: each of the n_cell subcells once (the deduplicated stencil)
-  const bool dedup = radix < 2 * reach + 1;
-#pragma unroll
-  for (int k = D - 1; k >= 0; k--) {
-    int dig = q % radix;
-    q /= radix;
-    int oo = dedup ? dig : dig - reach;
-    int c2 = ci[k] + oo;
-    c2 = c2 < 0 ? c2 + nc : (c2 >= nc ? c2 - nc : c2);
-    cj[k] = c2;
-    o[k] = dedup ? c2 - ci[k] : oo;
-  }
-}
-
-template <int D, bool WRAP, int BLK>
-__global__ __launch_bounds__(BLK) void k_build(KArgs a) {
-  constexpr int DY = Dims<D>::DY, QW = Dims<D>::QW;
-  constexpr int SW = WRAP ? DY : 4;  // staged words per candidate
-  constexpr int UNR = WRAP ? 4 : 8;  // candidates tested per batch of LDS reads
-  __shared__ float stage[BLK * SW];
-  __shared__ int qbuf[kQCap * BLK];
-  const int tid = threadIdx.x;
-  for (int t = blockIdx.x;; t += gridDim.x) {
-    SysDev* s;
-    int hc;
-    if (!fetch_cell_tile(a, t, s, hc)) break;
-    if (!running(s) || !need_rebuild(s)) {
-      if (a.single) break;  // one system: the same for every tile
-      continue;
-    }
-    const int h0 = cell_start(s, hc), h1 = cell_start(s, hc + 1);
-    if (h0 == h1) continue;
-    const int nc = s->ncell, radix = s->radix, nst = s->nstencil, npad = s->npad;
-    const int reach = s->reach;
-    const int W = s->width;
-    const double* __restrict__ xb = s->x[s->xcur];
-    int* __restrict__ nl = s->nl;
-    const double L = s->L, hL = s->hL, cut = s->cutoff, skin = s->skin;
-    const float lscf = s->lscf, Lf = s->Lf, rl2f = s->rl2f;
-    const int tq = s->tq;
-    int ci[D];
-    {
-      int u = hc;
-#pragma unroll
-      for (int k = D - 1; k >= 0; k--) {
-        ci[k] = u % nc;
-        u /= nc;
-      }
-    }
-    int rowmax = 0;
-    for (int hb = h0; hb < h1; hb += BLK) {
-      const int i = hb + tid;
-      const bool vi = i < h1;
-      const int ii = vi ? i : h0;
-      double xi[D], si;
-      load_rec<D>(xb, ii, xi, si);
-      float yi[D];
-      int qi[QW], qik[D], qn2 = 0;
-      if (WRAP) {
-#pragma unroll
-        for (int k = 0; k < D; k++) yi[k] = s->ycell[(size_t)ii * DY + k];
-      } else {
-#pragma unroll
-        for (int k = 0; k < QW; k++) qi[k] = s->qc[(size_t)ii * 4 + k];
-#pragma unroll
-        for (int k = 0; k < D; k++) {
-          qik[k] = sext8(qi[k / 4], k % 4);
-          qn2 += qik[k] * qik[k];
-        }
-      }
-      int len = 0, qn = 0;
-
-      auto flush = [&]() {
-        for (int m = 0; m < qn; m++) {
-          const int j = qbuf[m * BLK + tid];
-          double xj[D], sj;
-          load_rec<D>(xb, j, xj, sj);
-          const double r2 = dist2_exact<D>(xi, xj, L, hL);
-          if (r2 < list_r2(si, sj, cut, skin)) {
-            if (len < W) nl[(size_t)len * npad + i] = j;
-            len++;
-          }
-        }
-        qn = 0;
-      };
-
-      for (int q = 0; q < nst; q++) {
-        int o[D], cj[D];
-        decode_linked<D>(q, radix, reach, nc, ci, o, cj);
-        int J = 0;
-#pragma unroll
-        for (int k = 0; k < D; k++) J = J * nc + cj[k];
-        float tk[D];
-        int Ci = 0;
-        if (WRAP) {
-#pragma unroll
-          for (int k = 0; k < D; k++) tk[k] = (float)o[k] * lscf - yi[k];
-        } else {
-          Ci = qn2;
-#pragma unroll
-          for (int k = 0; k < D; k++) Ci -= 2 * kQScale * o[k] * qik[k];
-        }
-        const int j0 = __builtin_amdgcn_readfirstlane(cell_start(s, J));
-        const int j1 = __builtin_amdgcn_readfirstlane(cell_start(s, J + 1));
-        for (int jb = j0; jb < j1; jb += BLK) {
-          const int m = min(BLK, j1 - jb);
-          const int mp = (m + UNR - 1) / UNR * UNR;  // staged entries padded with sentinels
-          __syncthreads();
-          if (tid < mp) {
-            if (WRAP) {
-              float4* dst = reinterpret_cast<float4*>(stage + tid * SW);
-              if (tid < m) {
-                const float4* src = reinterpret_cast<const float4*>(s->ycell + (size_t)(jb + tid) * DY);
-#pragma unroll
-                for (int k = 0; k < DY / 4; k++) dst[k] = src[k];
-              } else {
-#pragma unroll
-                for (int k = 0; k < DY / 4; k++) dst[k] = make_float4(1e30f, 1e30f, 1e30f, 1e30f);
-              }
-            } else {
-              int w[4] = {0, 0, 0, 0x3fffffff};  // sentinel: A_j far above any threshold
-              if (tid < m) {
-#pragma unroll
-                for (int k = 0; k < QW; k++) w[k] = s->qc[(size_t)(jb + tid) * 4 + k];
-                int A = 0;
-#pragma unroll
-                for (int k = 0; k < D; k++) {
-                  const int c = sext8(w[k / 4], k % 4) + kQScale * o[k];
-                  A += c * c;
-                }
-                w[3] = A;  // QW <= 3 words of coordinates, then A_j
-              }
-              reinterpret_cast<int4*>(stage)[tid] = make_int4(w[0], w[1], w[2], w[3]);
-            }
-          }
-          __syncthreads();
-          for (int u0 = 0; u0 < mp; u0 += UNR) {
-            unsigned mask = 0;
-            if (WRAP) {
-              float yj[UNR][DY];
-#pragma unroll
-              for (int uu = 0; uu < UNR; uu++) {
-                const float4* src = reinterpret_cast<const float4*>(stage + (u0 + uu) * SW);
-#pragma unroll
-                for (int k = 0; k < DY / 4; k++) {
-                  const float4 v = src[k];
-                  yj[uu][4 * k] = v.x;
-                  yj[uu][4 * k + 1] = v.y;
-                  yj[uu][4 * k + 2] = v.z;
-                  yj[uu][4 * k + 3] = v.w;
-                }
-              }
-#pragma unroll
-              for (int uu = 0; uu < UNR; uu++) {
-                float r2 = 0.0f;
-#pragma unroll
-                for (int k = 0; k < D; k++) {
-                  float dx = fabsf(yj[uu][k] + tk[k]);
-                  dx = fminf(dx, Lf - dx);
-                  r2 = __builtin_fmaf(dx, dx, r2);
-                }
-                mask |= (r2 < rl2f ? 1u : 0u) << uu;
-              }
-            } else {
-              int4 w[UNR];
-#pragma unroll
-              for (int uu = 0; uu < UNR; uu++) w[uu] = reinterpret_cast<const int4*>(stage)[u0 + uu];
-#pragma unroll
-              for (int uu = 0; uu < UNR; uu++) {
-                int dot = __builtin_amdgcn_sdot4(qi[0], w[uu].x, 0, false);
-                if (QW > 1) dot = __builtin_amdgcn_sdot4(qi[QW > 1 ? 1 : 0], w[uu].y, dot, false);
-                if (QW > 2) dot = __builtin_amdgcn_sdot4(qi[QW > 2 ? 2 : 0], w[uu].z, dot, false);
-                mask |= (w[uu].w + Ci - 2 * dot < tq ? 1u : 0u) << uu;
-              }
-            }
-            if (vi && mask) {
-              while (mask) {
-                const int b = __builtin_ctz(mask);
-                mask &= mask - 1;
-                const int j = jb + u0 + b;
-                if (j != i) {
-                  qbuf[qn * BLK + tid] = j;
-                  qn++;
-                }
-              }
-            }
-            if (__any(qn > kQCap - UNR)) flush();
-          }
-        }
-      }
-      flush();
-      if (vi) {
-        s->nlen[i] = len;
-        rowmax = max(rowmax, len);
-      }
-    }
-    rowmax = wave_max_i(rowmax);
-    if ((tid & (kWave - 1)) == 0 && rowmax > 0) {
-      atomicMax(&s->max_row, rowmax);
-      if (rowmax > W) atomicOr(&s->err, ERR_OVERFLOW);
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Verlet-list build, candidate-lane form
+// Bound by VALU and scalar issue: per 256 pair tests one matrix instruction
+// and four sign-bit shifts, the rest is row set-up and listing.  Candidates
+// as ready operands and word-wise listing replaced per-row conversions,
+// operand transposes and a listing walk per home atom (4.4e8 instead of
+// 9.3e8 vector instructions per build): d = 6, N = 262144, 64 atoms per
+// subcell: 2.14 -> 1.30 ms; d = 6, N = 1e5, 24 per subcell: 1.03 -> 0.70;
+// d = 4, N = 65536, 6.6 per subcell (sparse form): 0.43 -> 0.16 ms.
 //
-// Same list, same row order and the same exact FP64 test as k_build; the
-// work is laid out the other way round.  The linked subcells come in rows
-// along the last axis (offsets -1, 0, +1; -2..+2 on half-size subcells, RAD
-// = 2), whose atoms are packed into 64-lane chunks: every lane takes one
-// candidate j, shifts its quantised offsets by the subcell offset (q'_j = q_j
-// + 250 o as int16, |q'| <= 125 + 250 RAD) and forms A_j = |q'_j|^2.  The home atoms i kept for the row are then
-// walked uniformly, their records (q_i as int16 pairs and B_i = |q_i|^2 - T_i)
-// coming through the scalar cache, each test being
-//   |q'_j - q_i|^2 < T_i + T_j  <=>  (T_j - A_j) + q_i.(2 q'_j) > B_i
-// (v_dot2_i32_i16 on int16 pairs), with per-atom threshold shares T that
-// follow the pair's own list radius (set where the records are written).
-// Wrapped systems (n_cell <= 2) test |u_j - u_i|^2 < tq on 16-bit wrapped
-// coordinates against the largest list radius.
-// The ballot of each test is written into lane i of a mask register, so
-// after a chunk lane i holds the 64-bit mask of its surviving candidates.
-// Every NB chunks the lanes turn back into home atoms and run the exact
-// test on their survivors in chunk and lane order, appending to their own
-// rows.
-//
-// A workgroup of G waves takes one home subcell; wave w takes the w-th of G
-// contiguous shares of its atoms (more waves in flight per subcell at the
-// price of repeating the candidate set-up), with no barrier between waves.
+// Systems of n_cell <= 2, where several images of a pair can be in reach
+// along an axis, take k_build_wrap below.
 // ---------------------------------------------------------------------------
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
 typedef _Float16 hv4 __attribute__((ext_vector_type(4)));
 typedef float fv4 __attribute__((ext_vector_type(4)));
 typedef unsigned uv2 __attribute__((ext_vector_type(2)));
-typedef unsigned uv4 __attribute__((ext_vector_type(4)));
-
-// Operands of the matrix-core form of the pair test.  A pair test
-//   S_ij = q_i.(2 q'_j) + C_j - B_i > 0   (C_j = T_j - A_j, B_i = |q_i|^2 - T_i)
-// is read off one entry of the product of a candidate matrix (rows) and a
-// home matrix (columns) over 16 slots:
-//   candidate [2q'_j,0 .. 2q'_j,d-1, 2048, 1, 1, floor(C_j/2048), C_j mod 2048, 0 ..]
-//   home      [-q_i,0 .. -q_i,d-1, floor(B_i/2048), B_i mod 2048, 1/2, -2048, -1, 0 ..]
-// gives 1/2 - S_ij, negative exactly when the test passes.  Every slot is an
-// integer of magnitude <= 2048 or 1/2 (exact in f16: |q| <= 127, |2q'| <=
-// 1254, -3.93e6 <= C < 2^22, |B| < 2^18) and every partial sum is a multiple
-// of 1/2 below 2^23 in magnitude, so the f32 accumulation is exact in any
-// order.
-__device__ inline unsigned pack_h2(_Float16 lo, _Float16 hi) {
-  return (unsigned)__builtin_bit_cast(unsigned short, lo) |
-         ((unsigned)__builtin_bit_cast(unsigned short, hi) << 16);
-}
-// f16 value of int16 half k of a packed word (converted from 16 bits: one
-// instruction, where a conversion from 32 bits goes through f32)
-__device__ inline _Float16 i16_half(int w, int k) {
-  return (_Float16)(short)(k ? (w >> 16) : w);
-}
-// f16 value of a small integer (|v| <= 2048)
-__device__ inline _Float16 small_h(int v) { return (_Float16)(short)v; }
-// the 16 slots as 8 words (word t: slots 2t, 2t + 1)
-__device__ inline void slot_words(const _Float16 (&sl)[16], unsigned (&w)[8]) {
-#pragma unroll
-  for (int t = 0; t < 8; t++) w[t] = pack_h2(sl[2 * t], sl[2 * t + 1]);
-}
-// home slots from the atom's int16 offset words and its term B
-template <int D>
-__device__ inline void home_slots(const int* ow, int B, unsigned (&w)[8]) {
-  _Float16 sl[16];
-#pragma unroll
-  for (int k = 0; k < 16; k++) sl[k] = (_Float16)0;
-#pragma unroll
-  for (int k = 0; k < D; k++) sl[k] = -i16_half(ow[k / 2], k % 2);
-  sl[D] = small_h(B >> 11);
-  sl[D + 1] = small_h(B & 2047);
-  sl[D + 2] = (_Float16)0.5f;
-  sl[D + 3] = (_Float16)(-2048);
-  sl[D + 4] = (_Float16)(-1);
-  slot_words(sl, w);
-}
-// candidate slots from its shifted, doubled offset words and C (an empty
-// lane's C, below -2^22, becomes -2^22: its entries stay negative)
-template <int D>
-__device__ inline void cand_slots(const int* cw, int C, unsigned (&w)[8]) {
-  C = max(C, -4194304);
-  _Float16 sl[16];
-#pragma unroll
-  for (int k = 0; k < 16; k++) sl[k] = (_Float16)0;
-#pragma unroll
-  for (int k = 0; k < D; k++) sl[k] = i16_half(cw[k / 2], k % 2);
-  sl[D] = (_Float16)2048;
-  sl[D + 1] = (_Float16)1;
-  sl[D + 2] = (_Float16)1;
-  sl[D + 3] = small_h(C >> 11);
-  sl[D + 4] = small_h(C & 2047);
-  slot_words(sl, w);
-}
-
-// Uniform loads of the home records go through the scalar cache: read
-// through the constant address space, which tells the compiler that the
-// kernel does not write them (they come from an earlier kernel).
-typedef __attribute__((address_space(4))) const v4i cv4i;
-typedef __attribute__((address_space(4))) const v8i cv8i;
+typedef __attribute__((address_space(4))) const int cint;
 
 // A pointer that is the same in every lane, moved into scalar registers (a
 // pointer read from device memory lands in vector registers otherwise).
@@ -748,19 +475,6 @@ __device__ inline double uniform_dbl(double v) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-// The lane-write intrinsic (v_writelane_b32): returns `old` with lane `ln`
-// replaced by the uniform `val`.
-__device__ int amdgcn_writelane(int val, int ln, int old) __asm("llvm.amdgcn.writelane");
-
-// Wave priority 3, 2, 1, 0 over the four quarters of done/total (uniform).
-__device__ inline void set_prio_by_progress(int done, int total) {
-  const int q = (4 * done) / total;
-  if (q == 0) __builtin_amdgcn_s_setprio(3);
-  else if (q == 1) __builtin_amdgcn_s_setprio(2);
-  else if (q == 2) __builtin_amdgcn_s_setprio(1);
-  else __builtin_amdgcn_s_setprio(0);
-}
-
 // Orders this wave's LDS writes before its later LDS reads (other lanes).
 __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -768,797 +482,757 @@ __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
-// One home subcell of a system that rebuilds, split over G waves: gw (< G)
-// selects this wave's share of the home atoms; msk/cand are the wave's LDS
-// arrays.
-template <int D, int G, bool WR, int RAD = 1, bool MF = false>
-__device__ inline void build_t_tile(SysDev* s, int hc, int gw, unsigned long long* msk, int* cand) {
-  static_assert(RAD == 1 || (RAD == 2 && !WR), "wrapped systems take the 3^d stencil");
-  static_assert(!(MF && WR), "the matrix-core test is for subcells of n_cell >= 3");
-  constexpr int HW = (D + 1) / 2;        // int16 pair words of q
-  // subcell slots of a row along the last axis: offsets -RAD..+RAD (wrapped:
-  // the subcell itself and, for n_cell = 2, the other one; the third slot empty)
-  constexpr int NRS = WR ? 3 : 2 * RAD + 1;
-  constexpr int RW = HW < 4 ? 4 : 8;     // record words read per home atom
-  constexpr int BW = RW - 1;             // word of B = |q|^2
-  constexpr int CB = 4;                  // chunks of a row tested per home-record load
-  constexpr int NB = 8;                  // chunks per exact pass (a multiple of CB)
-  typedef typename std::conditional<RW == 4, v4i, v8i>::type Rec;
-  typedef typename std::conditional<RW == 4, cv4i, cv8i>::type CRec;
-  typedef __attribute__((address_space(4))) const int cint;
-  typedef short short2v __attribute__((ext_vector_type(2)));
-  const int lane = threadIdx.x & 63;
-  // the position in a chunk of the candidate a lane takes: its lane, or for
-  // the matrix-core test (MF) the position whose sign bit lands in bit order
-  // (row 4g + v of candidate block cb = lane / 16: position 16g + 15 - 4cb - v)
-  const int cpos = MF ? 16 * ((lane >> 2) & 3) + 15 - 4 * (lane >> 4) - (lane & 3) : lane;
-  // subcell starts come through the scalar cache (written by an earlier kernel)
-  cint* flat = (cint*)uniform_ptr(s->cell_flat);
-  const int c0h = flat[hc];
-  const int c1h = flat[hc + 1];
-  // this wave's share of the home atoms
-  const int per = (c1h - c0h + G - 1) / G;
-  const int h0 = c0h + gw * per;
-  const int h1 = min(c1h, h0 + per);
-  if (h0 >= h1) return;
-  const int nc = uniform_int(s->ncell), npad = uniform_int(s->npad);
-  const int W = uniform_int(s->width), tq = uniform_int(s->tq), tcull = uniform_int(s->tcull);
-  // sparse subcells (not wrapped): a row's NRS subcells hold 48 atoms or fewer on average
-  const bool sparse = !WR && NRS * uniform_int(s->n) <= 48 * uniform_int(s->ncells);
-  const double* __restrict__ xb = uniform_ptr(s->x[s->xcur]);
-  const int* __restrict__ qc16 = uniform_ptr(s->qc16);
-  HDMD_GLOBAL int* __restrict__ nl = gbl(uniform_ptr(s->nl));
-  const double L = uniform_dbl(s->L), invL = 1.0 / L, hL = uniform_dbl(s->hL);
-  const double cut = uniform_dbl(s->cutoff), skin = uniform_dbl(s->skin);
-  int ci[D - 1], stride[D - 1];
-  int cl;
-  {
-    int u = hc, st = 1;
-    cl = u % nc;
-    u /= nc;
-    st = nc;
-#pragma unroll
-    for (int k = D - 2; k >= 0; k--) {
-      ci[k] = u % nc;
-      u /= nc;
-      stride[k] = st;
-      st *= nc;
-    }
-  }
-  // rows of linked subcells: radix 2 RAD + 1 (offsets -RAD..+RAD; 3 for
-  // subcells of side >= r_l,max, 5 for half-size subcells) or, for n_cell <=
-  // 2, radix n_cell (offsets 0, +1: the deduplicated stencil)
-  const int R = WR ? nc : NRS;
-  int nrow = 1;
-#pragma unroll
-  for (int k = 0; k < D - 1; k++) nrow *= R;
-  // the subcells of a row along the last axis and their offsets in the int16
-  // half of the last axis (n_cell >= 2 RAD + 1 when not wrapped: all distinct)
-  constexpr int lsh = 16 * ((D - 1) % 2);
-  auto lcell = [&](int r) -> int {
-    if (WR) return r == 0 ? cl : (cl == nc - 1 ? 0 : cl + 1);
-    const int c2 = cl + r - RAD;
-    return c2 < 0 ? c2 + nc : (c2 >= nc ? c2 - nc : c2);
-  };
-  auto lvalid = [&](int r) -> bool { return !WR || r == 0 || (r == 1 && R >= 2); };
-  auto lshift = [&](int r) -> int {
-    return WR ? 0 : (int)((unsigned)((kQScale * (r - RAD)) & 0xffff) << lsh);
-  };
-  // base subcell index of a row of linked subcells (offset digits of `row`
-  // in base R over the first d-1 axes, last digit fastest)
-  auto row_base = [&](int row, int (&Dp)[HW], int (&og)[D - 1]) -> int {
-    int P = 0, r = row;
-#pragma unroll
-    for (int k = 0; k < HW; k++) Dp[k] = 0;
-#pragma unroll
-    for (int k = D - 2; k >= 0; k--) {
-      const int o = WR ? r % R : r % R - RAD;
-      r /= R;
-      og[k] = o;
-      int c2 = ci[k] + o;
-      c2 = c2 < 0 ? c2 + nc : (c2 >= nc ? c2 - nc : c2);
-      P += c2 * stride[k];
-      Dp[k / 2] |= ((kQScale * o) & 0xffff) << (16 * (k % 2));
-    }
-    return P;
-  };
-  int rowmax = 0;
-  // home atoms in passes of up to 128: lane l holds atoms hb + l and hb + 64 + l
-  for (int hb = h0; hb < h1; hb += 128) {
-    const int hcnt = uniform_int(min(128, h1 - hb));
-    const bool two = hcnt > 64;
-    const int i0 = hb + lane, i1 = hb + 64 + lane;
-    const bool v0 = lane < hcnt, v1 = lane + 64 < hcnt;
-    const int ii0 = v0 ? i0 : hb, ii1 = v1 ? i1 : hb;
-    int qh0[D], qh1[D];
-    // the row-cull threshold of each home atom (n_cell >= 3: its own reach;
-    // wrapped: r_l,max)
-    const int tc0 = WR ? tcull : qc16[(size_t)ii0 * 8 + 5];
-    const int tc1 = WR ? tcull : qc16[(size_t)ii1 * 8 + 5];
-    auto own_q = [&](int ii, int (&qh)[D]) {
-      const v4i w0 = *reinterpret_cast<const v4i*>(qc16 + (size_t)ii * 8);
-      int w[5] = {w0.x, w0.y, w0.z, w0.w, 0};
-      if (HW > 4) w[4] = qc16[(size_t)ii * 8 + 4];
-#pragma unroll
-      for (int k = 0; k < D; k++) {
-        const int word = w[k / 2];
-        if (WR) {
-          // gap to the other subcell along axis k (n_cell = 2: it touches both
-          // faces), one unit short: L_sc/2 - |u - centre| - 1 in 2^16/L units
-          const int u = (k % 2) ? ((word >> 16) & 0xffff) : (word & 0xffff);
-          const int cc = (k < D - 1 ? ci[k < D - 1 ? k : 0] : cl) * 32768 + 16384;
-          const int y = (int)(short)((u - cc) & 0xffff);
-          qh[k] = max(16384 - abs(y) - 1, 0);
-        } else {
-          qh[k] = (k % 2) ? (word >> 16) : (int)(short)(word & 0xffff);
-        }
-      }
-    };
-    if constexpr (WR) {  // (n_cell >= 3: the offsets come from the record words)
-      own_q(ii0, qh0);
-      own_q(ii1, qh1);
-    }
-    // the lane's own home record (offset words and the home term), from
-    // which the pair tests of n_cell >= 3 systems take each home atom's words
-    // with v_readlane: the records of every wave of a CU (one subcell each)
-    // do not fit the scalar cache.  Wrapped systems, whose waves walk long
-    // runs of one crowded subcell, read them with scalar loads.
-    int ow0[HW + 1], ow1[HW + 1];
-#pragma unroll
-    for (int k = 0; k < HW; k++) {
-      ow0[k] = qc16[(size_t)ii0 * 8 + k];
-      ow1[k] = qc16[(size_t)ii1 * 8 + k];
-    }
-    ow0[HW] = qc16[(size_t)ii0 * 8 + BW];
-    ow1[HW] = qc16[(size_t)ii1 * 8 + BW];
-    int len0 = 0, len1 = 0, nb = 0;
+// The lane-write intrinsic (v_writelane_b32): returns `old` with lane `ln`
+// replaced by the uniform `val`.
+__device__ int amdgcn_writelane(int val, int ln, int old) __asm("llvm.amdgcn.writelane");
 
-    // exact test of the survivors, spread over the lanes.  The survivors of
-    // the pass are listed home atom by home atom (set 0, then set 1; each
-    // atom's in chunk and bit order, the row order) as 16-bit codes (home
-    // atom, chunk, bit) in the free chunk slots after the pass's masks (at
-    // least one: chunks are tested only while nb + CB <= NB - 1), and taken
-    // 64 at a time, one per lane.  In a batch the survivors of one home atom are a
-    // run of consecutive lanes; a passing one goes to the atom's row at its
-    // length so far plus the passing survivors of its run on lower lanes, so
-    // every row takes its pairs in the row order.  (Walking each atom's own
-    // survivors in its lane instead leaves most lanes idle: in a pass only
-    // the atoms near its rows have survivors.)
-    // The nearest image is taken with rint: with n_cell >= 3 the list radius
-    // is at most L/3 (on half-size subcells, at least 5 per axis: 2L/5), so
-    // every pair it can admit has all |dx_k| clear of L/2, where rint and
-    // the definition's shift give the same value bit for bit; pairs with
-    // some |dx_k| near L/2 are beyond the radius either way.
-    static_assert(NB <= 8, "the chunk index fits three bits of a code");
-    auto exact_pass = [&]() {
-      wave_lds_sync();
-      // survivor counts of the lane's two home atoms, and the chunks that
-      // hold any (bit set * NB + b)
-      int c0 = 0, c1 = 0;
-      unsigned ne = 0;
-      for (int b = 0; b < nb; b++) {
-        const int n0 = __builtin_popcountll(msk[b * 128 + lane]);
-        const int n1 = two ? __builtin_popcountll(msk[b * 128 + 64 + lane]) : 0;
-        c0 += n0;
-        c1 += n1;
-        ne |= (n0 ? 1u << b : 0u) | (n1 ? 1u << (NB + b) : 0u);
-      }
-      int p0 = c0, p1 = c1;  // inclusive prefix sums over the lanes
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int u0 = __shfl_up(p0, o), u1 = __shfl_up(p1, o);
-        if (lane >= o) {
-          p0 += u0;
-          p1 += u1;
-        }
-      }
-      const int S0 = __shfl(p0, 63), S = S0 + __shfl(p1, 63);
-      // first list index and count of each atom's survivors, packed
-      // (index < 7 * 64 * 128 < 2^16, count <= 7 * 64)
-      const unsigned r0 = ((unsigned)(p0 - c0) << 16) | (unsigned)c0;
-      const unsigned r1 = ((unsigned)(S0 + p1 - c1) << 16) | (unsigned)c1;
-      // Survivors spread evenly over the lanes (dense subcells and long rows
-      // in d <= 4: the largest lane count within a few times the mean) are
-      // walked lane by lane, each lane its own atoms' (set 0, then set 1;
-      // chunk and bit order), which needs no listing.  (In higher d a pass's
-      // rows are a small part of the stencil and its survivors crowd into
-      // few atoms; the walk is not compiled there.)
-      if (D <= 4 && 11 * wave_max_i(c0 + c1) <= S) {
-        unsigned long long m = 0;
-        int cb = 0, cur = -1, i = 0;
-        double xi[D], si;  // own record, loaded when the walk reaches its set
-        while (true) {
-          if (m == 0) {
-            if (ne == 0) break;
-            cb = __builtin_ctz(ne);
-            ne &= ne - 1;
-            const int set = cb >= NB ? 1 : 0;
-            m = msk[(cb % NB) * 128 + set * 64 + lane];
-            if (set != cur) {
-              cur = set;
-              i = set ? i1 : i0;
-              load_rec<D>(xb, set ? ii1 : ii0, xi, si);
-            }
-          }
-          const int j = cand[(cb % NB) * 64 + __builtin_ctzll(m)];
-          m &= m - 1;
-          double xj[D], sj;
-          load_rec<D>(xb, j, xj, sj);
-          if (j != i) {
-            double r2 = 0.0;
-#pragma unroll
-            for (int k = 0; k < D; k++) {
-              const double dx = WR ? min_image(xj[k] - xi[k], L, hL)
-                                   : near_image(xj[k] - xi[k], L, invL);
-              r2 = __builtin_fma(dx, dx, r2);
-              __builtin_amdgcn_sched_barrier(0);  // one axis at a time: few live registers
-            }
-            if (r2 < list_r2(si, sj, cut, skin)) {
-              const int len = cur ? len1 : len0;
-              if (len < W) nl[(size_t)len * npad + i] = j;
-              if (cur) len1 = len + 1;
-              else len0 = len + 1;
-            }
-          }
-        }
-        wave_lds_sync();
-        nb = 0;
-        return;
-      }
-      unsigned short* code = reinterpret_cast<unsigned short*>(msk + nb * 128);
-      const int cap = 512 * (NB - nb);
-      // each lane's walk over its survivors (set 0, then set 1; chunk and
-      // bit order), resumed round after round: list index e, current chunk
-      // cb and its remaining bits m
-      int e = (int)(r0 >> 16), cb = 0;
-      unsigned long long m = 0;
-      for (int e0 = 0; e0 < S; e0 += cap) {
-        const int e1 = min(S, e0 + cap);
-        // the codes of list entries e0 .. e1 - 1
-        while (e < e1) {
-          if (m == 0) {
-            if (ne == 0) break;
-            const int nx = __builtin_ctz(ne);
-            ne &= ne - 1;
-            if (nx >= NB && cb < NB) e = (int)(r1 >> 16);  // on to set 1's list entries
-            cb = nx;
-            m = msk[(cb % NB) * 128 + (cb >= NB ? 64 : 0) + lane];
-            if (e >= e1) break;
-          }
-          // up to two codes per trip (the trips are set by the lane with most)
-          const int hc = (((cb >= NB ? 64 : 0) + lane) << 9) | ((cb % NB) << 6);
-          code[e - e0] = (unsigned short)(hc | __builtin_ctzll(m));
-          m &= m - 1;
-          e++;
-          if (m != 0 && e < e1) {
-            code[e - e0] = (unsigned short)(hc | __builtin_ctzll(m));
-            m &= m - 1;
-            e++;
-          }
-        }
-        wave_lds_sync();
-        for (int t = e0; t < e1; t += 64) {
-          const bool valid = t + lane < e1;
-          const int cd = valid ? (int)code[t + lane - e0] : 0;
-          const int h = cd >> 9;
-          const int i = hb + h;
-          const int j = valid ? cand[((cd >> 6) & 7) * 64 + (cd & 63)] : i;
-          // the lanes below this one in its run (the run's head: the highest
-          // lane at or below it whose home atom differs from the lane
-          // below's), and the atom's row length so far
-          const int hp = __shfl_up(h, 1);
-          const unsigned long long H = __ballot(lane == 0 || hp != h);
-          const unsigned long long below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-          const int head = 63 - __builtin_clzll(H & (below | (1ull << lane)));
-          const unsigned long long run = below & ~((1ull << head) - 1);
-          const int la = __shfl(len0, h & 63), lb = __shfl(len1, h & 63);
-          const int base = h >= 64 ? lb : la;
-          __builtin_amdgcn_sched_barrier(0);
-          double xi[D], si, xj[D], sj;
-          load_rec<D>(xb, i, xi, si);
-          load_rec<D>(xb, j, xj, sj);
-          bool pass = false;
-          if (j != i) {
-            double r2 = 0.0;
-#pragma unroll
-            for (int k = 0; k < D; k++) {
-              const double dx = WR ? min_image(xj[k] - xi[k], L, hL)
-                                   : near_image(xj[k] - xi[k], L, invL);
-              r2 = __builtin_fma(dx, dx, r2);
-              __builtin_amdgcn_sched_barrier(0);  // one axis at a time: few live registers
-            }
-            pass = r2 < list_r2(si, sj, cut, skin);
-          }
-          const unsigned long long P = __ballot(pass);
-          const int pos = base + __builtin_popcountll(P & run);
-          if (pass && pos < W) nl[(size_t)pos * npad + i] = j;
-          // the lane's own atoms take their passing survivors of the batch
-          auto add = [&](unsigned rs, int& len) {
-            const int st = (int)(rs >> 16), c = (int)(rs & 0xffff);
-            const int lo = max(st - t, 0), hi = min(st + c - t, 64);
-            if (lo < hi) {
-              const unsigned long long mk =
-                  (hi == 64 ? ~0ull : ((1ull << hi) - 1)) & ~((1ull << lo) - 1);
-              len += __builtin_popcountll(P & mk);
-            }
-          };
-          add(r0, len0);
-          add(r1, len1);
-        }
-        wave_lds_sync();  // the codes are read before the next round lists over them
-      }
-      nb = 0;
-    };
-
-    // ballots of the kept home atoms of one set against `nch` chunks, four
-    // home atoms per group of scalar loads (a short last group repeats its
-    // last atom); lane h of m[c] receives home atom h's ballot for chunk c
-    auto test_set = [&](unsigned long long km, const int (&ow)[HW + 1], int rb, int nch,
-                        const int (&cw)[CB][HW], const int (&tA)[CB], unsigned (&mlo)[CB],
-                        unsigned (&mhi)[CB]) {
-      while (km) {
-        int hh[4];
-        hh[0] = __builtin_ctzll(km);
-        km &= km - 1;
-#pragma unroll
-        for (int u = 1; u < 4; u++) {
-          hh[u] = km ? __builtin_ctzll(km) : hh[u - 1];
-          km &= km - 1;
-        }
-        int r[4][HW + 1];
-#pragma unroll
-        for (int u = 0; u < 4; u++) {
-          if constexpr (WR) {
-            const Rec w = *(CRec*)(qc16 + (size_t)(rb + hh[u]) * 8);
-#pragma unroll
-            for (int k = 0; k < HW; k++) r[u][k] = w[k];
-          } else {
-#pragma unroll
-            for (int k = 0; k <= HW; k++) r[u][k] = __builtin_amdgcn_readlane(ow[k], hh[u]);
-          }
-        }
-#pragma unroll
-        for (int c = 0; c < CB; c++) {
-          if (c >= nch) break;
-          unsigned long long m[4];
-          if (WR) {
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-              // |u_j - u_i|^2 over 16-bit wrapped differences (saturating: far
-              // pairs clamp at INT_MAX) against the lane's threshold
-              int acc = 0;
-#pragma unroll
-              for (int k = 0; k < HW; k++) {
-                const short2v dq = __builtin_bit_cast(short2v, cw[c][k]) -
-                                   __builtin_bit_cast(short2v, (int)r[u][k]);
-                acc = __builtin_amdgcn_sdot2(dq, dq, acc, true);
-              }
-              m[u] = __ballot(acc < tA[c]);
-            }
-          } else {
-            // the four home atoms' products word by word, so that each dot
-            // product's result is not needed by the next instruction; the
-            // first in the three-operand form, so the lane's threshold needs
-            // no copy into an accumulator register
-            int acc[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++)
-              asm("v_dot2_i32_i16 %0, %1, %2, %3"
-                  : "=v"(acc[u])
-                  : "s"((int)r[u][0]), "v"(cw[c][0]), "v"(tA[c]));
-#pragma unroll
-            for (int k = 1; k < HW; k++)
-#pragma unroll
-              for (int u = 0; u < 4; u++)
-                acc[u] = __builtin_amdgcn_sdot2(__builtin_bit_cast(short2v, (int)r[u][k]),
-                                                __builtin_bit_cast(short2v, cw[c][k]), acc[u],
-                                                false);
-#pragma unroll
-            for (int u = 0; u < 4; u++) m[u] = __ballot(acc[u] > r[u][HW]);
-          }
-#pragma unroll
-          for (int u = 0; u < 4; u++) {
-            mlo[c] = (unsigned)amdgcn_writelane((int)(unsigned)m[u], hh[u], (int)mlo[c]);
-            mhi[c] = (unsigned)amdgcn_writelane((int)(unsigned)(m[u] >> 32), hh[u], (int)mhi[c]);
-          }
-        }
-      }
-    };
-
-    // home atoms that can reach a row: gap to the neighbouring faces along
-    // the first d-1 axes, one quantisation unit short per axis
-    // the int16 offset of axis k from a home record's offset words (n_cell >= 3)
-    auto oq = [](const int (&w)[HW + 1], int k) -> int {
-      return (k % 2) ? (w[k / 2] >> 16) : (int)(short)(w[k / 2] & 0xffff);
-    };
-    auto row_keep = [&](const int (&og)[D - 1], unsigned long long& keep0,
-                        unsigned long long& keep1) {
-      int S0 = 0, S1 = 0;
-#pragma unroll
-      for (int k = 0; k < D - 1; k++) {
-        const int o = og[k];
-        int g0, g1;
-        if (WR) {
-          g0 = o ? qh0[k] : 0;
-          g1 = o ? qh1[k] : 0;
-        } else if (RAD == 1) {
-          g0 = (kQScale / 2) - o * oq(ow0, k) - 1;
-          g1 = (kQScale / 2) - o * oq(ow1, k) - 1;
-          g0 = (o == 0 || g0 < 0) ? 0 : g0;
-          g1 = (o == 0 || g1 < 0) ? 0 : g1;
-        } else {
-          // the near face of a subcell |o| away: (|o| - 1/2) sides from the centre
-          const int ao = o < 0 ? -o : o;
-          const int face = (kQScale / 2) * (2 * ao - 1);
-          g0 = face - (o > 0 ? oq(ow0, k) : -oq(ow0, k)) - 1;
-          g1 = face - (o > 0 ? oq(ow1, k) : -oq(ow1, k)) - 1;
-          g0 = (o == 0 || g0 < 0) ? 0 : g0;
-          g1 = (o == 0 || g1 < 0) ? 0 : g1;
-        }
-        S0 += g0 * g0;
-        S1 += g1 * g1;
-      }
-      keep0 = __ballot(v0 && S0 < tc0);
-      keep1 = two ? __ballot(v1 && S1 < tc1) : 0ull;
-    };
-    // candidate tt of a row of T atoms whose subcell slot r (stencil order)
-    // holds the candidates from cum[r-1] on, atom tt + db[0] + ... + db[r]:
-    // its record (an in-range atom for an empty lane) shifted by the subcell
-    // offset as packed int16 adds; returns the atom, or -1 for an empty lane.
-    // (The atom is a sum of increments rather than a pick among run bases:
-    // the compiler turns such a pick into an indexed load from scratch.)
-    auto cand_words = [&](int tt, int T, const int (&db)[NRS], const int (&cum)[NRS],
-                          const int (&Dp)[HW], int (&cwc)[HW], int& tAc)
-        __attribute__((always_inline)) -> int {
-      const bool valid = tt < T;
-      int j = tt + db[0], lastv = lshift(0);
-#pragma unroll
-      for (int r = 1; r < NRS; r++) {
-        const bool past = tt >= cum[r - 1];
-        j += past ? db[r] : 0;
-        lastv = past ? lshift(r) : lastv;
-      }
-      const HDMD_GLOBAL int* src = gbl(qc16 + (size_t)(valid ? j : hb) * 8);
-      if (WR) {
-#pragma unroll
-        for (int k = 0; k < HW; k++) cwc[k] = src[k];
-        tAc = valid ? tq : -1;  // the lane's threshold; none for an empty lane
-      } else {
-        int A = 0;
-#pragma unroll
-        for (int k = 0; k < HW; k++) {
-          const short2v q2 = __builtin_bit_cast(short2v, src[k]);
-          const short2v o2 = __builtin_bit_cast(short2v, Dp[k] + (k == (D - 1) / 2 ? lastv : 0));
-          const short2v r2 = q2 + o2;
-          A = __builtin_amdgcn_sdot2(r2, r2, A, false);
-          cwc[k] = __builtin_bit_cast(int, r2 + r2);
-        }
-        tAc = valid ? src[6] - A : -0x3fffffff;  // never passes for an empty lane
-      }
-      return valid ? j : -1;
-    };
-    // (T_j - A_j) + q_i.(2 q'_j) > |q_i|^2 - T_i  <=>  |q'_j - q_i|^2 < T_i + T_j
-    // for the kept home atoms of both sets against nch chunks (LDS slots nb..)
-    // The matrix-core form of the same tests (MF).  Per chunk and block of
-    // 16 kept home atoms of a set (columns, compacted; their slots staged in
-    // LDS in the chunk slots whose masks this call writes last), one
-    // 16x16x16 product per block of 16 candidates (rows): entry 1/2 - S_ij,
-    // whose sign bit is the test's outcome.  Lane l of the chunk holds the
-    // candidate at position cpos(l), so that the sign bits of the four
-    // result registers of the four candidate blocks, shifted in order into
-    // one word per lane, come out in position order: lane 16g + j holds home
-    // column j's bits of positions 16g .. 16g + 15.  A half swap per block,
-    // and a select between the two blocks of a pair, join them into the two
-    // 32-bit halves of each home atom's 64-bit mask (lane r: positions 0..31
-    // of compacted home r of the pair, lane 32 + r: positions 32..63), which
-    // are scattered at the end to the home atoms' slots (all others zero).
-    auto test_chunks_mf = [&](unsigned long long keep0, unsigned long long keep1, int nch,
-                              const int (&cw)[CB][HW], const int (&tA)[CB]) {
-      constexpr int EW = 8;  // staged words per home atom: all 16 slots
-      static_assert(CB * 128 * 8 >= 2 * 64 * 4 * EW, "two sets of staged home slots fit CB chunk slots");
-      unsigned* stg = reinterpret_cast<unsigned*>(msk + nb * 128);  // free: nb + CB <= NB - 1
-      const int nk0 = __builtin_popcountll(keep0), nk1 = __builtin_popcountll(keep1);
-      // stage the kept atoms' slots at their rank; returns, in lanes j and
-      // j + 32, the home lanes of compacted rows j (first) and 32 + j
-      // (second): kept atoms go to their rank, the others after them, a
-      // permutation of the lanes
-      auto stage = [&](unsigned long long km, int nk, const int (&ow)[HW + 1], unsigned* st, int& s0,
-                       int& s1) {
-        const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(km >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((unsigned)km, 0u));
-        const bool kept = (km >> lane) & 1ull;
-        if (kept) {
-          // (converted here, each time: hoisted out of the row loop, the
-          // slots of both sets would hold 16 registers through it)
-          int owl[HW + 1];
-#pragma unroll
-          for (int k = 0; k <= HW; k++) {
-            owl[k] = ow[k];
-            asm volatile("" : "+v"(owl[k]));
-          }
-          unsigned w[8];
-          home_slots<D>(owl, owl[HW], w);
-          uv4* e = reinterpret_cast<uv4*>(st + EW * rank);
-          e[0] = uv4{w[0], w[1], w[2], w[3]};
-          e[1] = uv4{w[4], w[5], w[6], w[7]};
-        }
-        const int dst = kept ? rank : nk + (lane - rank);
-        const unsigned src = (unsigned)__builtin_amdgcn_ds_permute(dst * 4, lane);
-        const auto sw = __builtin_amdgcn_permlane32_swap(src, src, false, false);
-        s0 = (int)sw[0];
-        s1 = (int)sw[1];
-      };
-      int sa0, sb0, sa1 = 0, sb1 = 0;
-      stage(keep0, nk0, ow0, stg, sa0, sb0);
-      if (nk1 > 0) stage(keep1, nk1, ow1, stg + 64 * EW, sa1, sb1);
-      wave_lds_sync();
-      const int q = lane >> 4;
-      // one set's home blocks 2p and 2p + 1 (compacted homes 32p ..) against
-      // the chunk's candidate blocks X: lane r < 32 receives positions 0..31
-      // of home 32p + r, lane 32 + r its positions 32..63
-      auto mf_pair = [&](const unsigned* st, int nk, int p, const hv4 (&X)[4])
-          __attribute__((always_inline)) -> unsigned {
-        unsigned R[2] = {0u, 0u};
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-          const int b = 2 * p + h;
-          if (16 * b >= nk) break;
-          const uv2* e = reinterpret_cast<const uv2*>(st + EW * (16 * b + (lane & 15)));
-          const hv4 Hb = __builtin_bit_cast(hv4, e[q]);
-          unsigned P = 0u;
-#pragma unroll
-          for (int cb = 0; cb < 4; cb++) {
-            const fv4 zero = {};
-            const fv4 e4 = __builtin_amdgcn_mfma_f32_16x16x16f16(X[cb], Hb, zero, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; v++) P = __builtin_amdgcn_alignbit(P, __float_as_uint(e4[v]), 31u);
-          }
-          // lanes j, 16 + j: positions 0..31 of home j; lanes 32 + j, 48 + j: 32..63
-          const auto sw = __builtin_amdgcn_permlane16_swap(P, P, false, false);
-          R[h] = (unsigned)sw[0] | ((unsigned)sw[1] << 16);
-        }
-        return (lane & 16) ? R[1] : R[0];
-      };
-      unsigned r00[CB], r01[CB], r10[CB], r11[CB];  // set, pair of home blocks
-#pragma unroll
-      for (int c = 0; c < CB; c++) {
-        r00[c] = r01[c] = r10[c] = r11[c] = 0u;
-        if (c >= nch) continue;
-        unsigned w[8];
-        cand_slots<D>(cw[c], tA[c], w);
-        // lane group g of block X[cb] takes slot words 2g, 2g + 1 of the
-        // candidate in lane 16 cb + (lane mod 16): a 4x4 transpose of lane
-        // groups and word pairs in two rounds of half swaps
-        unsigned W[4][2];
-#pragma unroll
-        for (int t = 0; t < 2; t++) {
-#pragma unroll
-          for (int g = 0; g < 4; g++) W[g][t] = w[2 * g + t];
-#pragma unroll
-          for (int g = 0; g < 2; g++) {
-            const auto sw = __builtin_amdgcn_permlane32_swap(W[g][t], W[g + 2][t], false, false);
-            W[g][t] = sw[0];
-            W[g + 2][t] = sw[1];
-          }
-#pragma unroll
-          for (int g = 0; g < 4; g += 2) {
-            const auto sw = __builtin_amdgcn_permlane16_swap(W[g][t], W[g + 1][t], false, false);
-            W[g][t] = sw[0];
-            W[g + 1][t] = sw[1];
-          }
-        }
-        hv4 X[4];
-#pragma unroll
-        for (int g = 0; g < 4; g++) X[g] = __builtin_bit_cast(hv4, uv2{W[g][0], W[g][1]});
-        if (nk0 > 0) r00[c] = mf_pair(stg, nk0, 0, X);
-        if (nk0 > 32) r01[c] = mf_pair(stg, nk0, 1, X);
-        if (nk1 > 0) r10[c] = mf_pair(stg + 64 * EW, nk1, 0, X);
-        if (nk1 > 32) r11[c] = mf_pair(stg + 64 * EW, nk1, 1, X);
-      }
-      // (the stage has been read: one wave's LDS operations complete in order)
-      unsigned* mw = reinterpret_cast<unsigned*>(msk);
-      const int hf = lane >> 5, rj = lane & 31;
-#pragma unroll
-      for (int c = 0; c < CB; c++) {
-        if (c >= nch) continue;
-        const int base = (nb + c) * 128;
-        msk[base + lane] = 0ull;
-        if (two) msk[base + 64 + lane] = 0ull;
-        if (rj < nk0) mw[2 * (base + sa0) + hf] = r00[c];
-        if (32 + rj < nk0) mw[2 * (base + sb0) + hf] = r01[c];
-        if (rj < nk1) mw[2 * (base + 64 + sa1) + hf] = r10[c];
-        if (32 + rj < nk1) mw[2 * (base + 64 + sb1) + hf] = r11[c];
-      }
-      nb += nch;
-    };
-    auto test_chunks = [&](unsigned long long keep0, unsigned long long keep1, int nch,
-                           const int (&cw)[CB][HW], const int (&tA)[CB]) {
-      if constexpr (MF) {
-        test_chunks_mf(keep0, keep1, nch, cw, tA);
-        return;
-      }
-      unsigned m0lo[CB], m0hi[CB], m1lo[CB], m1hi[CB];
-#pragma unroll
-      for (int c = 0; c < CB; c++) m0lo[c] = m0hi[c] = m1lo[c] = m1hi[c] = 0u;
-      test_set(keep0, ow0, hb, nch, cw, tA, m0lo, m0hi);
-      test_set(keep1, ow1, hb + 64, nch, cw, tA, m1lo, m1hi);
-#pragma unroll
-      for (int c = 0; c < CB; c++) {
-        if (c < nch) {
-          msk[(nb + c) * 128 + lane] = ((unsigned long long)m0hi[c] << 32) | m0lo[c];
-          msk[(nb + c) * 128 + 64 + lane] = ((unsigned long long)m1hi[c] << 32) | m1lo[c];
-        }
-      }
-      nb += nch;
-    };
-
-    // one row of linked subcells, walked chunk by chunk
-    auto do_row = [&](int row) __attribute__((always_inline)) {
-      // A SIMD issues for its oldest waves first, so without this the waves
-      // of a launch finish one by one and the last ones run alone, their
-      // latencies exposed.  A wave's priority falls as it gets through its
-      // rows: the waves that lag get the issue slots, and those of a SIMD
-      // finish together.
-      set_prio_by_progress(row, nrow);
-      // The row's set-up is redone for each round of CB chunks, after any
-      // pass of exact tests: nothing of it stays live across that pass.
-      for (int k0 = 0;; k0 += CB * 64) {
-        if (nb + CB > NB - 1) exact_pass();
-        int Dp[HW], og[D - 1];
-        const int P = row_base(row, Dp, og);
-        unsigned long long keep0, keep1;
-        row_keep(og, keep0, keep1);
-        if ((keep0 | keep1) == 0) return;
-        // the row's subcells in stencil order: (-RAD..+RAD) or, wrapped, (0, +1)
-        // (all scalar loads issued before the first is used)
-        int f[2 * NRS];
-#pragma unroll
-        for (int r = 0; r < NRS; r++) {
-          f[2 * r] = lvalid(r) ? flat[P + lcell(r)] : 0;
-          f[2 * r + 1] = lvalid(r) ? flat[P + lcell(r) + 1] : 0;
-        }
-        int db[NRS], cum[NRS], T = 0;
-#pragma unroll
-        for (int r = 0; r < NRS; r++) {
-          // run r starts at atom f[2r] and takes candidates T.. (T before it)
-          db[r] = r == 0 ? f[0] : (f[2 * r] - f[2 * r - 2]) - (cum[r - 1] - (r >= 2 ? cum[r - 2] : 0));
-          T += f[2 * r + 1] - f[2 * r];
-          cum[r] = T;
-        }
-        if (k0 >= T) return;
-        const int nch = min(CB, (T - k0 + 63) / 64);
-        int cw[CB][HW], tA[CB];
-#pragma unroll
-        for (int c = 0; c < CB; c++) {
-          if (c >= nch) continue;
-          cand[(nb + c) * 64 + cpos] = cand_words(k0 + c * 64 + cpos, T, db, cum, Dp, cw[c], tA[c]);
-        }
-        test_chunks(keep0, keep1, nch, cw, tA);
-      }
-    };
-
-    if (sparse) {
-      // CB consecutive rows that each fit one chunk share a round of
-      // candidate loads and tests (the loads of all CB rows are in flight
-      // together), tested against the home atoms kept by any of them; the
-      // chunks stay in row order, so the lists and their order are those of
-      // the row-by-row walk, which a group with a longer row takes instead
-      for (int row = 0; row < nrow; row += CB) {
-        set_prio_by_progress(row, nrow);
-        if (nb + CB > NB - 1) exact_pass();
-        // in phases, so that the scalar loads of all CB rows and then their
-        // candidate loads are issued before any of them is waited for
-        int P[CB], Dps[CB][HW];
-        unsigned long long k0m = 0, k1m = 0;
-#pragma unroll
-        for (int c = 0; c < CB; c++) {
-          const bool rv = row + c < nrow;
-          int og[D - 1];
-          P[c] = row_base(rv ? row + c : row, Dps[c], og);
-          unsigned long long kp0, kp1;
-          row_keep(og, kp0, kp1);
-          k0m |= rv ? kp0 : 0ull;
-          k1m |= rv ? kp1 : 0ull;
-        }
-        if ((k0m | k1m) == 0) continue;
-        int fl[CB][2 * NRS];
-#pragma unroll
-        for (int c = 0; c < CB; c++) {
-#pragma unroll
-          for (int r = 0; r < NRS; r++) {
-            fl[c][2 * r] = flat[P[c] + lcell(r)];
-            fl[c][2 * r + 1] = flat[P[c] + lcell(r) + 1];
-          }
-        }
-        int tmx = 0, Tr[CB];
-#pragma unroll
-        for (int c = 0; c < CB; c++) {
-          Tr[c] = 0;
-#pragma unroll
-          for (int r = 0; r < NRS; r++) Tr[c] += fl[c][2 * r + 1] - fl[c][2 * r];
-          tmx = max(tmx, Tr[c]);
-        }
-        if (tmx > 64) {
-#pragma unroll 1
-          for (int c = 0; c < CB && row + c < nrow; c++) do_row(row + c);
-          continue;
-        }
-        int rw[CB][HW + 1];  // the candidate's offset words and its threshold share
-        int jj[CB], lv[CB];
-#pragma unroll
-        for (int c = 0; c < CB; c++) {
-          const int T = row + c < nrow ? Tr[c] : 0;
-          int j = fl[c][0] + cpos, acc = fl[c][1] - fl[c][0];
-          lv[c] = lshift(0);
-#pragma unroll
-          for (int r = 1; r < NRS; r++) {
-            if (cpos >= acc) {
-              j = fl[c][2 * r] - acc + cpos;
-              lv[c] = lshift(r);
-            }
-            acc += fl[c][2 * r + 1] - fl[c][2 * r];
-          }
-          jj[c] = cpos < T ? j : -1;
-          const HDMD_GLOBAL int* src = gbl(qc16 + (size_t)(cpos < T ? j : hb) * 8);
-#pragma unroll
-          for (int k = 0; k < HW; k++) rw[c][k] = src[k];
-          rw[c][HW] = src[6];
-        }
-        int cw[CB][HW], tA[CB];
-#pragma unroll
-        for (int c = 0; c < CB; c++) {
-          int A = 0;
-#pragma unroll
-          for (int k = 0; k < HW; k++) {
-            const short2v q2 = __builtin_bit_cast(short2v, rw[c][k]);
-            const short2v o2 =
-                __builtin_bit_cast(short2v, Dps[c][k] + (k == (D - 1) / 2 ? lv[c] : 0));
-            const short2v r2 = q2 + o2;
-            A = __builtin_amdgcn_sdot2(r2, r2, A, false);
-            cw[c][k] = __builtin_bit_cast(int, r2 + r2);
-          }
-          tA[c] = jj[c] >= 0 ? rw[c][HW] - A : -0x3fffffff;  // never passes for an empty lane
-          cand[(nb + c) * 64 + cpos] = jj[c];
-        }
-        test_chunks(k0m, k1m, CB, cw, tA);
-      }
-    } else {
-      for (int row = 0; row < nrow; row++) do_row(row);
-    }
-    exact_pass();
-    if (v0) {
-      s->nlen[i0] = len0;
-      rowmax = max(rowmax, len0);
-    }
-    if (v1) {
-      s->nlen[i1] = len1;
-      rowmax = max(rowmax, len1);
-    }
-  }
-  rowmax = wave_max_i(rowmax);
-  if (lane == 0 && rowmax > 0) {
-    atomicMax(&s->max_row, rowmax);
-    if (rowmax > W) atomicOr(&s->err, ERR_OVERFLOW);
-  }
+// the lanes below this one whose bit is set in m
+__device__ inline int rank_in(unsigned long long m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                        __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
-template <int D, int G, bool WR, int RAD = 1, bool MF = false>
-__global__ __launch_bounds__(64 * G, G >= 8 ? 16 / G : 8) void k_build_t(KArgs a) {
-  // per wave: survivor masks of up to 128 home atoms and the candidates of 8 chunks
-  __shared__ unsigned long long msk_all[G][8 * 128];
-  __shared__ int cand_all[G][8 * 64];
+// Inclusive prefix sum over the wave's lanes.
+__device__ inline int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr 1, 2, 4, 8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast 15 to rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast 31 to rows 2, 3
+  return v;
+}
+
+// One wave's survivors on their way to the exact test.  The sign bits of the
+// matrix products come as words of up to 32 bits, most of them zero; the
+// others are queued (push), and 64 queued words at a time, one per lane, are
+// expanded into codes, one per survivor (expand), so that neither step loops
+// over the mostly empty lanes.  Words and codes keep their order: the
+// survivors of one home atom come in its candidates' order whatever other
+// home atoms share the wave.
+constexpr int kWordCap = 192, kCodeCap = 192;
+template <typename TAG>
+struct SurvivorLds {
+  unsigned word[kWordCap];
+  unsigned code[kCodeCap];
+  TAG tag[kWordCap];
+};
+template <typename TAG>
+struct Survivors {
+  SurvivorLds<TAG>* q;
+  int nw, nq;
+
+  // queues the lanes' non-zero words (bit 31 - p of a word stands for the
+  // code 32 tag + p); the caller sees to it that at most kWordCap - 64 are
+  // queued before
+  __device__ __attribute__((always_inline)) void push(unsigned w, unsigned tag) {
+    const unsigned long long any = __ballot(w != 0u);
+    if (w != 0u) {
+      const int at = nw + rank_in(any);
+      q->word[at] = w;
+      q->tag[at] = (TAG)tag;
+    }
+    nw += __builtin_popcountll(any);
+  }
+  // expands the first queued words (up to 64) into codes, as many words as
+  // the code list has room for; true when it took all of them
+  __device__ __attribute__((always_inline)) bool expand(int lane) {
+    wave_lds_sync();
+    const int n = min(nw, 64);
+    unsigned w = lane < n ? q->word[lane] : 0u;
+    const unsigned tag = 32u * (unsigned)q->tag[lane];
+    const int c = __builtin_popcount(w), e = wave_scan(c);
+    const unsigned long long fit = __ballot(lane < n && nq + e <= kCodeCap);
+    const int na = __builtin_popcountll(fit);
+    if (!((fit >> lane) & 1ull)) w = 0u;
+    int at = nq + e - c;
+    while (w) {
+      const int p = __builtin_clz(w);
+      w &= ~(0x80000000u >> p);
+      q->code[at++] = tag + p;
+    }
+    if (na > 0) nq += __builtin_amdgcn_readlane(e, na - 1);
+    // the words left move to the front
+    const int rest = nw - na;
+    unsigned wl[kWordCap / 64];
+    TAG tl[kWordCap / 64];
+#pragma unroll
+    for (int u = 0; u < kWordCap / 64; u++) {
+      const int from = min(na + 64 * u + lane, kWordCap - 1);
+      wl[u] = q->word[from];
+      tl[u] = q->tag[from];
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int u = 0; u < kWordCap / 64; u++) {
+      if (64 * u + lane < rest) {
+        q->word[64 * u + lane] = wl[u];
+        q->tag[64 * u + lane] = tl[u];
+      }
+    }
+    nw = rest;
+    return na == n;
+  }
+  // hands the codes to `batch(code, valid)` 64 at a time, one per lane:
+  // whole batches only, or, with all, every code and word there is
+  template <typename F>
+  __device__ __attribute__((always_inline)) void drain(int lane, bool all, F batch) {
+    for (;;) {
+      wave_lds_sync();
+      const bool last = all && nw == 0;
+      int t = 0;
+      for (; t + 64 <= nq || (last && t < nq); t += 64) {
+        const bool valid = t + lane < nq;
+        batch(q->code[min(t + lane, kCodeCap - 1)], valid);
+      }
+      // the codes left move to the front
+      const int rest = max(nq - t, 0);
+      const unsigned c0 = q->code[min(t + lane, kCodeCap - 1)];
+      wave_lds_sync();
+      if (lane < rest) q->code[lane] = c0;
+      nq = rest;
+      if (nw >= 64 || (all && nw > 0)) expand(lane);
+      else break;
+    }
+  }
+};
+
+// Appends a batch's passing pairs to their rows: each sets its bit in its
+// home atom's LDS word, whose bits below its own are the pairs before it in
+// the batch.  Every lane takes the new length of its own home atoms.
+struct RowAppend {
+  unsigned long long* hit;  // per home atom
+  HDMD_GLOBAL int* nl;
+  int npad, W;
+  __device__ __attribute__((always_inline)) void operator()(int lane, bool two, bool pass, int h, int i,
+                                                            int j, int& len0, int& len1) const {
+    if (pass) atomicOr(hit + h, 1ull << lane);
+    const int la = __shfl(len0, h & 63), lb = two ? __shfl(len1, h & 63) : 0;
+    wave_lds_sync();
+    if (pass) {
+      const int pos = (h >= 64 ? lb : la) + rank_in(hit[h]);
+      if (pos < W) nl[(size_t)pos * npad + i] = j;
+    }
+    len0 += __builtin_popcountll(hit[lane]);
+    if (two) len1 += __builtin_popcountll(hit[64 + lane]);
+    wave_lds_sync();
+    hit[lane] = 0ull;
+    if (two) hit[64 + lane] = 0ull;
+    wave_lds_sync();
+  }
+};
+
+// LDS of one wave of the matrix-core build: under 10240 bytes with the 3^d
+// stencil, so that 16 such waves share a CU, four per SIMD.
+constexpr int kBuildTags = 16;  // segments of candidate blocks the codes may refer to
+template <int RAD>
+struct BuildLds {
+  static constexpr int SW = 6 + 2 * (2 * RAD + 1);  // words per staged home atom
+  uv2 stage[128 * SW / 2];         // home slots 4..15, then slots 0..3 per last-axis offset
+  unsigned long long hit[64 * 2];  // RowAppend
+  SurvivorLds<unsigned short> q;
+  int base[kBuildTags][16];        // first atom of each candidate block of a segment
+  unsigned char hid[128];          // home atom of each compacted column
+};
+
+// One home subcell of a system that rebuilds, split over G waves: gw (< G)
+// selects this wave's share of the home atoms.
+//
+// A row is the 2 RAD + 1 linked subcells along the last axis.  BUILD_DENSE
+// (more than 16 atoms per subcell on average): a segment is one row's
+// candidates in blocks of 16, up to NB per subcell, all held in registers
+// while the kept home atoms of the row (compacted into columns) pass over
+// them 16 at a time.  BUILD_SPARSE (the 3^d stencil): a segment is the rows along the last
+// two axes, one block of each of their 9 subcells, against all home atoms of
+// a pass of up to 40, so that their loads are in flight together.
+template <int D, int RAD, int MODE>
+struct BuildTile {
+  static constexpr bool DENSE = MODE != BUILD_SPARSE;
+  static_assert(RAD == 1 || MODE == BUILD_DENSE, "half-size subcells take the dense form");
+  static constexpr int NRS = 2 * RAD + 1;
+  static constexpr int SW = BuildLds<RAD>::SW;
+  static constexpr int NR = DENSE ? 1 : NRS;       // rows per segment
+  static constexpr int NB = DENSE ? 15 / NRS : 1;  // blocks per subcell and segment
+  static constexpr int NT = NR * NRS * NB;         // blocks per segment (at most 15)
+  static constexpr int NW = (D + 4) / 2 - 1;       // packed words of slots 4 .. d+4
+  static constexpr int HP = DENSE ? 128 : 40;      // home atoms per pass
+
+  cSys* s;
+  BuildLds<RAD>* m;
+  cint* flat;
+  const int* rec;
+  const double* xb;
+  HDMD_GLOBAL int* nl;
+  double L, invL, cut, skin;
+  int nc, npad, W, hb, hcnt, lane;
+  int ci[D], stride[D];
+  bool two, v0, v1;
+  Survivors<unsigned short> sv;
+  int ntag;                    // segments tagged
+  int len0, len1;      // row lengths of the lane's home atoms
+  unsigned hn0[NW], hn1[NW];   // packed f16 slots 4 .. d+4 at offset zero
+  float ql0, ql1, B0, B1, tc0, tc1;
+
+  // home slots of slot word t at outer offsets `oa` (packed 250 o)
+  __device__ __attribute__((always_inline)) void put_home(const unsigned (&hn)[NW], float ql, float B,
+                                                          const unsigned (&oa)[NW], int osq, int slot) {
+    uv2* e = m->stage + slot * (SW / 2);
+    unsigned w[6];
+    float sB = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 6; t++) {
+      w[t] = 0u;
+      if (t < NW) {
+        // -q' = -q + 250 o;  sum of 250 o (-q) for B'
+        w[t] = h2u(u2h(hn[t]) + u2h(oa[t]));
+        sB = __builtin_amdgcn_fdot2(u2h(hn[t]), u2h(oa[t]), sB, false);
+      }
+    }
+    e[0] = uv2{w[0], w[1]};
+    e[1] = uv2{w[2], w[3]};
+    e[2] = uv2{w[4], w[5]};
+    const float Bo = B + 2.0f * sB + (float)(kQScale * kQScale) * (float)osq;
+#pragma unroll
+    for (int r = 0; r < NRS; r++) {
+      const float sh = (float)(kQScale * (r - RAD));
+      const float b = Bo + 2.0f * sh * ql + sh * sh;
+      const float hi = floorf(b * (1.0f / 2048.0f)), lo = __builtin_fmaf(-2048.0f, hi, b);
+      e[3 + r] = uv2{__builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(ql + sh, hi)),
+                     __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(lo, 0.5f))};
+    }
+  }
+
+  // squared gap of the lane's home atoms to the subcells o away along axis k
+  // (one unit short), added to S
+  __device__ __attribute__((always_inline)) void add_gap(int k, int o, float& S0, float& S1) const {
+    if (o == 0) return;
+    const float face = (float)((kQScale / 2) * (2 * (o < 0 ? -o : o) - 1) - 1);
+    const float sg = o < 0 ? -1.0f : 1.0f;
+    const float a0 = (float)u2h(hn0[k / 2])[k % 2], a1 = (float)u2h(hn1[k / 2])[k % 2];
+    const float g0 = fmaxf(__builtin_fmaf(sg, a0, face), 0.0f);
+    const float g1 = fmaxf(__builtin_fmaf(sg, a1, face), 0.0f);
+    S0 = __builtin_fmaf(g0, g0, S0);
+    S1 = __builtin_fmaf(g1, g1, S1);
+  }
+
+  __device__ __attribute__((always_inline)) int wrapc(int c) const {
+    return c < 0 ? c + nc : (c >= nc ? c - nc : c);
+  }
+  // packed 250 o of axis k added to the offset words
+  __device__ __attribute__((always_inline)) static unsigned off_word(int k, int o) {
+    // f16 250 = 0x5bd0, 500 = 0x5fd0
+    const unsigned a = o == 0 ? 0u : ((o == 1 || o == -1) ? 0x5bd0u : 0x5fd0u) | (o < 0 ? 0x8000u : 0u);
+    return a << (16 * (k % 2));
+  }
+
+  // exact test of the listed survivors, one per lane
+  __device__ __attribute__((always_inline)) void drain(bool all) {
+    const RowAppend append{m->hit, nl, npad, W};
+    sv.drain(lane, all, [&](unsigned cd, bool valid) {
+      // code: home atom, segment, lane group, position (4 block + row)
+      const int h = valid ? (int)(cd >> 12) : 0, i = hb + h;
+      int j = m->base[(cd >> 8) & 15][(cd >> 2) & 15] + 4 * ((cd >> 6) & 3) + (cd & 3);
+      j = valid ? j : i;
+      double xi[D], si, xj[D], sj;
+      load_rec<D>(xb, i, xi, si);
+      load_rec<D>(xb, j, xj, sj);
+      // The nearest image is taken with rint: the radius is at most L/3 (on
+      // half-size subcells, at least 5 per axis: 2L/5), so every pair it can
+      // admit has all |dx_k| clear of L/2, where rint and the definition's
+      // shift give the same value bit for bit; pairs with some |dx_k| near
+      // L/2 are beyond the radius either way.
+      double r2 = 0.0;
+#pragma unroll
+      for (int k = 0; k < D; k++) {
+        const double dx = near_image(xj[k] - xi[k], L, invL);
+        r2 = __builtin_fma(dx, dx, r2);
+        __builtin_amdgcn_sched_barrier(0);  // one axis at a time: few live registers
+      }
+      const bool pass = j != i && r2 < list_r2(si, sj, cut, skin);
+      append(lane, two, pass, h, i, j, len0, len1);
+    });
+    if (all) ntag = 0;
+  }
+
+  // the candidate blocks of one segment (each subcell's atoms from k0 on)
+  // against the staged home columns of its rows (ncol columns, st apart).
+  // Block t = k NR NRS + r is the k-th of subcell r.
+  __device__ __attribute__((always_inline)) void segment(const int (&f0)[NR * NRS],
+                                                         const int (&f1)[NR * NRS], unsigned rows,
+                                                         int k0, int kn, int ncol, int st) {
+    constexpr int NS = NR * NRS;
+    const int g = lane >> 4, col = lane & 15;
+    const int nhb = (ncol + 15) >> 4;
+    int b0 = 0;
+    for (;;) {
+      hv4 X[NT];
+#pragma unroll
+      for (int k = 0; k < NB; k++) {
+        if (k > 0 && k >= kn) continue;
+#pragma unroll
+        for (int r = 0; r < NS; r++) {
+          const int a = f0[r] + k0;
+          int n = max(f1[r] - a, 0);
+          if (!DENSE) n = (rows >> (r / NRS)) & 1u ? n : 0;
+          // loads past the subcell's end give zero slots, which never pass
+          const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(rec + (size_t)a * 8), 0, n * 32,
+                                                            0x00020000);
+          X[k * NS + r] = __builtin_bit_cast(
+              hv4, __builtin_amdgcn_raw_buffer_load_b64(rs, col * 32 + g * 8 + k * 512, 0, 0));
+        }
+      }
+      {  // where the codes of this segment find their atoms
+        int b;
+        if constexpr (DENSE) {
+          const int r = lane % NRS;
+          b = f0[0];
+#pragma unroll
+          for (int q = 1; q < NRS; q++) b = r == q ? f0[q] : b;
+          b += k0 + 16 * (lane / NRS);
+        } else {
+          b = 0;
+#pragma unroll
+          for (int r = 0; r < NS; r++) b = amdgcn_writelane(f0[r] + k0, r, b);
+        }
+        if (lane < 16) m->base[ntag][lane] = b;
+      }
+      bool full = false;
+      for (; b0 < nhb && !full; b0++) {
+        const int hs = 16 * b0 + col;
+        hv4 H[NS];
+#pragma unroll
+        for (int u = 0; u < NR; u++)
+#pragma unroll
+          for (int r = 0; r < NRS; r++)
+            H[u * NRS + r] = __builtin_bit_cast(
+                hv4, m->stage[(st * u + hs) * (SW / 2) + (g == 0 ? 3 + r : g - 1)]);
+        unsigned w0 = 0u, w1 = 0u;
+#pragma unroll
+        for (int k = 0; k < NB; k++) {
+          // (levels beyond the longest subcell: their bits are zero)
+          if (k > 0 && k >= kn) {
+#pragma unroll
+            for (int r = 0; r < NS; r++) {
+              if (k * NS + r < 8) w0 <<= 4;
+              else w1 <<= 4;
+            }
+            continue;
+          }
+          // a row's products at a time, their results packed before the next
+          // row's (few live registers)
+#pragma unroll
+          for (int u = 0; u < NR; u++) {
+            if (!DENSE && !((rows >> u) & 1u)) {
+              // no home atom reaches the row: its columns were not staged
+#pragma unroll
+              for (int r = 0; r < NRS; r++) {
+                if (k * NS + u * NRS + r < 8) w0 <<= 4;
+                else w1 <<= 4;
+              }
+              continue;
+            }
+            fv4 e[NRS];
+#pragma unroll
+            for (int r = 0; r < NRS; r++) {
+              const fv4 zero = {};
+              const int t = k * NS + u * NRS + r;
+              e[r] = __builtin_amdgcn_mfma_f32_16x16x16f16(X[t], H[u * NRS + r], zero, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < NRS; r++) {
+              unsigned& w = k * NS + u * NRS + r < 8 ? w0 : w1;
+#pragma unroll
+              for (int v = 0; v < 4; v++)
+                w = __builtin_amdgcn_alignbit(w, __float_as_uint(e[r][v]), 31u);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+        static_assert(NT > 8 && NT <= 16, "two words of bits");
+        w1 <<= 4 * (16 - NT);
+        // columns past the last home atom hold whatever the stage held
+        const bool hv = hs < ncol;
+        const int h = DENSE ? (int)m->hid[hs] : hs;
+        const unsigned tag = (unsigned)((h << 7) | (ntag << 3) | (g << 1));
+        sv.push(hv ? w0 : 0u, tag);
+        if (!DENSE || kn * NS > 8) sv.push(hv ? w1 : 0u, tag | 1u);
+        while (sv.nw >= 64 && !full) full = !sv.expand(lane);
+      }
+      const bool done = b0 >= nhb;
+      if (done) ntag++;
+      // the exact test runs outside the blocks' register lifetime: a segment
+      // it interrupts loads them again
+      if (full || sv.nq >= 128 || ntag == kBuildTags) drain(ntag == kBuildTags);
+      if (done) break;
+    }
+  }
+
+  // one segment's rows: subcell bounds, staging, and the walk over subcells
+  // longer than a segment
+  __device__ __attribute__((always_inline)) void rows_at(float S0, float S1, int P,
+                                                         const unsigned (&oa)[NW], int osq) {
+    int f0[NR * NRS], f1[NR * NRS];
+    unsigned rows = 0;
+    unsigned long long km0 = 0, km1 = 0;
+    int mx = 0;
+#pragma unroll
+    for (int u = 0; u < NR; u++) {
+      int Pu = P;
+      if (!DENSE) Pu += wrapc(ci[D - 2] + u - RAD) * nc;
+#pragma unroll
+      for (int r = 0; r < NRS; r++) {
+        const int c = Pu + wrapc(ci[D - 1] + r - RAD);
+        f0[u * NRS + r] = flat[c];
+        f1[u * NRS + r] = flat[c + 1];
+      }
+    }
+    wave_lds_sync();  // the previous rows' columns have been read
+    int ncol = 0, st = 0;
+    if (DENSE) {
+      km0 = __ballot(v0 && S0 < tc0);
+      km1 = two ? __ballot(v1 && S1 < tc1) : 0ull;
+      const int nk0 = __builtin_popcountll(km0);
+      ncol = nk0 + __builtin_popcountll(km1);
+      if ((km0 >> lane) & 1ull) {
+        const int r = rank_in(km0);
+        m->hid[r] = (unsigned char)lane;
+        put_home(hn0, ql0, B0, oa, osq, r);
+      }
+      if (km1 && ((km1 >> lane) & 1ull)) {
+        const int r = nk0 + rank_in(km1);
+        m->hid[r] = (unsigned char)(64 + lane);
+        put_home(hn1, ql1, B1, oa, osq, r);
+      }
+      rows = 1u;
+    } else {
+      ncol = hcnt;
+      st = hcnt;
+#pragma unroll
+      for (int u = 0; u < NR; u++) {
+        const int o = u - RAD;
+        float T0 = S0, T1 = S1;
+        add_gap(D - 2, o, T0, T1);
+        if (__ballot(v0 && T0 < tc0) == 0ull) continue;
+        rows |= 1u << u;
+        if (v0) {
+          unsigned ou[NW];
+#pragma unroll
+          for (int t = 0; t < NW; t++) ou[t] = oa[t];
+          ou[(D - 2) / 2] |= off_word(D - 2, o);
+          put_home(hn0, ql0, B0, ou, osq + o * o, u * hcnt + lane);
+        }
+      }
+      if (!rows) return;
+    }
+#pragma unroll
+    for (int r = 0; r < NR * NRS; r++) mx = max(mx, f1[r] - f0[r]);
+    wave_lds_sync();
+    for (int k0 = 0; k0 < mx; k0 += 16 * NB)
+      segment(f0, f1, rows, k0, min((mx - k0 + 15) >> 4, NB), ncol, st);
+  }
+
+  // outer offsets of axis K and beyond (in stencil order, last axis fastest),
+  // leaving out those that no home atom reaches
+  template <int K>
+  __device__ __attribute__((always_inline)) void walk(float S0, float S1, int P, const unsigned (&oa)[NW],
+                                                      int osq) {
+    if constexpr (K >= (DENSE ? D - 1 : D - 2)) {
+      rows_at(S0, S1, P, oa, osq);
+    } else {
+#pragma unroll 1
+      for (int o = -RAD; o <= RAD; o++) {
+        // A SIMD issues for its oldest waves first, so that without this the
+        // waves of a launch finish one by one and the last ones run alone,
+        // their latencies exposed.  A wave's priority falls as it gets
+        // through its rows: those that lag get the issue slots.
+        if constexpr (K == 0) {
+          if (o == -RAD) __builtin_amdgcn_s_setprio(2);
+          else if (o == 0) __builtin_amdgcn_s_setprio(1);
+          else if (o == RAD) __builtin_amdgcn_s_setprio(0);
+        }
+        float T0 = S0, T1 = S1;
+        add_gap(K, o, T0, T1);
+        if (__ballot((v0 && T0 < tc0) || (v1 && T1 < tc1)) == 0ull) continue;
+        unsigned ob[NW];
+#pragma unroll
+        for (int t = 0; t < NW; t++) ob[t] = oa[t] | (t == K / 2 ? off_word(K, o) : 0u);
+        walk<K + 1>(T0, T1, P + wrapc(ci[K] + o) * stride[K], ob, osq + o * o);
+      }
+    }
+  }
+
+  // the lane's home atom of slot ii: its own candidate record turned into
+  // home slots at offset zero, and its reach for the row cull: its share of
+  // the radius plus half the largest, a_i + r_l,max/2
+  __device__ __attribute__((always_inline)) void own(int ii, unsigned (&hn)[NW], float& ql, float& B,
+                                                     float& tc) const {
+    const v4i a = *reinterpret_cast<const v4i*>(rec + (size_t)ii * 8);
+    const v4i b = *reinterpret_cast<const v4i*>(rec + (size_t)ii * 8 + 4);
+    const unsigned w[8] = {(unsigned)a.x, (unsigned)a.y, (unsigned)a.z, (unsigned)a.w,
+                           (unsigned)b.x, (unsigned)b.y, (unsigned)b.z, (unsigned)b.w};
+    auto slot = [&](int k) { return u2h(w[k / 2])[k % 2]; };
+    ql = -0.5f * (float)slot(0);
+    B = -__builtin_fmaf(2048.0f, (float)slot(D + 3), (float)slot(D + 4));
+#pragma unroll
+    for (int t = 0; t < NW; t++) {
+      hv2 v;
+#pragma unroll
+      for (int e = 0; e < 2; e++) {
+        const int k = 4 + 2 * t + e;
+        v[e] = k < D + 3 ? (_Float16)-0.5f * slot(k)
+                         : (k == D + 3 ? (_Float16)-2048.0f : (k == D + 4 ? (_Float16)-1.0f : (_Float16)0.0f));
+      }
+      hn[t] = h2u(v);
+    }
+    const double sg = xb[(size_t)ii * Dims<D>::DR + D];
+    const double reach = (0.5 * (cut * sg + skin) + 0.5 * s->rlmax) * s->qinv;
+    tc = (float)ceil(reach * reach);
+  }
+
+  __device__ __attribute__((always_inline)) void run(SysDev* sys, int hc, int gw, int G, BuildLds<RAD>* lds) {
+    s = (cSys*)sys;
+    m = lds;
+    lane = threadIdx.x & 63;
+    // subcell starts come through the scalar cache (written by an earlier kernel)
+    flat = (cint*)s->cell_flat;
+    const int c0h = flat[hc], c1h = flat[hc + 1];
+    const int per = (c1h - c0h + G - 1) / G;
+    const int h0 = c0h + gw * per, h1 = min(c1h, h0 + per);
+    if (h0 >= h1) return;
+    nc = s->ncell;
+    npad = s->npad;
+    W = s->width;
+    xb = s->x[s->xcur];
+    rec = s->qc16;
+    nl = gbl(s->nl);
+    L = s->L;
+    invL = 1.0 / L;
+    cut = s->cutoff;
+    skin = s->skin;
+    {
+      int u = hc, sd = 1;
+#pragma unroll
+      for (int k = D - 1; k >= 0; k--) {
+        ci[k] = u % nc;
+        u /= nc;
+        stride[k] = sd;
+        sd *= nc;
+      }
+    }
+    int rowmax = 0;
+    // home atoms in passes of up to HP: lane l holds atoms hb + l and hb + 64 + l
+    for (hb = h0; hb < h1; hb += HP) {
+      hcnt = min(HP, h1 - hb);
+      two = DENSE && hcnt > 64;
+      v0 = lane < hcnt;
+      v1 = two && lane + 64 < hcnt;
+      own(v0 ? hb + lane : hb, hn0, ql0, B0, tc0);
+      own(v1 ? hb + 64 + lane : hb, hn1, ql1, B1, tc1);
+      len0 = len1 = 0;
+      sv.q = &m->q;
+      sv.nw = sv.nq = 0;
+      ntag = 0;
+      m->hit[lane] = 0ull;
+      m->hit[64 + lane] = 0ull;
+      unsigned oa[NW];
+#pragma unroll
+      for (int t = 0; t < NW; t++) oa[t] = 0u;
+      walk<0>(0.0f, 0.0f, 0, oa, 0);
+      drain(true);
+      if (v0) {
+        gbl(s->nlen)[hb + lane] = len0;
+        rowmax = max(rowmax, len0);
+      }
+      if (v1) {
+        gbl(s->nlen)[hb + 64 + lane] = len1;
+        rowmax = max(rowmax, len1);
+      }
+    }
+    rowmax = wave_max_i(rowmax);
+    if (lane == 0 && rowmax > 0) {
+      atomicMax(&sys->max_row, rowmax);
+      if (rowmax > W) atomicOr(&sys->err, ERR_OVERFLOW);
+    }
+  }
+};
+
+template <int D, int RAD, int MODE>
+__device__ __forceinline__ void build_mf_tile(SysDev* s, int hc, int gw, int G, BuildLds<RAD>* lds) {
+  BuildTile<D, RAD, MODE> t;
+  t.run(s, hc, gw, G, lds);
+}
+
+template <int D, int G, int RAD, int MODE>
+__global__ __launch_bounds__(64 * G, 4) void k_build_mf(KArgs a) {
+  __shared__ BuildLds<RAD> lds[G];
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   for (int t = xcd_tile(blockIdx.x, gridDim.x);; t += gridDim.x) {
     SysDev* s;
     int hc;
-    if (!fetch_cell_tile(a, t, s, hc)) break;
-    s = uniform_ptr(s);
-    hc = uniform_int(hc);
-    if (!running(s) || !need_rebuild(s) || uniform_int(s->reach) != RAD) {
+    if (!fetch_cell_tile_u(a, t, s, hc)) break;
+    cSys* c = (cSys*)s;
+    if (!running(c) | !need_rebuild(c) | (c->reach != RAD) | (c->wrap != 0) | (c->bmode != MODE)) {
       if (a.single) break;  // one system: the same for every tile
       continue;
     }
-    build_t_tile<D, G, WR, RAD, MF>(s, hc, wv, msk_all[wv], cand_all[wv]);
+    build_mf_tile<D, RAD, MODE>(s, hc, wv, G, &lds[wv]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Verlet-list build of systems of n_cell <= 2 (a list radius of a third of
+// the box or more): every atom is a candidate of every other, and the pair
+// test runs on the matrix cores too.  Along each axis the atom is put on the
+// circle, e = (cos, sin)(2 pi x / L): the chord between two atoms does not
+// exceed the arc, so a pair within its radius r_ij = a_i + a_j has
+//   sum_k |e_i - e_j|_k^2 <= (2 pi r_ij / L)^2
+//   <=>  sum_k e_i.e_j >= d - (2 pi r_ij / L)^2 / 2,
+// whatever images the periodic box takes, and (a_i + a_j)^2 <= 2 a_i^2 + 2
+// a_j^2 splits the bound into a share t = d/2 - (2 pi a / L)^2 (minus a margin
+// for the f16 rounding) per atom:
+//   t_i + t_j - sum_k e_i.e_j < 0
+// is one entry of a product over 2 d + 2 f16 slots
+//   candidate [cos, sin of every axis, 1, t_j, 0 ..],  home [-cos, -sin, t_i, 1, 0 ..].
+// (The chord test keeps about twice the pairs of the list in d = 8; it takes
+// no row cull, no shifts and no wrapped differences.)  2 d + 2 <= 16 (d <=
+// 7): records of 16 slots and 16x16x16 products; above: 24 slots, 16x16x32.
+// A wave takes 64 home atoms as four blocks of columns held in registers and
+// streams all atoms past them, 128 at a time: 32 matrix instructions and 128
+// sign-bit shifts per 8192 pair tests, and the exact tests of the survivors.
+// d = 8, N = 131072 (mean row 200): 2.5 ms, where packed int16 tests of the
+// 45 % of the pairs that a row cull left took 7.6.
+// ---------------------------------------------------------------------------
+struct WrapLds {
+  unsigned long long hit[64];
+  SurvivorLds<unsigned> q;
+};
+
+// The 64 home atoms of one tile.
+template <int D>
+__device__ __forceinline__ void build_wrap_tile(SysDev* sys, int tile, WrapLds* m) {
+  typedef WrapRec<D> R;
+  typedef typename std::conditional<R::LW == 2, hv4, hv8>::type Op;
+  cSys* s = (cSys*)sys;
+  const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
+  const int n = s->n, npad = s->npad, W = s->width;
+  const int hb = tile * 64;
+  if (hb >= n) return;
+  const int hcnt = min(64, n - hb);
+  const double* __restrict__ xb = s->x[s->xcur];
+  const int* __restrict__ rec = s->qc16;
+  const double L = s->L, hL = s->hL, cut = s->cutoff, skin = s->skin;
+  // operand words of the atom `a + col` (zero past `cnt` atoms, which gives
+  // an entry of t_i + 0 or 0: masked by the caller for homes, and never
+  // negative for candidates, whose slots are all zero)
+  auto operand = [&](int a, int cnt) __attribute__((always_inline)) -> Op {
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)(rec + (size_t)a * R::WORDS), 0,
+                                                      max(min(cnt, 16), 0) * R::WORDS * 4, 0x00020000);
+    if constexpr (R::LW == 2) {
+      return __builtin_bit_cast(Op, __builtin_amdgcn_raw_buffer_load_b64(rs, col * 32 + g * 8, 0, 0));
+    } else {
+      // 24 slots: the fourth lane group's eight are zero (out of range)
+      const int off = g < 3 ? col * 48 + g * 16 : 16 * 48;
+      return __builtin_bit_cast(Op, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+    }
+  };
+  Op H[4];
+#pragma unroll
+  for (int b = 0; b < 4; b++) {
+    // home slots from the atom's record: signs flipped, 1 and t exchanged
+    Op h = operand(hb + 16 * b, hcnt - 16 * b);
+    constexpr int GS = R::LW * 2;             // slots per lane group
+    constexpr int PG = 2 * D / GS, PS = 2 * D % GS;  // group and place of the slots (1, t)
+#pragma unroll
+    for (int e = 0; e < GS; e++) H[b][e] = -h[e];
+    if (g == PG) {
+      H[b][PS] = h[PS + 1];
+      H[b][PS + 1] = h[PS];
+    }
+  }
+  Survivors<unsigned> sv{&m->q, 0, 0};
+  m->hit[lane] = 0ull;
+  const RowAppend append{m->hit, gbl(s->nl), npad, W};
+  int len0 = 0, len1 = 0;
+  constexpr int SPAN = 1 << 26;  // candidates a code can name
+  for (int c0 = 0; c0 < n; c0 += SPAN) {
+    const int ce = min(n - c0, SPAN);
+    auto drain = [&](bool all) __attribute__((always_inline)) {
+      sv.drain(lane, all, [&](unsigned cd, bool valid) {
+        // code: pair of chunks, home atom, lane group, position (4 block + row)
+        const int h = valid ? (int)(cd >> 7) & 63 : 0, i = hb + h, p = cd & 31;
+        int j = c0 + (int)(cd >> 13) * 128 + 16 * (p >> 2) + 4 * ((cd >> 5) & 3) + (p & 3);
+        j = valid ? j : i;
+        double xi[D], si, xj[D], sj;
+        load_rec<D>(xb, i, xi, si);
+        load_rec<D>(xb, j, xj, sj);
+        const bool pass = j != i && dist2_exact<D>(xi, xj, L, hL) < list_r2(si, sj, cut, skin);
+        append(lane, false, pass, h, i, j, len0, len1);
+      });
+    };
+    for (int c = 0; c < ce; c += 128) {
+      unsigned w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int half = 0; half < 2; half++) {
+        Op X[4];
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+          const int a = c + 64 * half + 16 * b;
+          X[b] = operand(c0 + min(a, ce), ce - a);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; b++) {
+          fv4 e[4];
+#pragma unroll
+          for (int h = 0; h < 4; h++) {
+            const fv4 zero = {};
+            if constexpr (R::LW == 2) e[h] = __builtin_amdgcn_mfma_f32_16x16x16f16(X[b], H[h], zero, 0, 0, 0);
+            else e[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[b], H[h], zero, 0, 0, 0);
+          }
+#pragma unroll
+          for (int h = 0; h < 4; h++)
+#pragma unroll
+            for (int v = 0; v < 4; v++)
+              w[h] = __builtin_amdgcn_alignbit(w[h], __float_as_uint(e[h][v]), 31u);
+          __builtin_amdgcn_sched_barrier(0);  // one block's results at a time
+        }
+      }
+#pragma unroll 1
+      for (int h = 0; h < 4; h++) {
+        const int hs = 16 * h + col;
+        const unsigned wh = h < 2 ? (h == 0 ? w[0] : w[1]) : (h == 2 ? w[2] : w[3]);
+        sv.push(hs < hcnt ? wh : 0u, (unsigned)(((c >> 7) << 8) | (hs << 2) | g));
+        bool full = false;
+        while (sv.nw >= 64 && !full) full = !sv.expand(lane);
+        if (full || sv.nq >= 128) drain(false);
+      }
+    }
+    drain(true);
+  }
+  int rowmax = 0;
+  if (lane < hcnt) {
+    gbl(s->nlen)[hb + lane] = len0;
+    rowmax = len0;
+  }
+  rowmax = wave_max_i(rowmax);
+  if (lane == 0 && rowmax > 0) {
+    atomicMax(&sys->max_row, rowmax);
+    if (rowmax > W) atomicOr(&sys->err, ERR_OVERFLOW);
+  }
+}
+
+template <int D>
+__global__ __launch_bounds__(64, 4) void k_build_wrap(KArgs a) {
+  __shared__ WrapLds lds;
+  for (int t = blockIdx.x;; t += gridDim.x) {
+    SysDev* s;
+    int tile;
+    if (!fetch_atom_tile_u(a, t, s, tile)) break;
+    cSys* c = (cSys*)s;
+    if (!running(c) | !need_rebuild(c) | (c->wrap == 0)) {
+      if (a.single) break;  // one system: the same for every tile
+      continue;
+    }
+    build_wrap_tile<D>(s, tile, &lds);
   }
 }
 

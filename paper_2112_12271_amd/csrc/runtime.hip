@@ -64,10 +64,11 @@ static SwapScratch swap_scratch(void* base) {
 // geometry and workspace plan
 // ---------------------------------------------------------------------------
 struct Plan {
-  int d = 0, dr = 0, dq = 0, dy = 0;
-  int n = 0, npad = 0, ncell = 0, radix = 0, ncells = 0, nstencil = 0, nchunks = 0;
+  int d = 0, dr = 0, dq = 0;
+  int n = 0, npad = 0, ncell = 0, ncells = 0, nchunks = 0;
   int ntiles = 0, nwaves = 0, width = 0;
-  bool wrap = false, mix = false, morse = false;
+  bool wrap = false;  // n_cell <= 2 on subcells of side >= r_l,max
+  bool mix = false, morse = false;
   // reach: stencil radius in subcells (1: side >= r_l,max, 3^d stencil; 2:
   // half-size subcells, 5^d stencil); key_wrap/key_occ: the autotuner's key,
   // taken from the grid of side >= r_l,max; nh_auto: half-size subcells per
@@ -76,7 +77,7 @@ struct Plan {
   int lpa = 1, row_key = 0;  // lanes per atom of the force kernels and their key
   double rlmax = 0;
   size_t off_desc = 0, off_x[2] = {0, 0}, off_q[2] = {0, 0}, off_v[2] = {0, 0},
-         off_oid[2] = {0, 0}, off_f = 0, off_xref = 0, off_disp[2] = {0, 0}, off_ycell = 0, off_qc = 0, off_qc16 = 0,
+         off_oid[2] = {0, 0}, off_f = 0, off_xref = 0, off_disp[2] = {0, 0}, off_qc16 = 0,
          off_cell_of = 0,
          off_rank = 0, off_cell_count = 0, off_cell_flat = 0, off_cell_local = 0, off_chunk_sum = 0,
          off_chunk_off = 0, off_key = 0, off_src = 0, off_nl = 0, off_nlen = 0, off_part = 0,
@@ -172,7 +173,6 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   p.d = s->d;
   p.dr = s->d <= 3 ? 4 : (s->d <= 7 ? 8 : 16);
   p.dq = s->d <= 2 ? 4 : (s->d <= 6 ? 8 : 16);
-  p.dy = (s->d + 3) & ~3;
   p.n = (int)s->n;
   p.npad = (int)((s->n + kTile - 1) / kTile * kTile);  // whole 64-atom tiles
   p.rlmax = s->cutoff * s->sigma_max + s->skin;
@@ -185,7 +185,6 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   p.key_wrap = ncf <= 2;
   p.key_occ = occ_bucket(p.n, cells_full);
   int64_t cells_alloc = cells_full;
-  bool need_ycell = ncf <= 2, need_qc = ncf > 2;
   p.reach = 1;
   p.ncell = ncf;
   if (s->subcells == HDMD_SUBCELLS_HALF) {
@@ -196,13 +195,10 @@ static int make_plan(const hdmd_system* s, Plan& p) {
     p.reach = 2;
     p.ncell = nh;
     cells_alloc = ipow(nh, p.d);
-    need_ycell = false;
-    need_qc = true;
   } else if (s->subcells == HDMD_SUBCELLS_AUTO) {
     p.nh_auto = half_ncell(*s, p.rlmax, cell_cap(*s));
     if (p.nh_auto) {
       cells_alloc = std::max<int64_t>(cells_alloc, ipow(p.nh_auto, p.d));
-      need_qc = true;
       if (tuned_reach(p.d, p.key_wrap, p.key_occ) == 2) {
         p.reach = 2;
         p.ncell = p.nh_auto;
@@ -211,9 +207,7 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   } else if (s->subcells != HDMD_SUBCELLS_FULL) {
     return fail(HDMD_ERR_ARG, "subcells must be HDMD_SUBCELLS_AUTO, _FULL or _HALF");
   }
-  p.radix = p.reach == 2 ? 5 : (p.ncell < 3 ? p.ncell : 3);
   p.ncells = (int)ipow(p.ncell, p.d);
-  p.nstencil = (int)ipow(p.radix, p.d);
   p.nchunks = (p.ncells + kChunk - 1) / kChunk;
   const int64_t chunks_alloc = (cells_alloc + kChunk - 1) / kChunk;
   p.ntiles = p.npad / kTile;
@@ -239,9 +233,8 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   p.off_f = take(np * p.d * vsz);
   p.off_xref = take(np * p.d * 8);
   for (int b = 0; b < 2; b++) p.off_disp[b] = take(np * p.d * 8);
-  p.off_ycell = take(need_ycell ? np * p.dy * 4 : 0);
-  p.off_qc = take(need_qc ? np * 16 : 0);
-  p.off_qc16 = take(np * 32);
+  // (n_cell <= 2 and d >= 8: records of 48 bytes)
+  p.off_qc16 = take(np * (ncf <= 2 && p.d >= 8 && s->subcells != HDMD_SUBCELLS_HALF ? 48 : 32));
   p.off_cell_of = take(np * 4);
   p.off_rank = take(np * 4);
   p.off_cell_count = take((size_t)cells_alloc * 4);
@@ -279,14 +272,13 @@ static SysDev make_desc(const hdmd_system* s, const Plan& p, void* ws) {
   h.ncell = p.ncell;
   h.reach = p.reach;
   h.lpa = p.lpa;
-  h.radix = p.radix;
   h.ncells = p.ncells;
-  h.nstencil = p.nstencil;
   h.width = p.width;
   h.nchunks = p.nchunks;
   h.ntiles = p.ntiles;
   h.mode = MODE_STATIC;
   h.wrap = p.wrap;
+  h.bmode = build_mode(p.reach, p.n, p.ncells);
   h.nwaves = p.nwaves;
   h.L = s->box_l;
   h.hL = 0.5 * s->box_l;
@@ -303,34 +295,6 @@ static SysDev make_desc(const hdmd_system* s, const Plan& p, void* ws) {
   h.qinv = (double)kQScale / h.lsc;
   h.qmarg = 0.5 * std::sqrt((double)p.d) * (1.0 + 1e-6);
   h.ysort = p.n < (1 << 23) ? 1 : 0;
-  if (p.wrap) {
-    // n_cell <= 2: prefilter on 16-bit wrapped coordinates, unit Delta = L/2^16;
-    // |u_j - u_i|^2 < tq keeps every pair within r_l,max (each axis is off by
-    // at most one unit), and a row is skipped when the gaps to its subcells,
-    // one unit short per axis, reach r_l,max
-    const double delta = s->box_l / 65536.0;
-    const double thr = p.rlmax / delta + std::sqrt((double)p.d) * (1.0 + 1e-6);
-    h.tq = (int32_t)std::min(std::floor(thr * thr) + 1.0, 2147483000.0);
-    const double rc = p.rlmax / delta;
-    h.tcull = (int32_t)std::min(std::ceil(rc * rc), 2147483000.0);
-  } else {
-    // int8 prefilter threshold: ((r_l,max + Delta sqrt(d)) / Delta)^2, Delta =
-    // L_sc / 250, rounded down and made strict (+1), with slack on sqrt(d)
-    const double delta = h.lsc / (double)kQScale;
-    const double thr = (p.rlmax + delta * std::sqrt((double)p.d) * (1.0 + 1e-6)) / delta;
-    h.tq = (int32_t)std::floor(thr * thr) + 1;
-    // a home atom skips a row of linked subcells when its gap to the row,
-    // taken one unit short per axis, is at least r_l,max: S >= (r_l,max/Delta)^2
-    const double rc = p.rlmax / delta;
-    h.tcull = (int32_t)std::ceil(rc * rc);
-  }
-  // FP32 prefilter radius: the largest list radius enlarged by a relative
-  // 1e-4 plus 1e-5 L, far above the FP32 rounding of offsets from subcell
-  // centres (|y| <= L_sc) and of the box length.
-  const double rf = p.rlmax * (1.0 + 1.0e-4) + 1.0e-5 * s->box_l;
-  h.rl2f = std::nextafter((float)(rf * rf), INFINITY);
-  h.lscf = (float)h.lsc;
-  h.Lf = (float)s->box_l;
   for (int b = 0; b < 2; b++) {
     h.x[b] = at<double>(ws, p.off_x[b]);
     h.q[b] = p.mix ? at<int32_t>(ws, p.off_q[b]) : nullptr;
@@ -340,9 +304,7 @@ static SysDev make_desc(const hdmd_system* s, const Plan& p, void* ws) {
   h.f = at<void>(ws, p.off_f);
   h.xref = at<double>(ws, p.off_xref);
   for (int b = 0; b < 2; b++) h.disp[b] = at<double>(ws, p.off_disp[b]);
-  h.ycell = p.wrap ? at<float>(ws, p.off_ycell) : nullptr;
-  h.qc = p.wrap ? nullptr : at<int32_t>(ws, p.off_qc);
-  h.qc16 = at<int32_t>(ws, p.off_qc16);  // int16 offsets, or wrapped 16-bit coordinates
+  h.qc16 = at<int32_t>(ws, p.off_qc16);
   h.cell_of = at<int32_t>(ws, p.off_cell_of);
   h.rank = at<int32_t>(ws, p.off_rank);
   h.cell_count = at<int32_t>(ws, p.off_cell_count);
@@ -472,7 +434,9 @@ static void chain_sort(const Plan& p, SysDev* dev, hipStream_t st) {
 }
 
 static void build_single(const Plan& p, SysDev* dev, hipStream_t st, int blk) {
-  dkernels(p.d)->build(p.reach, p.wrap, blk, single_args(dev, p.d), p.ncells, st);
+  const DKernels* K = dkernels(p.d);
+  if (p.wrap) K->build_wrap(single_args(dev, p.d), p.ntiles, st);
+  else K->build(p.reach, build_mode(p.reach, p.n, p.ncells), blk, single_args(dev, p.d), p.ncells, st);
 }
 
 static void chain_single(const Plan& p, SysDev* dev, hipStream_t st, int blk) {
@@ -556,18 +520,14 @@ static int tune_build(const hdmd_system* sys, const Plan& pf, const double* pos,
       // the same layout with the half-size grid
       p.reach = 2;
       p.ncell = pf.nh_auto ? pf.nh_auto : pf.ncell;
-      p.radix = 5;
       p.ncells = (int)ipow(p.ncell, p.d);
-      p.nstencil = (int)ipow(5, p.d);
       p.nchunks = (p.ncells + kChunk - 1) / kChunk;
       p.wrap = false;
     } else {
       p.reach = 1;
       p.ncell = choose_ncell(*sys, pf.rlmax);
-      p.radix = p.ncell < 3 ? p.ncell : 3;
       p.ncells = (int)ipow(p.ncell, p.d);
-      p.nstencil = (int)ipow(p.radix, p.d);
-      p.nchunks = (p.ncells + kChunk - 1) / kChunk;
+          p.nchunks = (p.ncells + kChunk - 1) / kChunk;
       p.wrap = p.ncell <= 2;
     }
     SysDev* dev = at<SysDev>(ws, p.off_desc);
@@ -581,10 +541,8 @@ static int tune_build(const hdmd_system* sys, const Plan& pf, const double* pos,
       if (rc) return rc;
     }
     float best = 1e30f;
-    for (int cand : {1, 2, 4, 1 | kBuildMF, 2 | kBuildMF, 4 | kBuildMF, 8, 16, 64, 128, 256}) {
-      if (reach == 2 && (cand & ~kBuildMF) > 4) break;
-      if (!p.wrap && (cand == 8 || cand == 16)) continue;  // 8 and 16 waves: crowded subcells only
-      if (p.wrap && (cand & kBuildMF)) continue;  // matrix-core tests: n_cell >= 3 only
+    for (int cand : {1, 2, 4}) {
+      if (p.wrap && cand > 1) break;  // n_cell <= 2: one form
       build_single(p, dev, st, cand);  // warm-up
       HIPCHK(hipEventRecord(e0, st));
       build_single(p, dev, st, cand);
@@ -1342,7 +1300,7 @@ struct HostBatch {
   bool dirty = true;
   // current composition
   int n_atom[kMaxD + 1] = {0}, n_cell[kMaxD + 1] = {0}, n_nowrap[kMaxD + 1] = {0};
-  int n_chunk = 0, n_sys = 0, blk[kMaxD + 1] = {0};  // wrap-variant build tile per d
+  int n_chunk = 0, n_sys = 0;
   int n_atom_all = 0, n_cell_all = 0, n_nowrap_all = 0;
   bool has_fire = false, has_md = false, has_wrap[kMaxD + 1] = {false},
        has_nowrap[kMaxD + 1] = {false}, mix[kMaxD + 1] = {false},
@@ -1414,7 +1372,6 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
   for (int d = kMinD; d <= kMaxD; d++) {
     a_off[d] = atom_base;
     c_off[d] = cell_base;
-    int occ_tot = 0, occ_n = 0;
     for (int s = 0; s < B->max_slots; s++) {
       const SlotInfo& S = B->slots[s];
       if (!S.used || S.p.d != d) continue;
@@ -1425,10 +1382,8 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
       const int kind = 1 << ((S.p.mix ? 1 : 0) | (S.p.morse ? 2 : 0) | (lpa_index(S.p.lpa) << 2));
       if (S.mode == MODE_MD) B->kinds_md[d] |= kind;
       else B->kinds_fire[d] |= kind;
-      occ_tot += S.p.n;
-      occ_n += S.p.ncells;
     }
-    // cell tiles: systems with n_cell >= 3 first, then the wrap systems
+    // cell tiles: systems with n_cell >= 3 first, then those of n_cell <= 2
     for (int pass = 0; pass < 2; pass++) {
       for (int s = 0; s < B->max_slots; s++) {
         const SlotInfo& S = B->slots[s];
@@ -1441,15 +1396,6 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
     }
     atom_base += B->n_atom[d];
     cell_base += B->n_cell[d];
-    double occ = occ_n ? (double)occ_tot / occ_n : 1.0;
-    // candidate-lane build for the n_cell <= 2 systems too, four waves per
-    // subcell (few, crowded subcells per system; HDMD_WRAP_G overrides)
-    {
-      const char* e = std::getenv("HDMD_WRAP_G");
-      const int g = e ? std::atoi(e) : 4;
-      B->blk[d] = (g == 1 || g == 2 || g == 4) ? g : 4;
-    }
-    (void)occ;
   }
   for (int s = 0; s < B->max_slots; s++) {
     const SlotInfo& S = B->slots[s];
@@ -1474,8 +1420,8 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
   }
   t.n_atom[0] = (int32_t)atom_base;  // class 0: every class
   // class 0 lists its cell tiles in an array of its own, the n_cell >= 3
-  // subcells of every class before the wrap ones (the list build of a batch
-  // gives the former one wave each and the latter a workgroup each)
+  // subcells of every class before the others (the list build of a batch
+  // goes over the former only; it takes n_cell <= 2 systems by atom tiles)
   std::vector<int2> cell_all;
   cell_all.reserve(cell.size());
   for (int pass = 0; pass < 2; pass++)
@@ -1549,9 +1495,13 @@ static void enqueue_batch_iter(HostBatch* B, const std::vector<int>& grids, hipS
   // list builds: one launch per stencil radius present (a launch serves the
   // systems of its own radius and passes over the others' subcells)
   auto class_builds = [&](int d) {
-    if (B->has_nowrap[d]) dkernels(d)->build(1, false, 1, batch_args(B, d, 1), gc(d), st);
-    if (B->has_half[d]) dkernels(d)->build(2, false, 1, batch_args(B, d, 1), gc(d), st);
-    if (B->has_wrap[d]) dkernels(d)->build(1, true, B->blk[d], batch_args(B, d, 2), gc(d), st);
+    const DKernels* K = dkernels(d);
+    if (B->has_nowrap[d]) {
+      K->build(1, BUILD_SPARSE, 1, batch_args(B, d, 1), gc(d), st);
+      K->build(1, BUILD_DENSE, 1, batch_args(B, d, 1), gc(d), st);
+    }
+    if (B->has_half[d]) K->build(2, BUILD_DENSE, 1, batch_args(B, d, 1), gc(d), st);
+    if (B->has_wrap[d]) K->build_wrap(batch_args(B, d), ga(d), st);
   };
   if (gb_all > 0) {
     bool half = false;
@@ -1704,7 +1654,7 @@ int hdmd_batch_run(void* table_ws, int32_t iterations, void* stream) {
   for (int d = kMinD; d <= kMaxD; d++) {
     grids.push_back(B->n_atom[d] ? pow2_grid(B->n_atom[d], 4096) : 0);
     grids.push_back(B->n_cell[d] ? pow2_grid(B->n_cell[d], 8192) : 0);
-    grids.push_back(B->blk[d] * 4 + (B->has_wrap[d] ? 2 : 0) + (B->has_nowrap[d] ? 1 : 0) +
+    grids.push_back((B->has_wrap[d] ? 2 : 0) + (B->has_nowrap[d] ? 1 : 0) +
                     (B->mix[d] ? 1024 : 0) + (B->has_half[d] ? 2048 : 0));
   }
   for (int d = kMinD; d <= kMaxD; d++) grids.push_back(B->kinds_md[d] | (B->kinds_fire[d] << 12));
@@ -1715,7 +1665,7 @@ int hdmd_batch_run(void* table_ws, int32_t iterations, void* stream) {
   // one list-build launch over every class (0: one launch per class and variant)
   grids.push_back(std::getenv("HDMD_BUILD_PER_CLASS")
                       ? 0
-                      : pow2_grid((B->n_nowrap_all + 3) / 4 + (B->n_cell_all - B->n_nowrap_all), 8192));
+                      : pow2_grid((B->n_nowrap_all + 3) / 4 + (B->n_atom_all + 3) / 4, 8192));
   grids.push_back(iterations);
   if (!graphs_enabled()) {
     for (int k = 0; k < iterations; k++) enqueue_batch_iter(B, grids, st);
