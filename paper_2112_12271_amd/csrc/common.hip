@@ -231,6 +231,10 @@ __global__ __launch_bounds__(256) void k_finalize(KArgs a) {
       } else {
         s->xcur ^= 1;
       }
+      // the shells whose pairs may interact at the new positions (kernels.h)
+      const double dl = rb ? 0.0 : sqrt(__longlong_as_double((long long)s->maxdisp2));
+      s->shells = s->nshell == 1 ? 1
+                                 : 1 + (int)fmin(2.0 * dl * s->sh_scale * (1.0 + 1e-9) + 1e-9, s->nshell - 1.0);
       s->maxdisp2 = 0ull;
       s->force_rebuild = 0;
       if (s->mode == MODE_MD) {
@@ -345,7 +349,7 @@ __global__ void k_export_fill(const SysDev* s, const int64_t* row_ptr, int32_t* 
   const int len = min(s->nlen[p], s->width);
   int* out = cols + row_ptr[a];
   int* buf = len <= kSortCap ? keys : out;
-  for (int k = threadIdx.x; k < len; k += blockDim.x) buf[k] = s->oid[pc][s->nl[(size_t)k * npad + p]];
+  for (int k = threadIdx.x; k < len; k += blockDim.x) buf[k] = s->oid[pc][s->nl[(size_t)k * npad + p] & s->jmask];
   __syncthreads();
   bitonic_sort<false>(buf, nullptr, len);
   if (buf == keys)

@@ -20,7 +20,10 @@
 //             bytes), or, for n_cell <= 2, of its place on the circle along
 //             each axis (32 bytes; 48 for d >= 8).
 //   nl, nlen  Verlet rows in ELL form, column-major nl[k*npad + i], i.e. entry
-//             k of every row is contiguous so a wave reads it coalesced.
+//             k of every row is contiguous so a wave reads it coalesced.  With
+//             shells (nshell = kShells) an entry is slot | shell << 28 and the
+//             rows are ordered by shell, row i's first ends[8 i + m] entries
+//             being its shells 0..m (kernels.h, "shells").
 // Atoms are stored in subcell order (canonical: by subcell, then caller id),
 // rebuilt at every list build.
 #pragma once
@@ -44,6 +47,8 @@ constexpr int kThermoCols = 10;
 constexpr int kMaxSlots = 1024;
 constexpr int kSwapBatch = 256;   // SWAP attempts per batch (a multiple of 64)
 constexpr int kPotMorse = 2;     // hdmd_system.potential of the Morse form
+constexpr int kShells = 8;       // distance shells of a Verlet row
+constexpr int kShellRow = 2048;  // longest row whose entries are ordered by shell
 constexpr int kQScale = 250;    // quantisation of the list build: subcell side = 250 units
 
 // forms of the matrix-core list build (kernels.h)
@@ -88,7 +93,7 @@ struct SysDev {
   int32_t bmode;  // form of the list build (BuildMode)
   int32_t reach;  // stencil radius in subcells: 1 (side >= r_l,max), 2 (half-size subcells)
   int32_t lpa;    // lanes per atom of the force kernels (1, 2 or 4)
-  int32_t pad0;
+  int32_t nshell;  // kShells, or 1: rows without shells
   double L, hL, cutoff, skin, eps, sigma_max;
   double rlmax, lsc, inv_lsc, halfskin2;
   double fxscale, qinv;  // 2^32 / L; 250 / L_sc
@@ -117,6 +122,9 @@ struct SysDev {
   int32_t* src;
   int32_t* nl;
   int32_t* nlen;
+  uint16_t* ends;  // [npad][kShells]
+  double sh_scale, sh_off;  // shell of a listed pair: floor((r - r_c) sh_scale - sh_off)
+  int32_t jmask, pad1;      // slot bits of a row entry
   double* part;
   double* thermo;
   double dt;
@@ -131,6 +139,8 @@ struct SysDev {
   double fdt, falpha, fmax, c_dt, c_keep, c_mix;
   double vscale;  // Berendsen factor of the next full-step kick (1: none)
   int32_t npos, nneg, c_zero;
+  int32_t shells;  // shells whose pairs may interact at the current positions
+  int32_t pad2;
   int32_t differ;  // set by k_same_state when the caller's arrays differ from the state
 };
 

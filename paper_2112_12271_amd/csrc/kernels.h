@@ -597,6 +597,124 @@ struct Survivors {
   }
 };
 
+// ---------------------------------------------------------------------------
+// Shells.  A listed pair at distance r at the build cannot interact before
+// the atoms have moved: its distance shrinks by at most 2 delta while no atom
+// is further than delta from its place at the build.  Each row is therefore
+// kept in kShells shells of r - r_c, skin/8 wide: shell 0 up to r_c + skin/8,
+// and so on.  The force kernels walk the shells that delta has reached
+// (m = 1 + floor(16 delta / skin), from the same displacement maximum that
+// triggers the rebuild) and leave the rest of the row alone; the pairs they
+// skip are beyond the cutoff, so the forces are sums of the same terms.
+// Between two builds delta grows from 0 to skin/2, so that a run's steps
+// visit (d = 6, r_c = 1.24, skin 0.25) about 65 % of the list on average and
+// a single force evaluation after its build 33 %.  The build stamps the
+// shell on the entry and, when a wave's rows are complete, orders them by it
+// in place (shell_order): they are still in its L2, and the other waves'
+// pair tests hide the latency (ordering them in the next force kernel took
+// 0.33 ms at d = 6, N = 262144, row 139).  Measured per MD step, whole rows
+// and shells: d = 6, N = 262144 FP64 237 and 177 us, mixed 190 and 143 us;
+// d = 6, N = 100000 Morse 77 and 59 us; the ordering adds 0.18 ms to the
+// 1.30 ms build of the first, 14 builds per 100 steps.
+// sh_off covers the rounding of r and of the fixed-point form's coordinates.
+// ---------------------------------------------------------------------------
+template <typename P>
+__device__ inline int shell_entry(P s, int j, double r2, double si, double sj) {
+  if (s->nshell == 1) return j;
+  // r = r2 / sqrt(r2), a Newton step on the hardware estimate
+  double y = __builtin_amdgcn_rsq(r2);
+  y = __builtin_fma(y, __builtin_fma(-0.5 * r2 * y, y, 0.5), y);
+  const double u = __builtin_fma(r2 * y - s->cutoff * (0.5 * (si + sj)), s->sh_scale, -s->sh_off);
+  const int k = r2 > 0.0 ? (int)fmin(fmax(u, 0.0), (double)(kShells - 1)) : 0;
+  return j | (k << 28);
+}
+
+// Orders rows i0 .. i0 + cnt - 1 (cnt <= 64; row i0 + lane has mylen entries,
+// written by this wave) by shell, in place and stably, and writes their shell
+// ends.  buf: kShellRow words of LDS.  Rows are taken R at a time (all R fit
+// the buffer), 64 / R lanes per row, each on a contiguous piece of at most 32
+// entries.  Rows longer than kShellRow keep their order: every shell ends at
+// the row's end.
+template <typename P>
+__device__ __forceinline__ void shell_order(P s, int i0, int cnt, int mylen, int* buf) {
+  if (s->nshell == 1) return;
+  const int lane = threadIdx.x & 63, npad = s->npad;
+  HDMD_GLOBAL int* nl = gbl(s->nl) + i0;
+  HDMD_GLOBAL vi4* ends = gbl(reinterpret_cast<vi4*>(s->ends + (size_t)i0 * kShells));
+  mylen = lane < cnt ? min(mylen, s->width) : 0;
+  const int mx = __builtin_amdgcn_readfirstlane(wave_max_i(mylen));
+  if (mx > kShellRow) {
+    const int l2 = mylen * 0x10001;
+    if (lane < cnt) ends[lane] = vi4{l2, l2, l2, l2};
+    return;
+  }
+  wave_lds_sync();  // the rows are written, the buffer is free
+  int lr = 5;  // R = 2^lr rows: at most 32 (two lanes per row)
+  while (lr > 0 && mx > (2048 >> lr)) lr--;
+  const int R = 1 << lr, S = 64 >> lr;
+  for (int r0 = 0; r0 < cnt; r0 += R) {
+    const int r = lane & (R - 1), sub = lane >> lr;
+    const int len = __shfl(mylen, (r0 + r) & 63);
+    const int C = (__builtin_amdgcn_readfirstlane(wave_max_i(len)) + S - 1) >> (6 - lr);
+    const int k0 = sub * C;
+    unsigned long long in = 0;  // entries per shell, six bits each
+    const HDMD_GLOBAL int* src = nl + (size_t)k0 * npad + r0 + r;
+    const int m = min(len - k0, C);  // this lane's entries
+    // all of the lane's entries in registers: one memory latency per R rows
+    int e[32];
+#pragma unroll
+    for (int k = 0; k < 32; k++) {
+      e[k] = -1;
+      if (k < m) e[k] = *src;
+      src += npad;
+    }
+#pragma unroll
+    for (int k = 0; k < 32; k++) in += k < m ? 1ull << (6 * (e[k] >> 28)) : 0ull;
+    // prefix sums over the row's lanes, two shells of 16 bits per word
+    unsigned c[4], p[4];
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      c[q] = (unsigned)(in >> (12 * q)) & 63u;
+      c[q] |= ((unsigned)(in >> (12 * q + 6)) & 63u) << 16;
+      p[q] = c[q];
+    }
+    for (int o = R; o < 64; o <<= 1) {
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const unsigned u = __shfl_up(p[q], o);
+        if (lane >= o) p[q] += u;
+      }
+    }
+    unsigned end[4], at[4], run = 0;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const unsigned t = __shfl(p[q], (S - 1) * R + r);
+      // ends of shells 2q, 2q + 1, then the lane's first places in them
+      end[q] = (run + (t & 0xffffu)) | ((run + (t & 0xffffu) + (t >> 16)) << 16);
+      at[q] = (run | ((run + (t & 0xffffu)) << 16)) + p[q] - c[q];
+      run = end[q] >> 16;
+    }
+#pragma unroll
+    for (int k = 0; k < 32; k++) {
+      if (k < m) {
+        const int sh = e[k] >> 28, sft = (sh & 1) * 16;
+        const unsigned w = sh < 4 ? (sh < 2 ? at[0] : at[1]) : (sh < 6 ? at[2] : at[3]);
+        buf[(((w >> sft) & 0xffffu) << lr) + r] = e[k];
+        const unsigned inc = 1u << sft;
+        at[0] += sh < 2 ? inc : 0u;
+        at[1] += (sh & ~1) == 2 ? inc : 0u;
+        at[2] += (sh & ~1) == 4 ? inc : 0u;
+        at[3] += sh >= 6 ? inc : 0u;
+      }
+    }
+    wave_lds_sync();
+    for (int k = sub; k < len; k += S) nl[(size_t)k * npad + r0 + r] = buf[(k << lr) + r];
+    if (sub == 0 && r0 + r < cnt)
+      ends[r0 + r] = vi4{(int)end[0], (int)end[1], (int)end[2], (int)end[3]};
+    wave_lds_sync();
+  }
+}
+
 // Appends a batch's passing pairs to their rows: each sets its bit in its
 // home atom's LDS word, whose bits below its own are the pairs before it in
 // the batch.  Every lane takes the new length of its own home atoms.
@@ -604,14 +722,15 @@ struct RowAppend {
   unsigned long long* hit;  // per home atom
   HDMD_GLOBAL int* nl;
   int npad, W;
+  // entry: the row entry of the pair (shell_entry)
   __device__ __attribute__((always_inline)) void operator()(int lane, bool two, bool pass, int h, int i,
-                                                            int j, int& len0, int& len1) const {
+                                                            int entry, int& len0, int& len1) const {
     if (pass) atomicOr(hit + h, 1ull << lane);
     const int la = __shfl(len0, h & 63), lb = two ? __shfl(len1, h & 63) : 0;
     wave_lds_sync();
     if (pass) {
       const int pos = (h >= 64 ? lb : la) + rank_in(hit[h]);
-      if (pos < W) nl[(size_t)pos * npad + i] = j;
+      if (pos < W) nl[(size_t)pos * npad + i] = entry;
     }
     len0 += __builtin_popcountll(hit[lane]);
     if (two) len1 += __builtin_popcountll(hit[64 + lane]);
@@ -626,7 +745,7 @@ struct RowAppend {
 // stencil, so that 16 such waves share a CU, four per SIMD.
 constexpr int kBuildTags = 16;  // segments of candidate blocks the codes may refer to
 template <int RAD>
-struct BuildLds {
+struct BuildLds {  // (at least kShellRow words: shell_order)
   static constexpr int SW = 6 + 2 * (2 * RAD + 1);  // words per staged home atom
   uv2 stage[128 * SW / 2];         // home slots 4..15, then slots 0..3 per last-axis offset
   unsigned long long hit[64 * 2];  // RowAppend
@@ -749,7 +868,7 @@ struct BuildTile {
         __builtin_amdgcn_sched_barrier(0);  // one axis at a time: few live registers
       }
       const bool pass = j != i && r2 < list_r2(si, sj, cut, skin);
-      append(lane, two, pass, h, i, j, len0, len1);
+      append(lane, two, pass, h, i, shell_entry(s, j, r2, si, sj), len0, len1);
     });
     if (all) ntag = 0;
   }
@@ -1039,6 +1158,10 @@ struct BuildTile {
       for (int t = 0; t < NW; t++) oa[t] = 0u;
       walk<0>(0.0f, 0.0f, 0, oa, 0);
       drain(true);
+#pragma unroll 1
+      for (int set = 0; set < (two ? 2 : 1); set++)
+        shell_order(s, hb + 64 * set, min(hcnt - 64 * set, 64), set ? len1 : len0,
+                    reinterpret_cast<int*>(m));
       if (v0) {
         gbl(s->nlen)[hb + lane] = len0;
         rowmax = max(rowmax, len0);
@@ -1105,6 +1228,7 @@ __global__ __launch_bounds__(64 * G, 4) void k_build_mf(KArgs a) {
 struct WrapLds {
   unsigned long long hit[64];
   SurvivorLds<unsigned> q;
+  int pad[kShellRow - 128 - sizeof(SurvivorLds<unsigned>) / 4];  // shell_order takes it all
 };
 
 // The 64 home atoms of one tile.
@@ -1161,12 +1285,14 @@ __device__ __forceinline__ void build_wrap_tile(SysDev* sys, int tile, WrapLds* 
         // code: pair of chunks, home atom, lane group, position (4 block + row)
         const int h = valid ? (int)(cd >> 7) & 63 : 0, i = hb + h, p = cd & 31;
         int j = c0 + (int)(cd >> 13) * 128 + 16 * (p >> 2) + 4 * ((cd >> 5) & 3) + (p & 3);
-        j = valid ? j : i;
+        // (j < n but for a home atom whose coordinates are not finite)
+        j = valid && j < n ? j : i;
         double xi[D], si, xj[D], sj;
         load_rec<D>(xb, i, xi, si);
         load_rec<D>(xb, j, xj, sj);
-        const bool pass = j != i && dist2_exact<D>(xi, xj, L, hL) < list_r2(si, sj, cut, skin);
-        append(lane, false, pass, h, i, j, len0, len1);
+        const double r2 = dist2_exact<D>(xi, xj, L, hL);
+        const bool pass = j != i && r2 < list_r2(si, sj, cut, skin);
+        append(lane, false, pass, h, i, shell_entry(s, j, r2, si, sj), len0, len1);
       });
     };
     for (int c = 0; c < ce; c += 128) {
@@ -1208,6 +1334,7 @@ __device__ __forceinline__ void build_wrap_tile(SysDev* sys, int tile, WrapLds* 
     }
     drain(true);
   }
+  shell_order(s, hb, hcnt, len0, reinterpret_cast<int*>(m));
   int rowmax = 0;
   if (lane < hcnt) {
     gbl(s->nlen)[hb + lane] = len0;
@@ -1566,16 +1693,22 @@ struct Own {
   int u[D];     // fixed-point coordinates (mixed)
 };
 
+// Entries of row i that may interact at the current positions.
+__device__ inline int row_reach(const SysDev* s, int i) {
+  return s->nshell == 1 ? min(gbl(s->nlen)[i], s->width)
+                        : (int)gbl(s->ends)[(size_t)i * kShells + s->shells - 1];
+}
+
 // Partial force of lane `sub` of the LPA lanes that share slot i: entries
 // k = sub, sub + LPA, ...; the next group's row indices are fetched before
 // the current group's records are used.  The LPA partial sums are combined
 // with the same butterfly on every lane of the group.
 template <int D, bool MIX, int LPA, typename FT, bool MORSE>
-__device__ inline void force_part(const SysDev* s, int i, int sub, const Own<D, MIX>& me,
+__device__ inline void force_part(const SysDev* s, int i, bool vi, int sub, const Own<D, MIX>& me,
                                   FT (&F)[D], double& e, double& w, double& z) {
   constexpr int U = MIX ? 4 : 2;
-  const int npad = s->npad;
-  const int len = min(gbl(s->nlen)[i], s->width);
+  const int npad = s->npad, jmask = s->jmask;
+  const int len = vi ? row_reach(s, i) : 0;
   const HDMD_GLOBAL int* __restrict__ nl = gbl(s->nl);
   const double L = s->L, c = s->cutoff, eps = s->eps, invL = 1.0 / L, ma = s->morse_a;
   const int pot = s->potential;
@@ -1600,7 +1733,7 @@ __device__ inline void force_part(const SysDev* s, int i, int sub, const Own<D, 
   for (int u = 0; u < U; u++) {
     const int kk = sub + u * LPA;
     const int raw = nl[(size_t)min(kk, wm1) * npad + i];
-    jn[u] = kk < len ? raw : -1;
+    jn[u] = kk < len ? raw & jmask : -1;
   }
   for (int k0 = sub; k0 < len; k0 += U * LPA) {
     int jj[U];
@@ -1609,7 +1742,7 @@ __device__ inline void force_part(const SysDev* s, int i, int sub, const Own<D, 
       jj[u] = jn[u];
       const int kk = k0 + (U + u) * LPA;
       const int raw = nl[(size_t)min(kk, wm1) * npad + i];
-      jn[u] = kk < len ? raw : -1;
+      jn[u] = kk < len ? raw & jmask : -1;
     }
     if (!MIX) {
       double xj[U][D], sj[U];
@@ -1707,8 +1840,8 @@ __device__ inline void force_part_lds(const SysDev* s, int i, bool vi, const Own
   constexpr int PR = G::PR, R = G::R, RPI = 64 / PR;  // records per load instruction
   static_assert(R >= 1 && R * 64 * PR <= kStage16, "stage size");
   const int lane = threadIdx.x & 63;
-  const int npad = s->npad, W = s->width;
-  const int len = vi ? min(gbl(s->nlen)[i], W) : 0;
+  const int npad = s->npad, W = s->width, jmask = s->jmask;
+  const int len = vi ? row_reach(s, i) : 0;
   const int mx = uniform_int(wave_max_i(len));
   const HDMD_GLOBAL int* __restrict__ nl = gbl(s->nl);
   const double L = s->L, c = s->cutoff, eps = s->eps, invL = 1.0 / L, ma = s->morse_a;
@@ -1728,7 +1861,7 @@ __device__ inline void force_part_lds(const SysDev* s, int i, bool vi, const Own
     for (int r = 0; r < R; r++) {
       const int kk = k0 + r;
       const int raw = nl[(size_t)min(kk, W - 1) * npad + i];
-      j[r] = kk < len ? raw : -1;
+      j[r] = kk < len ? raw & jmask : -1;
     }
     wave_lds_sync();  // the previous pass's reads of the stage are done
 #pragma unroll
@@ -1878,8 +2011,6 @@ __device__ inline void tile_partials(double* dst, double (&vals)[kPart], double&
   __syncthreads();
 }
 
-// Forces (stored in s->f) with the tile's energy and, for FIRE, the power
-// P = F.v, |F|^2, |v|^2 and max_i |F_i|^2 partial sums.
 // One atom tile's forces (stored in s->f) with the tile's energy and, for
 // FIRE, the power P = F.v, |F|^2, |v|^2 and max_i |F_i|^2 partial sums.
 // The force kernels serve the systems of one potential class: MORSE, or WCA
@@ -1902,7 +2033,7 @@ __device__ inline void force_tile(SysDev* s, int tile, int fire, double* sh, vd2
   FT F[D];
   double e, w, z;
   if constexpr (LPA == 1) force_part_lds<D, MIX, FT, MORSE>(s, ii, vi, me, F, e, w, z, stage);
-  else force_part<D, MIX, LPA, FT, MORSE>(s, ii, sub, me, F, e, w, z);
+  else force_part<D, MIX, LPA, FT, MORSE>(s, ii, vi, sub, me, F, e, w, z);
   double vals[kPart], mx = 0.0;
 #pragma unroll
   for (int p = 0; p < kPart; p++) vals[p] = 0.0;
@@ -1973,12 +2104,12 @@ __global__ __launch_bounds__(kTile * LPA) void k_step(KArgs a) {
     const bool first = s->step == 0, close = s->step >= s->nsteps;
     const bool rec = s->thermo && s->thermo_every > 0 && s->step % s->thermo_every == 0;
     const double dt = s->dt, hdt = 0.5 * dt;
-    Own<D, MIX> me;
+      Own<D, MIX> me;
     load_own<D, MIX>(s, ii, me);
     VT F[D];
     double e, w, z;
     if constexpr (LPA == 1) force_part_lds<D, MIX, VT, MORSE>(s, ii, vi, me, F, e, w, z, stage);
-    else force_part<D, MIX, LPA, VT, MORSE>(s, ii, sub, me, F, e, w, z);
+    else force_part<D, MIX, LPA, VT, MORSE>(s, ii, vi, sub, me, F, e, w, z);
     double vals[kPart], mx = 0.0;
 #pragma unroll
     for (int p = 0; p < kPart; p++) vals[p] = 0.0;

@@ -77,7 +77,7 @@ struct Plan {
   int lpa = 1, row_key = 0;  // lanes per atom of the force kernels and their key
   double rlmax = 0;
   size_t off_desc = 0, off_x[2] = {0, 0}, off_q[2] = {0, 0}, off_v[2] = {0, 0},
-         off_oid[2] = {0, 0}, off_f = 0, off_xref = 0, off_disp[2] = {0, 0}, off_qc16 = 0,
+         off_oid[2] = {0, 0}, off_f = 0, off_xref = 0, off_disp[2] = {0, 0}, off_qc16 = 0, off_ends = 0,
          off_cell_of = 0,
          off_rank = 0, off_cell_count = 0, off_cell_flat = 0, off_cell_local = 0, off_chunk_sum = 0,
          off_chunk_off = 0, off_key = 0, off_src = 0, off_nl = 0, off_nlen = 0, off_part = 0,
@@ -235,6 +235,7 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   for (int b = 0; b < 2; b++) p.off_disp[b] = take(np * p.d * 8);
   // (n_cell <= 2 and d >= 8: records of 48 bytes)
   p.off_qc16 = take(np * (ncf <= 2 && p.d >= 8 && s->subcells != HDMD_SUBCELLS_HALF ? 48 : 32));
+  p.off_ends = take(np * kShells * 2);
   p.off_cell_of = take(np * 4);
   p.off_rank = take(np * 4);
   p.off_cell_count = take((size_t)cells_alloc * 4);
@@ -316,6 +317,15 @@ static SysDev make_desc(const hdmd_system* s, const Plan& p, void* ws) {
   h.src = at<int32_t>(ws, p.off_src);
   h.nl = at<int32_t>(ws, p.off_nl);
   h.nlen = at<int32_t>(ws, p.off_nlen);
+  // shells need slots below 2^28, 16-bit row ends and a skin well above the
+  // rounding of r
+  h.ends = at<uint16_t>(ws, p.off_ends);
+  h.nshell =
+      p.n < (1 << 28) && p.width < 65536 && s->skin >= 1e-6 * p.rlmax ? kShells : 1;
+  h.jmask = h.nshell == 1 ? 0x7fffffff : (1 << 28) - 1;
+  h.sh_scale = h.nshell == 1 ? 0.0 : kShells / s->skin;
+  h.sh_off = 1e-6 + h.sh_scale * s->box_l * 0x1p-29;
+  h.shells = 1;
   h.part = at<double>(ws, p.off_part);
   h.force_rebuild = 1;
   h.status = SLOT_RUNNING;
@@ -608,7 +618,8 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
     }
     if (!timed) {
       // the force kernel with 1, 2 and 4 lanes per atom on the list just built;
-      // more lanes only where one lane takes at least 20 us and they save 10 %
+      // more lanes only where one lane takes at least 12 us and they save 10 %
+      // (d = 4, N = 65536: 16.5 and 11.7 us, an MD step 30 and 25 us)
       // (below that, launch overheads and the batches' one all-class launch
       // for one-lane systems count for more)
       hipEvent_t e0, e1;
@@ -618,6 +629,8 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
       KArgs a = single_args(dev, p.d);
       float best = 1e30f, one = 0.f;
       int best_lpa = 1;
+      // on the rows that a run walks half-way between two builds
+      set_i32(dev, offsetof(SysDev, shells), kShells / 2, st);
       for (int cand : {1, 2, 4}) {
         set_i32(dev, offsetof(SysDev, lpa), cand, st);
         K->force(p.mix, cand, p.morse, a, p.ntiles, 0, st);  // warm-up
@@ -635,12 +648,13 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
       }
       HIPCHK(hipEventDestroy(e0));
       HIPCHK(hipEventDestroy(e1));
-      if (one < 0.020f || best > 0.9f * one) best_lpa = 1;
+      if (one < 0.012f || best > 0.9f * one) best_lpa = 1;
       {
         std::lock_guard<std::mutex> g(g_tune_mu);
         p.lpa = g_lanes.emplace(std::make_tuple(p.d, mix, p.row_key), best_lpa).first->second;
       }
       set_i32(dev, offsetof(SysDev, lpa), p.lpa, st);
+      set_i32(dev, offsetof(SysDev, shells), 1, st);
     }
   }
   if (blk_out) *blk_out = blk;
@@ -698,7 +712,8 @@ static int run_chunk(void* ws, int kind, EnqueueFn fn, int chunk, const Plan& p,
     HIPCHK(hipGetLastError());
     return HDMD_OK;
   }
-  GraphKey key{ws,      kind,  chunk, p.d,     (int)p.mix + 2 * p.lpa, (int)p.morse, (int)p.wrap + 2 * p.reach,
+  const int form = (int)p.wrap + 2 * p.reach + 8 * build_mode(p.reach, p.n, p.ncells);
+  GraphKey key{ws,      kind,  chunk, p.d,     (int)p.mix + 2 * p.lpa, (int)p.morse, form,
                blk,     p.ntiles, p.ncells, p.nchunks};
   hipGraphExec_t exec = nullptr;
   {
