@@ -67,7 +67,7 @@ __global__ __launch_bounds__(256) void k_scan1(KArgs a) {
     SysDev* s;
     int ch;
     if (!fetch_chunk_tile(a, t, s, ch)) break;
-    if (!running(s) || !need_rebuild(s)) {
+    if (!rebuilding(a, s)) {
       if (a.single) break;  // one system: the same for every tile
       continue;
     }
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void k_scan2(KArgs a) {
   for (int t = blockIdx.x;; t += gridDim.x) {
     SysDev* s;
     if (!fetch_sys(a, t, s)) break;
-    if (!running(s) || !need_rebuild(s)) {
+    if (!rebuilding(a, s)) {
       if (a.single) break;  // one system: the same for every tile
       continue;
     }
@@ -139,195 +139,33 @@ __global__ __launch_bounds__(kTile) void k_scatter(KArgs a) {
     SysDev* s;
     int tile;
     if (!fetch_atom_tile(a, t, s, tile)) break;
-    if (!running(s) || !need_rebuild(s)) {
+    if (!rebuilding(a, s)) {
       if (a.single) break;  // one system: the same for every tile
       continue;
     }
     const int i = tile * kTile + threadIdx.x;
     if (i >= s->n) continue;
-    const int c = s->cell_of[i];
-    const int slot = cell_start(s, c) + s->rank[i];
-    int key = s->oid[s->pcur][i];
-    if (s->ysort) {
-      // the offset along the last axis exactly as the subcell sort quantises
-      // it (caller ids below 2^23)
-      const double xl = s->x[s->xcur ^ 1][(size_t)i * rec_stride(s->d) + s->d - 1];
-      key |= (quant8(xl - last_centre(s, c), s->qinv) + 128) << 23;
-    }
-    s->key[slot] = key;
-    s->src[slot] = i;
+    scatter_atom(s, i, s->cell_of[i], s->rank[i]);
   }
 }
 
-// End of a step / iteration for one system: energy reductions and thermo
-// row (MD), buffer flips (the permuted buffers after a rebuild, otherwise the
-// freshly written position buffer), trigger reset, step counter.
-__global__ __launch_bounds__(256) void k_finalize(KArgs a) {
-  __shared__ double sh[256];
-  const int tid = threadIdx.x;
+// Finalisation of the systems of a batch (and of a system's first build).
+__global__ __launch_bounds__(64) void k_finalize(KArgs a) {
   for (int t = blockIdx.x;; t += gridDim.x) {
     SysDev* s;
     if (!fetch_sys(a, t, s)) break;
-    if (!running(s)) continue;
-    const bool rb = need_rebuild(s);
-    if (s->mode == MODE_MD) {
-      const int nw = s->nwaves, per = (nw + 255) / 256;
-      const bool rec = s->thermo && s->thermo_every > 0 && s->step % s->thermo_every == 0;
-      double pe = 0.0, ke = 0.0, vir = 0.0, nc = 0.0, m2 = 0.0, m4 = 0.0, ov = 0.0;
-      for (int w = tid * per; w < min(nw, (tid + 1) * per); w++) {
-        const double* pw = s->part + (size_t)w * kPart;
-        pe += pw[P_PE];
-        ke += pw[P_KE];
-        if (rec) {
-          vir += pw[P_VIR];
-          nc += pw[P_NC];
-          m2 += pw[P_M2];
-          m4 += pw[P_M4];
-          ov += pw[P_OV];
-        }
-      }
-      pe = block_sum<256>(pe, sh);
-      ke = block_sum<256>(ke, sh);
-      if (rec) {
-        vir = block_sum<256>(vir, sh);
-        nc = block_sum<256>(nc, sh);
-        m2 = block_sum<256>(m2, sh);
-        m4 = block_sum<256>(m4, sh);
-        ov = block_sum<256>(ov, sh);
-      }
-      if (tid == 0) {
-        s->pe = pe;
-        s->ke = ke;
-        if (!isfinite(pe + ke)) s->err |= ERR_RUN_NAN;
-        // Berendsen factor for the next full-step kick, from this step's T
-        if (s->tau_t > 0.0 && ke > 0.0) {
-          const double T = 2.0 * ke / ((double)s->d * (double)(s->n - 1));
-          s->vscale = sqrt(1.0 + s->dt / s->tau_t * (s->temp_t / T - 1.0));
-        } else {
-          s->vscale = 1.0;
-        }
-        if (rec) {
-          double* r = s->thermo + kThermoCols * (s->step / s->thermo_every);
-          r[0] = (double)s->step;
-          r[1] = ke;
-          r[2] = pe;
-          r[3] = ke + pe;
-          r[4] = vir;                 // sum over pairs of r_ij . F_ij
-          r[5] = nc / (double)s->n;   // mean neighbours inside the cutoff (Z)
-          // displacement moments since the run's start, alpha_2 (eq. ngp; 0
-          // while nothing has moved) and f_ov (eq. fov)
-          const double msd = m2 / (double)s->n, mqd = m4 / (double)s->n;
-          r[6] = msd;
-          r[7] = mqd;
-          r[8] = msd > 0.0 ? s->d * mqd / ((s->d + 2) * msd * msd) - 1.0 : 0.0;
-          r[9] = ov / (double)s->n;
-        }
-      }
-    }
-    if (tid == 0) {
-      if (rb) {
-        s->pcur ^= 1;
-        s->builds++;
-      } else {
-        s->xcur ^= 1;
-      }
-      // the shells whose pairs may interact at the new positions (kernels.h)
-      const double dl = rb ? 0.0 : sqrt(__longlong_as_double((long long)s->maxdisp2));
-      s->shells = s->nshell == 1 ? 1
-                                 : 1 + (int)fmin(2.0 * dl * s->sh_scale * (1.0 + 1e-9) + 1e-9, s->nshell - 1.0);
-      s->maxdisp2 = 0ull;
-      s->force_rebuild = 0;
-      if (s->mode == MODE_MD) {
-        s->step++;
-        if (s->step > s->nsteps) s->status = SLOT_DONE;
-      }
-      if (s->err) s->status = SLOT_DONE;
-    }
-    __syncthreads();
+    finalize_system(s, need_rebuild(s));
   }
 }
 
-// FIRE 2.0 control for one system (semi-implicit Euler variant, unit masses):
-// fixed-order reductions of the wave partials, convergence test on the
-// current forces, then the P = F.v branch, dt / alpha updates and the mixing
-// coefficients.  |v + dt F|^2 is formed from |v|^2, F.v and |F|^2.
-__global__ __launch_bounds__(256) void k_fire_ctrl(KArgs a) {
-  __shared__ double sh[256];
-  const int tid = threadIdx.x;
+// FIRE 2.0 control of the systems of a batch and of large systems.
+__global__ __launch_bounds__(64) void k_fire_ctrl(KArgs a) {
   for (int t = blockIdx.x;; t += gridDim.x) {
     SysDev* s;
     if (!fetch_sys(a, t, s)) break;
-    if (!running(s) || s->mode != MODE_FIRE) continue;
-    const int nw = s->nwaves, per = (nw + 255) / 256;
-    double pe = 0, fv = 0, ff = 0, vv = 0, fm = 0;
-    for (int w = tid * per; w < min(nw, (tid + 1) * per); w++) {
-      const double* p = s->part + (size_t)w * kPart;
-      pe += p[P_PE];
-      fv += p[P_FV];
-      ff += p[P_FF];
-      vv += p[P_VV];
-      fm = fmax(fm, p[P_FMAX2]);
-    }
-    pe = block_sum<256>(pe, sh);
-    fv = block_sum<256>(fv, sh);
-    ff = block_sum<256>(ff, sh);
-    vv = block_sum<256>(vv, sh);
-    fm = block_max<256>(fm, sh);
-    if (tid == 0) {
-      const FireCtl& c = s->fc;
-      s->pe = pe;
-      s->fmax = sqrt(fm);
-      if (!isfinite(pe) || !isfinite(ff)) {
-        s->err |= ERR_RUN_NAN;
-        s->status = SLOT_DONE;
-        s->fstatus = -5;
-      } else if (sqrt(fm) < c.ftol || (c.etol > 0.0 && pe / (double)s->n < c.etol)) {
-        s->status = SLOT_DONE;
-        s->fstatus = 0;
-      } else if (s->iters >= c.maxiter) {
-        s->status = SLOT_DONE;
-        s->fstatus = 1;
-      } else {
-        double dt = s->fdt, alpha = s->falpha;
-        int zero = 0;
-        bool stop = false;
-        if (fv > 0.0) {
-          s->npos++;
-          s->nneg = 0;
-          if (s->npos > c.ndelay) {
-            dt = fmin(dt * c.finc, c.dtmax);
-            alpha *= c.falpha;
-          }
-        } else {
-          s->npos = 0;
-          s->nneg++;
-          if (s->nneg > c.nnegmax) {
-            stop = true;
-          } else {
-            if (!(c.initdelay && s->iters < c.ndelay)) {
-              if (dt * c.fdec >= c.dtmin) dt *= c.fdec;
-              alpha = c.alpha0;
-            }
-            zero = 1;
-          }
-        }
-        if (stop) {
-          s->status = SLOT_DONE;
-          s->fstatus = 1;
-        } else {
-          const double v2 = zero ? dt * dt * ff : vv + 2.0 * dt * fv + dt * dt * ff;
-          const double vn = sqrt(v2), fn = sqrt(ff);
-          s->fdt = dt;
-          s->falpha = alpha;
-          s->c_zero = zero;
-          s->c_dt = dt;
-          s->c_keep = fn > 0.0 ? 1.0 - alpha : 1.0;
-          s->c_mix = fn > 0.0 ? alpha * vn / fn : 0.0;
-          s->iters++;
-        }
-      }
-    }
-    __syncthreads();
+    if (!live(s) || s->mode != MODE_FIRE) continue;
+    const FireNext f = fire_control(s);
+    if (threadIdx.x == 0) fire_commit(s, f);
   }
 }
 
@@ -338,6 +176,37 @@ __global__ void k_export_lens(const SysDev* s, int64_t* row_ptr) {
   int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= s->n) return;
   row_ptr[s->oid[s->pcur][p] + 1] = min(s->nlen[p], s->width);
+}
+
+// All-ascending bitonic network; entries at index >= cnt act as +infinity, so
+// any length works.
+__device__ inline void bitonic_sort(int* keys, int cnt) {
+  int p2 = 1;
+  while (p2 < cnt) p2 <<= 1;
+  const int half = p2 >> 1;
+  auto cas = [&](int i, int p) {
+    if (p < cnt && keys[i] > keys[p]) {
+      const int k = keys[i];
+      keys[i] = keys[p];
+      keys[p] = k;
+    }
+  };
+  for (int size = 2; size <= p2; size <<= 1) {
+    const int hs = size >> 1;
+    for (int t = threadIdx.x; t < half; t += blockDim.x) {
+      const int blk = t / hs, off = t % hs;
+      cas(blk * size + off, blk * size + size - 1 - off);
+    }
+    __syncthreads();
+    for (int st = size >> 2; st > 0; st >>= 1) {
+      for (int t = threadIdx.x; t < half; t += blockDim.x) {
+        const int blk = t / st, off = t % st;
+        const int i = blk * 2 * st + off;
+        cas(i, i + st);
+      }
+      __syncthreads();
+    }
+  }
 }
 
 __global__ void k_export_fill(const SysDev* s, const int64_t* row_ptr, int32_t* cols) {
@@ -351,7 +220,7 @@ __global__ void k_export_fill(const SysDev* s, const int64_t* row_ptr, int32_t* 
   int* buf = len <= kSortCap ? keys : out;
   for (int k = threadIdx.x; k < len; k += blockDim.x) buf[k] = s->oid[pc][s->nl[(size_t)k * npad + p] & s->jmask];
   __syncthreads();
-  bitonic_sort<false>(buf, nullptr, len);
+  bitonic_sort(buf, len);
   if (buf == keys)
     for (int k = threadIdx.x; k < len; k += blockDim.x) out[k] = keys[k];
 }
@@ -403,10 +272,10 @@ void launch_scatter(const KArgs& a, int grid, hipStream_t st) {
   k_scatter<<<grid, kTile, 0, st>>>(a);
 }
 void launch_finalize(const KArgs& a, int grid, hipStream_t st) {
-  k_finalize<<<grid, 256, 0, st>>>(a);
+  k_finalize<<<grid, 64, 0, st>>>(a);
 }
 void launch_fire_ctrl(const KArgs& a, int grid, hipStream_t st) {
-  k_fire_ctrl<<<grid, 256, 0, st>>>(a);
+  k_fire_ctrl<<<grid, 64, 0, st>>>(a);
 }
 // slot_of[caller id] = position in subcell order
 __global__ __launch_bounds__(256) void k_slot_of(const SysDev* s, int32_t* slot_of) {

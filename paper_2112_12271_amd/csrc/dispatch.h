@@ -15,7 +15,8 @@ struct DKernels {
                      const double* vel, const double* diam);
   void (*disp_restart)(SysDev* s, int grid, hipStream_t st);
   void (*bin)(const KArgs& a, int grid, hipStream_t st);
-  void (*cellsort)(bool mix, const KArgs& a, int grid, hipStream_t st);
+  // grid: workgroups of four tiles, and one for the finalisation
+  void (*place)(bool mix, const KArgs& a, int grid, hipStream_t st);
   // list build of the systems of n_cell >= 3 on one stencil radius (reach 1:
   // subcells of side >= r_l,max, 3^d stencil; 2: half-size subcells, 5^d
   // stencil) and of one form (BuildMode), with G = 1, 2 or 4 waves per subcell
@@ -45,7 +46,7 @@ const DKernels* dkernels(int d);
 // (KArgs.cls = 0; kern_all.hip)
 void launch_bin_all(const KArgs& a, int grid, hipStream_t st);
 void launch_fire_update_all(const KArgs& a, int grid, hipStream_t st);
-void launch_cellsort_all(const KArgs& a, int grid, hipStream_t st);
+void launch_place_all(const KArgs& a, int grid, hipStream_t st);
 void launch_force_all(const KArgs& a, int grid, int fire, bool morse, hipStream_t st);
 // list build and FIRE forces of the classes d <= kBuildAllMaxD; larger d keep
 // per-class launches

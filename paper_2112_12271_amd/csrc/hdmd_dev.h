@@ -39,7 +39,8 @@ constexpr int kMinD = 2;
 constexpr int kTile = 64;       // atoms per atom tile (one wave at one lane per atom)
 constexpr int kWave = 64;
 constexpr int kChunk = 1024;    // subcells per scan chunk
-constexpr int kSortCap = 4096;  // subcell occupancy sorted in LDS (larger: in global memory)
+constexpr int kSortCap = 4096;  // exported row sorted in LDS (longer: in global memory)
+constexpr int kBinBlock = 1024;  // threads per workgroup of the binning
 constexpr int kPart = 11;       // doubles per wave in the partial-sum array
 // step, KE, PE, KE+PE, virial W, coordination Z, <|Delta|^2>, <|Delta|^4>,
 // non-Gaussian alpha_2, overlap f_ov
@@ -81,6 +82,12 @@ enum Part : int {
 struct FireCtl {
   double dt0, dtmax, dtmin, finc, fdec, alpha0, falpha, ftol, etol;
   int64_t ndelay, nnegmax, maxiter, initdelay;
+};
+
+// What the FIRE control decides for an iteration (fire_control).
+struct FireNext {
+  double pe, fmax, fdt, falpha, c_keep, c_mix;
+  int32_t npos, nneg, zero, status, fstatus, err;
 };
 
 struct SysDev {
@@ -136,11 +143,16 @@ struct SysDev {
   int32_t max_row, max_cell, status, fstatus;
   int64_t step, builds, iters;
   double ke, pe;
-  double fdt, falpha, fmax, c_dt, c_keep, c_mix;
+  double fdt, falpha, fmax, c_keep, c_mix;
+  FireNext fnext;  // a lone system's iteration under way
   double vscale;  // Berendsen factor of the next full-step kick (1: none)
   int32_t npos, nneg, c_zero;
   int32_t shells;  // shells whose pairs may interact at the current positions
-  int32_t pad2;
+  // a rebuild under way: the state buffers before it (finalisation may flip
+  // the current ones while its kernels run) and, for a system alone, whether
+  // this iteration rebuilds
+  int32_t rx, rp, rb;
+  int32_t ticket;  // workgroups of the binning that have ended
   int32_t differ;  // set by k_same_state when the caller's arrays differ from the state
 };
 
@@ -166,11 +178,14 @@ struct Table {
 // Kernel arguments: either one system (tile = blockIdx) or a batch table.
 // part selects a sub-range of the cell tiles: 0 all, 1 systems with
 // n_cell >= 3, 2 systems with n_cell <= 2 (crowded subcells).
+// fin (a system alone): the placement kernel also finalises the iteration; 2:
+// a FIRE iteration whose update takes the control's decision itself.
 struct KArgs {
   SysDev* single;
   Table* tab;
   int32_t cls;
   int32_t part;
+  int32_t fin;
 };
 
 // Workgroups of a launch are handed to the eight XCDs in turn (workgroup b to
@@ -249,6 +264,19 @@ __device__ inline bool need_rebuild(P s) {
   return (s->force_rebuild != 0) | (__longlong_as_double((long long)s->maxdisp2) > s->halfskin2);
 }
 
+// The force, step and FIRE kernels also pass over a system whose list
+// overflowed in a build after its finalisation: it ends at the next one.
+template <typename P>
+__device__ inline bool live(P s) {
+  return running(s) && s->err == 0;
+}
+
+// Whether the rebuild chain's kernels after the binning have work.
+template <typename P>
+__device__ inline bool rebuilding(const KArgs& a, P s) {
+  return a.single ? s->rb != 0 : running(s) && need_rebuild(s);
+}
+
 // Descriptors and tables read through the constant address space: scalar
 // loads, whose values the compiler knows to be the same in every lane.  Only
 // for fields that the running kernel does not write.
@@ -286,6 +314,25 @@ __device__ inline bool fetch_cell_tile_u(const KArgs& a, int t, SysDev*& s, int&
   cell = e->y;
   return true;
 }
+
+// What the last workgroup of a lone system's binning does itself.  A step
+// without a rebuild pays 2.2 us for each launch of the chain, and there are
+// five to ten such steps to a rebuild.  Measured per rebuild, the binning
+// alone, with the prefix, and with both (launches of their own before):
+// d = 6, N = 262144, 46656 subcells 27 us (bin 99, scans 21 and 2 launches);
+// d = 3, N = 8192 36 us and N = 1000 17 us (bin, scans and scatter 20 and 4
+// launches).  Past 65536 subcells or 8192 atoms one workgroup takes longer
+// than the launches saved; k_scan1, k_scan2 and k_scatter run.
+__host__ __device__ constexpr bool bin_scans(int nchunks) { return nchunks <= 65536 / kChunk; }
+__host__ __device__ constexpr bool bin_scatters(int n, int nchunks) {
+  return n <= 8192 && bin_scans(nchunks);
+}
+
+// Largest system (in tiles) whose FIRE update kernel takes the control's
+// decision in every workgroup: the reduction of 256 partial sums costs each
+// wave about 2 us, the control's launch 6 (N = 8192: 17.9 us per iteration
+// with it).
+constexpr int kFireFused = 256;
 
 // Subcell start (exclusive prefix of occupancies), split in chunk-local part
 // and chunk offset; start(ncells) = n.
@@ -496,20 +543,6 @@ __device__ inline double block_sum(double v, double* sh) {
 #pragma unroll
   for (int s = BS / 2; s > 0; s >>= 1) {
     if (t < s) sh[t] = sh[t] + sh[t + s];
-    __syncthreads();
-  }
-  double r = sh[0];
-  __syncthreads();
-  return r;
-}
-template <int BS>
-__device__ inline double block_max(double v, double* sh) {
-  int t = threadIdx.x;
-  sh[t] = v;
-  __syncthreads();
-#pragma unroll
-  for (int s = BS / 2; s > 0; s >>= 1) {
-    if (t < s) sh[t] = fmax(sh[t], sh[t + s]);
     __syncthreads();
   }
   double r = sh[0];

@@ -1,6 +1,6 @@
 // kern_all.hip -- per-tile kernels of a batch launched once over the tiles
 // of every dimension class: each tile's system selects the
-// dimension-templated body (update, binning, subcell sort, list build,
+// dimension-templated body (update, binning, placement, list build,
 // forces).  One launch per kernel instead of one per class keeps the launch
 // count of a batch iteration independent of how many dimensions it mixes.
 #include "kernels.h"
@@ -14,7 +14,7 @@ namespace hdmd {
 // launches of their own
 #define HDMD_BUILD_D(X) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
 
-// The rebuild chain's kernels (binning, subcell sort, list build) run in
+// The rebuild chain's kernels (binning, placement, list build) run in
 // every iteration but find work only in the systems that rebuild, often one
 // of hundreds.  Their workgroups therefore test many tiles at once, one per
 // lane (tile entry, system pointer, flags: three dependent loads), and then
@@ -26,25 +26,6 @@ __device__ inline bool tile_rebuilds(const Table* tab, const int2* tiles, int t,
   e = tiles[t];
   const SysDev* s = tab->sys[e.x];
   return running(s) && need_rebuild(s) && s->d <= dmax;
-}
-
-// The flags f of a 256-thread workgroup, as four 64-bit ballots handed to
-// every wave (uniform); false when no flag is set.  xch is 32 bytes of LDS
-// that no wave uses on entry or exit.
-__device__ inline bool block_ballots(bool f, unsigned long long* xch, unsigned long long (&mk)[4]) {
-  const unsigned long long bal = __ballot(f);
-  if ((threadIdx.x & 63) == 0) xch[threadIdx.x >> 6] = bal;
-  __syncthreads();
-  unsigned long long any = 0;
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    const unsigned long long v = xch[q];
-    mk[q] = ((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
-            (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v);
-    any |= mk[q];
-  }
-  __syncthreads();
-  return any != 0;
 }
 
 __global__ __launch_bounds__(kTile) void k_bin_all(KArgs a) {
@@ -75,13 +56,14 @@ __global__ __launch_bounds__(kTile) void k_fire_update_all(KArgs a) {
     SysDev* s;
     int tile;
     if (!fetch_atom_tile(a, t, s, tile)) break;
-    if (!running(s) || s->mode != MODE_FIRE) continue;
-    const bool mix = s->precision != 0;
+    if (!live(s) || s->mode != MODE_FIRE) continue;
+    const bool mix = s->precision != 0, zero = s->c_zero != 0;
+    const double dt = s->fdt, keep = s->c_keep, mx = s->c_mix;
     switch (s->d) {
-#define HDMD_CASE(DD)                                    \
-  case DD:                                               \
-    if (mix) fire_update_tile<DD, true>(s, tile);        \
-    else fire_update_tile<DD, false>(s, tile);           \
+#define HDMD_CASE(DD)                                                  \
+  case DD:                                                             \
+    if (mix) fire_update_tile<DD, true>(s, tile, dt, keep, mx, zero);  \
+    else fire_update_tile<DD, false>(s, tile, dt, keep, mx, zero);     \
     break;
       HDMD_EACH_D(HDMD_CASE)
 #undef HDMD_CASE
@@ -89,38 +71,28 @@ __global__ __launch_bounds__(kTile) void k_fire_update_all(KArgs a) {
   }
 }
 
-__global__ __launch_bounds__(256) void k_cellsort_all(KArgs a) {
-  __shared__ int sk[kSortCap];
-  __shared__ int sv[kSortCap];
-  const int n = a.tab->n_cell[0], g = gridDim.x;
-  const int2* tiles = a.tab->cell_tiles[0];
-  for (int base = blockIdx.x; base < n; base += 256 * g) {
-    int2 e;
-    unsigned long long mk[4];
-    if (!block_ballots(tile_rebuilds(a.tab, tiles, base + (int)threadIdx.x * g, n, e),
-                       reinterpret_cast<unsigned long long*>(sk), mk))
-      continue;
-    for (int q = 0; q < 4; q++) {
-      unsigned long long mq = mk[q];
-      while (mq) {
-        const int k = 64 * q + __builtin_ctzll(mq);
-        mq &= mq - 1;
-        const int2 ek = tiles[base + k * g];
-        SysDev* s = a.tab->sys[ek.x];
-        const int c = ek.y;
-        const bool mix = s->precision != 0;
-        switch (s->d) {
-#define HDMD_CASE(DD)                                \
-  case DD:                                           \
-    if (mix) cellsort_tile<DD, float>(s, c, sk, sv); \
-    else cellsort_tile<DD, double>(s, c, sk, sv);    \
+__global__ __launch_bounds__(kTile) void k_place_all(KArgs a) {
+  const int n = a.tab->n_atom[0], g = gridDim.x, lane = threadIdx.x;
+  const int2* tiles = a.tab->atom_tiles[0];
+  for (int base = blockIdx.x; base < n; base += 64 * g) {
+    int2 e = make_int2(0, 0);
+    unsigned long long m = __ballot(tile_rebuilds(a.tab, tiles, base + lane * g, n, e));
+    while (m) {
+      const int k = __builtin_ctzll(m);
+      m &= m - 1;
+      SysDev* s = uniform_ptr(a.tab->sys[__builtin_amdgcn_readlane(e.x, k)]);
+      const int tile = __builtin_amdgcn_readlane(e.y, k);
+      const bool mix = s->precision != 0;
+      switch (s->d) {
+#define HDMD_CASE(DD)                          \
+  case DD:                                     \
+    if (mix) place_tile<DD, float>(s, tile);   \
+    else place_tile<DD, double>(s, tile);      \
     break;
-          HDMD_EACH_D(HDMD_CASE)
+        HDMD_EACH_D(HDMD_CASE)
 #undef HDMD_CASE
-        }
       }
     }
-    __syncthreads();  // the LDS exchange area is free again
   }
 }
 
@@ -133,7 +105,7 @@ __global__ __launch_bounds__(kTile) void k_force_all(KArgs a, int fire) {
     SysDev* s;
     int tile;
     if (!fetch_atom_tile(a, t, s, tile)) break;
-    if (!running(s) || (s->potential == kPotMorse) != MORSE || s->lpa != 1) continue;
+    if (!live(s) || (s->potential == kPotMorse) != MORSE || s->lpa != 1) continue;
     if (fire && s->mode != MODE_FIRE) continue;
     const bool mix = s->precision != 0;
     switch (s->d) {
@@ -227,8 +199,8 @@ void launch_force_all(const KArgs& a, int grid, int fire, bool morse, hipStream_
 void launch_fire_update_all(const KArgs& a, int grid, hipStream_t st) {
   k_fire_update_all<<<grid, kTile, 0, st>>>(a);
 }
-void launch_cellsort_all(const KArgs& a, int grid, hipStream_t st) {
-  k_cellsort_all<<<grid, 256, 0, st>>>(a);
+void launch_place_all(const KArgs& a, int grid, hipStream_t st) {
+  k_place_all<<<grid, kTile, 0, st>>>(a);
 }
 
 }  // namespace hdmd

@@ -29,10 +29,10 @@ void l_same_state(bool mix, SysDev* s, int grid, hipStream_t st, const double* p
 void l_disp_restart(SysDev* s, int grid, hipStream_t st) {
   k_disp_restart<D><<<grid, kTile, 0, st>>>(s);
 }
-void l_bin(const KArgs& a, int grid, hipStream_t st) { k_bin<D><<<grid, kTile, 0, st>>>(a); }
-void l_cellsort(bool mix, const KArgs& a, int grid, hipStream_t st) {
-  if (mix) k_cellsort<D, float><<<grid, 256, 0, st>>>(a);
-  else k_cellsort<D, double><<<grid, 256, 0, st>>>(a);
+void l_bin(const KArgs& a, int grid, hipStream_t st) { k_bin<D><<<grid, kBinBlock, 0, st>>>(a); }
+void l_place(bool mix, const KArgs& a, int grid, hipStream_t st) {
+  if (mix) k_place<D, float><<<grid, 256, 0, st>>>(a);
+  else k_place<D, double><<<grid, 256, 0, st>>>(a);
 }
 void l_build(int reach, int mode, int G, const KArgs& a, int grid, hipStream_t st) {
   if (reach == 2) {
@@ -110,7 +110,7 @@ void l_swap_settle(SysDev* s, hipStream_t st, long long* ctl, const int32_t* off
   k_swap_settle<D><<<1, 1024, 0, st>>>(s, ctl, off_in, off_out, n_att, pairs, u, T, slot_of, de,
                                        conf, acc, diam);
 }
-const DKernels table = {l_load, l_unload, l_same_state, l_disp_restart, l_bin, l_cellsort, l_build, l_build_wrap, l_force, l_step,
+const DKernels table = {l_load, l_unload, l_same_state, l_disp_restart, l_bin, l_place, l_build, l_build_wrap, l_force, l_step,
                         l_fire_update, l_vanhove, l_swap_de, l_swap_settle};
 }  // namespace
 

@@ -3,8 +3,8 @@
 //  k_load        caller [n][d] arrays -> internal buffers (wrap, validate)
 //  k_bin         subcell of every atom + occupancy counts      (Sec. II.C)
 //  k_scatter     counting-sort placement by subcell            (common.hip)
-//  k_cellsort    per-subcell sort by caller id, permutation of every per-atom
-//                array, reference positions, prefilter offsets
+//  k_place       order within the subcell, permutation of every per-atom
+//                array, reference positions, list-build records; finalisation
 //  k_build_mf, k_build_wrap  Verlet rows over the linked subcells (Sec. II.C, Fig. 1)
 //  k_force       pair forces and energy (+ FIRE reductions)    (Sec. II.B)
 //  k_step        fused velocity-Verlet step + rebuild trigger (Sec. II.B/II.C)
@@ -187,76 +187,185 @@ __device__ inline int flat_cell(const SysDev* s, const double (&x)[D]) {
   return I;
 }
 
-// One atom tile of a system that rebuilds: subcell index and arrival rank.
+// Loads and stores that pass by the caches that are not coherent over the
+// device: values handed from workgroup to workgroup of one launch.
+__device__ inline int load_agent(const int* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void store_agent(int* p, int v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One atom tile (a wave) of a system that rebuilds: subcell index and arrival
+// rank.  The wave adds to a subcell's count once for all its atoms there: in
+// the order of the last build most of a wave's atoms share a few subcells, and
+// one addition each made the counts the bottleneck (d = 8, N = 131072, 256
+// subcells: 300 us of same-address additions).
 template <int D>
 __device__ inline void bin_tile(SysDev* s, int tile) {
-  if (tile == 0 && threadIdx.x == 0) s->max_cell = 0;
-  int i = tile * kTile + threadIdx.x;
-  if (i >= s->n) return;
-  double x[D];
-  load_x<D>(s->x[s->xcur ^ 1], i, x);
-  if (s->mode == MODE_MD) {
-    // fold the displacement since the last build into the unwrapped
-    // displacement (it stays below L/2 between builds, so the minimum image
-    // is the true one)
-    double* dp = s->disp[s->pcur];
-    const size_t np = s->npad;
+  const int lane = threadIdx.x & 63;
+  if (tile == 0 && lane == 0) {
+    s->max_cell = 0;
+    s->rx = s->xcur;
+    s->rp = s->pcur;
+  }
+  const int i = tile * kTile + lane;
+  const bool vi = i < s->n;
+  int c = -1;
+  if (vi) {
+    double x[D];
+    load_x<D>(s->x[s->xcur ^ 1], i, x);
+    if (s->mode == MODE_MD) {
+      // fold the displacement since the last build into the unwrapped
+      // displacement (it stays below L/2 between builds, so the minimum image
+      // is the true one)
+      double* dp = s->disp[s->pcur];
+      const size_t np = s->npad;
 #pragma unroll
-    for (int k = 0; k < D; k++)
-      dp[k * np + i] += min_image(x[k] - s->xref[k * np + i], s->L, s->hL);
+      for (int k = 0; k < D; k++)
+        dp[k * np + i] += min_image(x[k] - s->xref[k * np + i], s->L, s->hL);
+    }
+    c = flat_cell<D>(s, x);
   }
-  int c = flat_cell<D>(s, x);
-  s->cell_of[i] = c;
-  s->rank[i] = atomicAdd(&s->cell_count[c], 1);
+  int rk = 0, lead = lane, cnt = 0;
+  unsigned long long todo = __ballot(vi);
+  while (todo) {
+    const int l = __builtin_ctzll(todo);
+    const unsigned long long m = __ballot(c == __builtin_amdgcn_readlane(c, l));
+    if (m >> lane & 1) {
+      rk = __popcll(m & ((1ull << lane) - 1));
+      lead = l;
+      cnt = __popcll(m);
+    }
+    todo &= ~m;
+  }
+  int base = 0;
+  if (vi && rk == 0) base = atomicAdd(&s->cell_count[c], cnt);
+  base = __shfl(base, lead);
+  if (vi) {
+    store_agent(s->cell_of + i, c);
+    store_agent(s->rank + i, base + rk);
+  }
 }
 
-template <int D>
-__global__ __launch_bounds__(kTile) void k_bin(KArgs a) {
-  for (int t = blockIdx.x;; t += gridDim.x) {
-    SysDev* s;
-    int tile;
-    if (!fetch_atom_tile(a, t, s, tile)) break;
-    if (!running(s) || !need_rebuild(s)) {
-      if (a.single) break;  // one system: the same for every tile
-      continue;
-    }
-    bin_tile<D>(s, tile);
+// Counting-sort placement of atom i, arrival rank r in subcell c: slot =
+// start(subcell) + rank.  key: the atom's place in its subcell's order.
+__device__ inline void scatter_atom(SysDev* s, int i, int c, int r) {
+  const int slot = cell_start(s, c) + r;
+  int key = s->oid[s->pcur][i];
+  if (s->ysort) {
+    // the offset along the last axis exactly as k_place quantises it (caller
+    // ids below 2^23)
+    const double xl = s->x[s->xcur ^ 1][(size_t)i * rec_stride(s->d) + s->d - 1];
+    key |= (quant8(xl - last_centre(s, c), s->qinv) + 128) << 23;
   }
+  s->key[slot] = key;
+  s->src[slot] = i;
 }
 
-// ---------------------------------------------------------------------------
-// per-subcell sort (all-ascending bitonic network; entries at index >= cnt
-// act as +infinity so any occupancy works) and permutation of the atom arrays
-// ---------------------------------------------------------------------------
-template <bool KV>
-__device__ inline void bitonic_sort(int* keys, int* vals, int cnt) {
-  int p2 = 1;
-  while (p2 < cnt) p2 <<= 1;
-  const int half = p2 >> 1;
-  auto cas = [&](int i, int p) {
-    if (p < cnt && keys[i] > keys[p]) {
-      int k = keys[i]; keys[i] = keys[p]; keys[p] = k;
-      if (KV) { int v = vals[i]; vals[i] = vals[p]; vals[p] = v; }
+// Exclusive prefix of the subcell occupancies by one workgroup of kBinBlock
+// threads, 1024 subcells per wave and pass (sixteen independent wave scans).
+// sh: 2 x kBinBlock / 64 words.
+__device__ inline void scan_cells(SysDev* s, int* sh) {
+  constexpr int W = kBinBlock / 64, PER = 16;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nc = s->ncells;
+  int carry = 0, mx = 0;
+  for (int b = 0; b < nc; b += kBinBlock * PER) {
+    const int c0 = b + w * 64 * PER + lane;
+    int v[PER], x[PER];
+#pragma unroll
+    for (int u = 0; u < PER; u++) v[u] = c0 + 64 * u < nc ? load_agent(s->cell_count + c0 + 64 * u) : 0;
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+      mx = max(mx, v[u]);
+      x[u] = v[u];
     }
-  };
-  for (int size = 2; size <= p2; size <<= 1) {
-    const int hs = size >> 1;
-    for (int t = threadIdx.x; t < half; t += blockDim.x) {
-      int blk = t / hs, off = t % hs;
-      cas(blk * size + off, blk * size + size - 1 - off);
-    }
-    __syncthreads();
-    for (int st = size >> 2; st > 0; st >>= 1) {
-      for (int t = threadIdx.x; t < half; t += blockDim.x) {
-        int blk = t / st, off = t % st;
-        int i = blk * 2 * st + off;
-        cas(i, i + st);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+#pragma unroll
+      for (int u = 0; u < PER; u++) {
+        const int y = __shfl_up(x[u], o);
+        if (lane >= o) x[u] += y;
       }
-      __syncthreads();
     }
+    int tot = 0;
+#pragma unroll
+    for (int u = 0; u < PER; u++) {
+      const int t = __builtin_amdgcn_readlane(x[u], 63);
+      x[u] += tot - v[u];
+      tot += t;
+    }
+    if (lane == 0) sh[w] = tot;
+    __syncthreads();
+    int all = 0;
+    for (int q = 0; q < W; q++) {
+      const int t = sh[q];
+      if (q < w) carry += t;
+      else all += t;
+    }
+#pragma unroll
+    for (int u = 0; u < PER; u++)
+      if (c0 + 64 * u < nc) s->cell_local[c0 + 64 * u] = carry + x[u];
+    carry += all;
+    __syncthreads();
+  }
+  for (int ch = tid; ch < s->nchunks; ch += kBinBlock) s->chunk_off[ch] = 0;
+  mx = wave_max_i(mx);
+  if (lane == 0) sh[W + w] = mx;
+  __syncthreads();
+  if (tid == 0) {
+    for (int q = 1; q < W; q++) mx = max(mx, sh[W + q]);
+    s->max_cell = mx;
+    s->max_row = 0;
   }
 }
 
+// The binning of a system alone, and in its last workgroup to end (by
+// ticket) the prefix sums of the counts, and for few atoms the scatter too
+// (bin_scans, bin_scatters).
+template <int D>
+__global__ __launch_bounds__(kBinBlock) void k_bin(KArgs a) {
+  __shared__ int sh[2 * kBinBlock / 64];
+  SysDev* s = a.single;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool rb = running(s) && need_rebuild(s);
+  if (blockIdx.x == 0 && tid == 0) s->rb = rb;
+  if (!rb) return;
+  const int nt = s->ntiles, n = s->n;
+  for (int t = blockIdx.x * (kBinBlock / 64) + w; t < nt; t += gridDim.x * (kBinBlock / 64))
+    bin_tile<D>(s, t);
+  if (!bin_scans(s->nchunks)) return;
+  // every value the last workgroup reads of the others' went out past the
+  // caches (additions, store_agent); it has arrived when the wave's count of
+  // outstanding accesses is zero, so that no cache is written back here
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) sh[0] = atomicAdd(&s->ticket, 1) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (!sh[0]) return;
+  __syncthreads();
+  if (tid == 0) s->ticket = 0;
+  scan_cells(s, sh);
+  if (!bin_scatters(n, s->nchunks)) return;
+  __threadfence_block();
+  __syncthreads();
+  for (int b = tid; b < n; b += 4 * kBinBlock) {
+    int c[4], r[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const int i = min(b + u * kBinBlock, n - 1);
+      c[u] = load_agent(s->cell_of + i);
+      r[u] = load_agent(s->rank + i);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+      if (b + u * kBinBlock < n) scatter_atom(s, b + u * kBinBlock, c[u], r[u]);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// subcell order and permutation of the atom arrays
+// ---------------------------------------------------------------------------
 typedef _Float16 hv2 __attribute__((ext_vector_type(2)));
 __device__ inline unsigned h2u(hv2 v) { return __builtin_bit_cast(unsigned, v); }
 __device__ inline hv2 u2h(unsigned v) { return __builtin_bit_cast(hv2, v); }
@@ -313,101 +422,311 @@ __device__ inline void wrap_record(const SysDev* s, const double (&x)[D], double
   for (int t = 0; t < R::WORDS; t++) out[t] = (int)h2u(hv2{sl[2 * t], sl[2 * t + 1]});
 }
 
-// One subcell of a system that rebuilds (a block of 256 threads): its atoms
-// sorted by their keys (caller id, or, with ysort, the quantised offset along
-// the last axis and then caller id), then every per-atom array permuted into
-// subcell order.
+// One atom tile (a wave) of the placed slots: an atom's place in its subcell
+// is the number of smaller keys there (caller id, or, with ysort, the
+// quantised offset along the last axis and then caller id; all distinct), and
+// every per-atom array is permuted into that order.  Counting reads the few
+// keys of a subcell once per atom, from the caches; a bitonic sort per
+// subcell, one workgroup for each, was a chain of barriers over mostly idle
+// lanes (d = 4, N = 65536, 6.6 atoms per subcell: 80 us).
 template <int D, typename VT>
-__device__ inline void cellsort_tile(SysDev* s, int c, int* sk, int* sv) {
+__device__ inline void place_tile(SysDev* s, int tile) {
   constexpr bool MIX = sizeof(VT) == 4;
-  const int s0 = cell_start(s, c), cnt = cell_start(s, c + 1) - s0;
-  if (threadIdx.x == 0) {
+  const int lane = threadIdx.x & 63, nc = s->ncell, ncells = s->ncells, n = s->n;
+  for (int c = tile * kTile + lane; c < ncells; c += s->ntiles * kTile) {
     s->cell_count[c] = 0;  // ready for the next build
-    s->cell_flat[c] = s0;
-    if (c == s->ncells - 1) s->cell_flat[s->ncells] = s->n;
+    s->cell_flat[c] = cell_start(s, c);
   }
-  if (cnt == 0) return;
-  int* keys;
-  int* vals;
-  if (cnt <= kSortCap) {
-    for (int q = threadIdx.x; q < cnt; q += blockDim.x) {
-      sk[q] = s->key[s0 + q];
-      sv[q] = s->src[s0 + q];
-    }
-    keys = sk;
-    vals = sv;
-  } else {
-    keys = s->key + s0;
-    vals = s->src + s0;
-  }
-  __syncthreads();
-  bitonic_sort<true>(keys, vals, cnt);
-  // subcell centre
-  const int nc = s->ncell;
-  double cen[D];
-  {
-    int u = c;
+  if (tile == 0 && lane == 0) s->cell_flat[ncells] = n;
+  const int p = tile * kTile + lane;
+  if (p >= n) return;
+  const int key = s->key[p], src = s->src[p];
+  const int c = s->cell_of[src];
+  const int cur = s->rx, pc = s->rp, pn = pc ^ 1, npad = s->npad;
+  double x[D], sg;
+  load_rec<D>(s->x[cur ^ 1], src, x, sg);
+  const int s0 = cell_start(s, c), cnt = cell_start(s, c + 1) - s0;
+  const HDMD_GLOBAL int* kc = gbl(s->key) + s0;
+  int dst = s0;
+  for (int k = 0; k < cnt; k += 8) {
+    int o[8];
 #pragma unroll
-    for (int k = D - 1; k >= 0; k--) {
-      cen[k] = k == D - 1 ? last_centre(s, c) : ((double)(u % nc) + 0.5) * s->lsc - s->hL;
-      u /= nc;
-    }
+    for (int u = 0; u < 8; u++) o[u] = kc[min(k + u, cnt - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; u++) dst += (k + u < cnt) & (o[u] < key);
   }
-  const int cur = s->xcur, pc = s->pcur, pn = pc ^ 1, npad = s->npad;
-  const bool wrap = s->wrap != 0;
   const VT* vin = reinterpret_cast<const VT*>(s->v[pc]);
   VT* vout = reinterpret_cast<VT*>(s->v[pn]);
   const bool md = s->mode == MODE_MD;
   const double* din = s->disp[pc];
   double* dout = s->disp[pn];
-  for (int q = threadIdx.x; q < cnt; q += blockDim.x) {
-    const int src = vals[q], dst = s0 + q;
-    double x[D], sg;
-    load_rec<D>(s->x[cur ^ 1], src, x, sg);
-    store_rec<D>(s->x[cur], dst, x, sg);
-    if (MIX) store_q<D>(s->q[cur], dst, x, sg, s->hL, s->fxscale);
+  store_rec<D>(s->x[cur], dst, x, sg);
+  if (MIX) store_q<D>(s->q[cur], dst, x, sg, s->hL, s->fxscale);
 #pragma unroll
-    for (int k = 0; k < D; k++) {
-      s->xref[(size_t)k * npad + dst] = x[k];
-      vout[(size_t)k * npad + dst] = vin[(size_t)k * npad + src];
-      if (md) dout[(size_t)k * npad + dst] = din[(size_t)k * npad + src];
-    }
-    if (wrap) {
-      // slots on the circle (list build of n_cell <= 2)
-      wrap_record<D>(s, x, sg, s->qc16 + (size_t)dst * WrapRec<D>::WORDS);
-    } else {
-      // the candidate slots of the matrix-core build
-      int qv[D], Q = 0;
-#pragma unroll
-      for (int k = 0; k < D; k++) {
-        qv[k] = quant8(x[k] - cen[k], s->qinv);
-        Q += qv[k] * qv[k];
-      }
-      unsigned w[8];
-      cand_record<D>(qv, thresh_share(s, sg) - Q, w);
-      int4* pp = reinterpret_cast<int4*>(s->qc16 + (size_t)dst * 8);
-      pp[0] = make_int4((int)w[0], (int)w[1], (int)w[2], (int)w[3]);
-      pp[1] = make_int4((int)w[4], (int)w[5], (int)w[6], (int)w[7]);
-    }
-    s->oid[pn][dst] = s->ysort ? keys[q] & ((1 << 23) - 1) : keys[q];
+  for (int k = 0; k < D; k++) {
+    s->xref[(size_t)k * npad + dst] = x[k];
+    vout[(size_t)k * npad + dst] = vin[(size_t)k * npad + src];
+    if (md) dout[(size_t)k * npad + dst] = din[(size_t)k * npad + src];
   }
-  __syncthreads();
+  if (s->wrap) {
+    // slots on the circle (list build of n_cell <= 2)
+    wrap_record<D>(s, x, sg, s->qc16 + (size_t)dst * WrapRec<D>::WORDS);
+  } else {
+    // the candidate slots of the matrix-core build, from the offsets to the
+    // subcell's centre
+    int qv[D], Q = 0, u = c;
+#pragma unroll
+    for (int k = D - 1; k >= 0; k--) {
+      const double cen = k == D - 1 ? last_centre(s, c) : ((double)(u % nc) + 0.5) * s->lsc - s->hL;
+      u /= nc;
+      qv[k] = quant8(x[k] - cen, s->qinv);
+      Q += qv[k] * qv[k];
+    }
+    unsigned w[8];
+    cand_record<D>(qv, thresh_share(s, sg) - Q, w);
+    int4* pp = reinterpret_cast<int4*>(s->qc16 + (size_t)dst * 8);
+    pp[0] = make_int4((int)w[0], (int)w[1], (int)w[2], (int)w[3]);
+    pp[1] = make_int4((int)w[4], (int)w[5], (int)w[6], (int)w[7]);
+  }
+  s->oid[pn][dst] = s->ysort ? key & ((1 << 23) - 1) : key;
 }
 
-template <int D, typename VT>
-__global__ __launch_bounds__(256) void k_cellsort(KArgs a) {
-  __shared__ int sk[kSortCap];
-  __shared__ int sv[kSortCap];
-  for (int t = blockIdx.x;; t += gridDim.x) {
-    SysDev* s;
-    int c;
-    if (!fetch_cell_tile(a, t, s, c)) break;
-    if (!running(s) || !need_rebuild(s)) {
-      if (a.single) break;  // one system: the same for every tile
-      continue;
+// FIRE 2.0 control for one system (semi-implicit Euler variant, unit masses),
+// by one wave: fixed-order reductions of the tile partials, convergence test
+// on the current forces, then the P = F.v branch, dt / alpha updates and the
+// mixing coefficients.  |v + dt F|^2 is formed from |v|^2, F.v and |F|^2.
+__device__ inline FireNext fire_control(const SysDev* s) {
+  const int lane = threadIdx.x & 63, nw = s->nwaves;
+  double pe = 0, fv = 0, ff = 0, vv = 0, fm = 0;
+  const HDMD_GLOBAL double* part = gbl(s->part);
+  for (int w = lane; w < nw; w += 64 * 4) {
+    double p[4][5];
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      const HDMD_GLOBAL double* q = part + (size_t)min(w + 64 * u, nw - 1) * kPart;
+      p[u][0] = q[P_PE];
+      p[u][1] = q[P_FV];
+      p[u][2] = q[P_FF];
+      p[u][3] = q[P_VV];
+      p[u][4] = q[P_FMAX2];
     }
-    cellsort_tile<D, VT>(s, c, sk, sv);
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      if (w + 64 * u >= nw) break;
+      pe += p[u][0];
+      fv += p[u][1];
+      ff += p[u][2];
+      vv += p[u][3];
+      fm = fmax(fm, p[u][4]);
+    }
   }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    pe += __shfl_xor(pe, o, 64);
+    fv += __shfl_xor(fv, o, 64);
+    ff += __shfl_xor(ff, o, 64);
+    vv += __shfl_xor(vv, o, 64);
+    fm = fmax(fm, __shfl_xor(fm, o, 64));
+  }
+  const FireCtl& c = s->fc;
+  FireNext r;
+  r.pe = pe;
+  r.fmax = sqrt(fm);
+  r.fdt = s->fdt;
+  r.falpha = s->falpha;
+  r.c_keep = s->c_keep;
+  r.c_mix = s->c_mix;
+  r.npos = s->npos;
+  r.nneg = s->nneg;
+  r.zero = 0;
+  r.status = SLOT_DONE;
+  r.fstatus = s->fstatus;
+  r.err = 0;
+  if (!isfinite(pe) || !isfinite(ff)) {
+    r.err = ERR_RUN_NAN;
+    r.fstatus = -5;
+  } else if (sqrt(fm) < c.ftol || (c.etol > 0.0 && pe / (double)s->n < c.etol)) {
+    r.fstatus = 0;
+  } else if (s->iters >= c.maxiter) {
+    r.fstatus = 1;
+  } else {
+    double dt = s->fdt, alpha = s->falpha;
+    bool stop = false;
+    if (fv > 0.0) {
+      r.npos++;
+      r.nneg = 0;
+      if (r.npos > c.ndelay) {
+        dt = fmin(dt * c.finc, c.dtmax);
+        alpha *= c.falpha;
+      }
+    } else {
+      r.npos = 0;
+      r.nneg++;
+      if (r.nneg > c.nnegmax) {
+        stop = true;
+      } else {
+        if (!(c.initdelay && s->iters < c.ndelay)) {
+          if (dt * c.fdec >= c.dtmin) dt *= c.fdec;
+          alpha = c.alpha0;
+        }
+        r.zero = 1;
+      }
+    }
+    if (stop) {
+      r.fstatus = 1;
+    } else {
+      const double v2 = r.zero ? dt * dt * ff : vv + 2.0 * dt * fv + dt * dt * ff;
+      const double vn = sqrt(v2), fn = sqrt(ff);
+      r.status = SLOT_RUNNING;
+      r.fdt = dt;
+      r.falpha = alpha;
+      r.c_keep = fn > 0.0 ? 1.0 - alpha : 1.0;
+      r.c_mix = fn > 0.0 ? alpha * vn / fn : 0.0;
+    }
+  }
+  return r;
+}
+
+__device__ inline void fire_commit(SysDev* s, const FireNext& f) {
+  s->pe = f.pe;
+  s->fmax = f.fmax;
+  s->fdt = f.fdt;
+  s->falpha = f.falpha;
+  s->c_keep = f.c_keep;
+  s->c_mix = f.c_mix;
+  s->npos = f.npos;
+  s->nneg = f.nneg;
+  s->c_zero = f.zero;
+  s->fstatus = f.fstatus;
+  s->err |= f.err;
+  if (f.status == SLOT_RUNNING) s->iters++;
+  else s->status = f.status;
+}
+
+// End of a step / iteration for one system, by one wave: energy reductions
+// and thermo row (MD), buffer flips (the permuted buffers after a rebuild,
+// otherwise the freshly written position buffer), trigger reset, step counter.
+__device__ inline void finalize_system(SysDev* s, bool rb) {
+  if (!running(s)) return;
+  const int lane = threadIdx.x & 63;
+  if (s->err && s->mode != MODE_STATIC && !rb) {
+    // the list overflowed after the last finalisation: nothing has run since
+    if (lane == 0) s->status = SLOT_DONE;
+    return;
+  }
+  if (s->mode == MODE_MD) {
+    const int nw = s->nwaves;
+    const bool rec = s->thermo && s->thermo_every > 0 && s->step % s->thermo_every == 0;
+    double pe = 0.0, ke = 0.0;
+    const HDMD_GLOBAL double* part = gbl(s->part);
+    for (int w = lane; w < nw; w += 64 * 8) {
+      double a[8], b[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const size_t o = (size_t)min(w + 64 * u, nw - 1) * kPart;
+        a[u] = part[o + P_PE];
+        b[u] = part[o + P_KE];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; u++) {
+        const bool in = w + 64 * u < nw;
+        pe += in ? a[u] : 0.0;
+        ke += in ? b[u] : 0.0;
+      }
+    }
+    pe = wave_sum(pe);
+    ke = wave_sum(ke);
+    double vir = 0.0, nc = 0.0, m2 = 0.0, m4 = 0.0, ov = 0.0;
+    if (rec) {
+      for (int w = lane; w < nw; w += 64) {
+        const HDMD_GLOBAL double* pw = part + (size_t)w * kPart;
+        vir += pw[P_VIR];
+        nc += pw[P_NC];
+        m2 += pw[P_M2];
+        m4 += pw[P_M4];
+        ov += pw[P_OV];
+      }
+      vir = wave_sum(vir);
+      nc = wave_sum(nc);
+      m2 = wave_sum(m2);
+      m4 = wave_sum(m4);
+      ov = wave_sum(ov);
+    }
+    if (lane == 0) {
+      s->pe = pe;
+      s->ke = ke;
+      if (!isfinite(pe + ke)) s->err |= ERR_RUN_NAN;
+      // Berendsen factor for the next full-step kick, from this step's T
+      if (s->tau_t > 0.0 && ke > 0.0) {
+        const double T = 2.0 * ke / ((double)s->d * (double)(s->n - 1));
+        s->vscale = sqrt(1.0 + s->dt / s->tau_t * (s->temp_t / T - 1.0));
+      } else {
+        s->vscale = 1.0;
+      }
+      if (rec) {
+        double* r = s->thermo + kThermoCols * (s->step / s->thermo_every);
+        r[0] = (double)s->step;
+        r[1] = ke;
+        r[2] = pe;
+        r[3] = ke + pe;
+        r[4] = vir;                 // sum over pairs of r_ij . F_ij
+        r[5] = nc / (double)s->n;   // mean neighbours inside the cutoff (Z)
+        // displacement moments since the run's start, alpha_2 (eq. ngp; 0
+        // while nothing has moved) and f_ov (eq. fov)
+        const double msd = m2 / (double)s->n, mqd = m4 / (double)s->n;
+        r[6] = msd;
+        r[7] = mqd;
+        r[8] = msd > 0.0 ? s->d * mqd / ((s->d + 2) * msd * msd) - 1.0 : 0.0;
+        r[9] = ov / (double)s->n;
+      }
+    }
+  }
+  if (lane == 0) {
+    if (rb) {
+      s->pcur ^= 1;
+      s->builds++;
+    } else {
+      s->xcur ^= 1;
+    }
+    // the shells whose pairs may interact at the new positions
+    const double dl = rb ? 0.0 : sqrt(__longlong_as_double((long long)s->maxdisp2));
+    s->shells = s->nshell == 1
+                    ? 1
+                    : 1 + (int)fmin(2.0 * dl * s->sh_scale * (1.0 + 1e-9) + 1e-9, s->nshell - 1.0);
+    s->maxdisp2 = 0ull;
+    s->force_rebuild = 0;
+    if (s->mode == MODE_MD) {
+      s->step++;
+      if (s->step > s->nsteps) s->status = SLOT_DONE;
+    }
+    if (s->err) s->status = SLOT_DONE;
+  }
+}
+
+// Placement of a system alone over grid - 1 workgroups; with a.fin the first
+// one finalises the iteration.  The binning has noted whether it rebuilds and
+// from which buffers, so that neither the placement nor the list build reads
+// what the finalisation changes: an iteration needs no launch of its own for
+// it.
+template <int D, typename VT>
+__global__ __launch_bounds__(256) void k_place(KArgs a) {
+  SysDev* s = a.single;
+  const bool rb = s->rb != 0;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (blockIdx.x == 0) {
+    if (a.fin && w == 0) {
+      if (a.fin == 2 && live(s) && s->mode == MODE_FIRE) {
+        const FireNext f = s->fnext;
+        if (threadIdx.x == 0) fire_commit(s, f);
+        if (f.status != SLOT_RUNNING) return;
+      }
+      finalize_system(s, rb);
+    }
+    return;
+  }
+  if (!rb) return;
+  const int nt = s->ntiles;
+  for (int t = (blockIdx.x - 1) * 4 + w; t < nt; t += (gridDim.x - 1) * 4) place_tile<D, VT>(s, t);
 }
 
 // ---------------------------------------------------------------------------
@@ -1121,7 +1440,7 @@ struct BuildTile {
     nc = s->ncell;
     npad = s->npad;
     W = s->width;
-    xb = s->x[s->xcur];
+    xb = s->x[s->rx];
     rec = s->qc16;
     nl = gbl(s->nl);
     L = s->L;
@@ -1194,7 +1513,7 @@ __global__ __launch_bounds__(64 * G, 4) void k_build_mf(KArgs a) {
     int hc;
     if (!fetch_cell_tile_u(a, t, s, hc)) break;
     cSys* c = (cSys*)s;
-    if (!running(c) | !need_rebuild(c) | (c->reach != RAD) | (c->wrap != 0) | (c->bmode != MODE)) {
+    if (!rebuilding(a, c) | (c->reach != RAD) | (c->wrap != 0) | (c->bmode != MODE)) {
       if (a.single) break;  // one system: the same for every tile
       continue;
     }
@@ -1242,7 +1561,7 @@ __device__ __forceinline__ void build_wrap_tile(SysDev* sys, int tile, WrapLds* 
   const int hb = tile * 64;
   if (hb >= n) return;
   const int hcnt = min(64, n - hb);
-  const double* __restrict__ xb = s->x[s->xcur];
+  const double* __restrict__ xb = s->x[s->rx];
   const int* __restrict__ rec = s->qc16;
   const double L = s->L, hL = s->hL, cut = s->cutoff, skin = s->skin;
   // operand words of the atom `a + col` (zero past `cnt` atoms, which gives
@@ -1355,7 +1674,7 @@ __global__ __launch_bounds__(64, 4) void k_build_wrap(KArgs a) {
     int tile;
     if (!fetch_atom_tile_u(a, t, s, tile)) break;
     cSys* c = (cSys*)s;
-    if (!running(c) | !need_rebuild(c) | (c->wrap == 0)) {
+    if (!rebuilding(a, c) | (c->wrap == 0)) {
       if (a.single) break;  // one system: the same for every tile
       continue;
     }
@@ -2068,7 +2387,7 @@ __global__ __launch_bounds__(kTile * LPA) void k_force(KArgs a, int fire) {
     SysDev* s;
     int tile;
     if (!fetch_atom_tile(a, t, s, tile)) break;
-    if (!running(s) || !kernel_serves(s, MIX, MORSE, LPA)) continue;
+    if (!live(s) || !kernel_serves(s, MIX, MORSE, LPA)) continue;
     if (fire && s->mode != MODE_FIRE) continue;
     force_tile<D, MIX, LPA, MORSE>(s, tile, fire, sh, stage);
   }
@@ -2096,7 +2415,7 @@ __global__ __launch_bounds__(kTile * LPA) void k_step(KArgs a) {
     SysDev* s;
     int tile;
     if (!fetch_atom_tile(a, t, s, tile)) break;
-    if (!running(s) || s->mode != MODE_MD || !kernel_serves(s, MIX, MORSE, LPA)) continue;
+    if (!live(s) || s->mode != MODE_MD || !kernel_serves(s, MIX, MORSE, LPA)) continue;
     const int i = tile * kTile + slot;
     const int n = s->n, npad = s->npad, pc = s->pcur, cur = s->xcur;
     const bool vi = i < n;
@@ -2167,18 +2486,17 @@ __global__ __launch_bounds__(kTile * LPA) void k_step(KArgs a) {
 }
 
 // FIRE 2.0 semi-implicit Euler update with the coefficients of this
-// iteration (computed per system by k_fire_ctrl):
+// iteration (computed per system by fire_control):
 //   on P <= 0: x -= dt/2 v, v = 0;  v += dt F;  v = (1-a) v + a |v|/|F| F;
 //   x += dt v (wrapped, into the other buffer); displacement for the trigger.
 template <int D, bool MIX>
-__device__ inline void fire_update_tile(SysDev* s, int tile) {
+__device__ inline void fire_update_tile(SysDev* s, int tile, double dt, double keep, double mix,
+                                        bool zero) {
   typedef typename VType<MIX>::T VT;
   const int i = tile * kTile + threadIdx.x;
   const int n = s->n, npad = s->npad, pc = s->pcur, cur = s->xcur;
   double disp2 = 0.0;
   if (i < n) {
-    const double dt = s->c_dt, keep = s->c_keep, mix = s->c_mix;
-    const bool zero = s->c_zero != 0;
     const double L = s->L, h = s->hL;
     double x[D], sg;
     load_rec<D>(s->x[cur], i, x, sg);
@@ -2210,14 +2528,21 @@ __device__ inline void fire_update_tile(SysDev* s, int tile) {
     atomicMax(&s->maxdisp2, (unsigned long long)__double_as_longlong(dm));
 }
 
+// One system alone.  Up to kFireFused tiles every workgroup takes the
+// control's decision itself (the same bits in each), and the finalisation
+// writes it to the descriptor, which no workgroup reads then.
 template <int D, bool MIX>
 __global__ __launch_bounds__(kTile) void k_fire_update(KArgs a) {
-  for (int t = blockIdx.x;; t += gridDim.x) {
-    SysDev* s;
-    int tile;
-    if (!fetch_atom_tile(a, t, s, tile)) break;
-    if (!running(s) || s->mode != MODE_FIRE) continue;
-    fire_update_tile<D, MIX>(s, tile);
+  SysDev* s = a.single;
+  const int tile = blockIdx.x;
+  if (!live(s) || s->mode != MODE_FIRE || tile >= s->ntiles) return;
+  if (a.fin == 2) {
+    const FireNext f = fire_control(s);
+    if (tile == 0 && threadIdx.x == 0) s->fnext = f;
+    if (f.status == SLOT_RUNNING)
+      fire_update_tile<D, MIX>(s, tile, f.fdt, f.c_keep, f.c_mix, f.zero != 0);
+  } else {
+    fire_update_tile<D, MIX>(s, tile, s->fdt, s->c_keep, s->c_mix, s->c_zero != 0);
   }
 }
 

@@ -424,23 +424,29 @@ static KArgs single_args(SysDev* dev, int d) {
   a.tab = nullptr;
   a.cls = d;
   a.part = 0;
+  a.fin = 0;
   return a;
 }
 
-// bin -> scan -> scatter -> per-subcell sort/permute (chain_sort), then the
-// list build; every kernel exits at once for systems that need no rebuild.
-// The binning, placement and subcell-sort grids stride over their tiles:
-// at most 1024 workgroups, so that the launches of steps without a rebuild
-// (which exit at once) dispatch few of them.
-static void chain_sort(const Plan& p, SysDev* dev, hipStream_t st) {
+// bin (-> scan -> scatter) -> place (chain_sort), then the list build; every
+// kernel exits at once when the system needs no rebuild.  The binning's last
+// workgroup takes the prefix sums and the scatter of small systems itself
+// (bin_scans, bin_scatters).  fin: the placement's launch also finalises the
+// iteration.  The binning, scatter and placement grids stride over their
+// tiles, so that the launches of steps without a rebuild (which exit at once)
+// dispatch few workgroups.
+static void chain_sort(const Plan& p, SysDev* dev, hipStream_t st, int fin) {
   const DKernels* K = dkernels(p.d);
   KArgs a = single_args(dev, p.d);
-  const int gt = std::min(p.ntiles, 1024), gc = std::min(p.ncells, 1024);
-  K->bin(a, gt, st);
-  launch_scan1(a, p.nchunks, st);
-  launch_scan2(a, 1, st);
-  launch_scatter(a, gt, st);
-  K->cellsort(p.mix, a, gc, st);
+  a.fin = fin;
+  constexpr int per_bin = kBinBlock / kTile;
+  K->bin(a, std::min((p.ntiles + per_bin - 1) / per_bin, 256), st);
+  if (!bin_scans(p.nchunks)) {
+    launch_scan1(a, p.nchunks, st);
+    launch_scan2(a, 1, st);
+  }
+  if (!bin_scatters(p.n, p.nchunks)) launch_scatter(a, std::min(p.ntiles, 1024), st);
+  K->place(p.mix, a, std::min((p.ntiles + 3) / 4, 512) + 1, st);
 }
 
 static void build_single(const Plan& p, SysDev* dev, hipStream_t st, int blk) {
@@ -449,8 +455,8 @@ static void build_single(const Plan& p, SysDev* dev, hipStream_t st, int blk) {
   else K->build(p.reach, build_mode(p.reach, p.n, p.ncells), blk, single_args(dev, p.d), p.ncells, st);
 }
 
-static void chain_single(const Plan& p, SysDev* dev, hipStream_t st, int blk) {
-  chain_sort(p, dev, st);
+static void chain_single(const Plan& p, SysDev* dev, hipStream_t st, int blk, int fin) {
+  chain_sort(p, dev, st, fin);
   build_single(p, dev, st, blk);
 }
 
@@ -545,7 +551,7 @@ static int tune_build(const hdmd_system* sys, const Plan& pf, const double* pos,
     for (int rep = 0; rep < 2; rep++) {  // the second load and sort are timed
       load_system(sys, p, pos, diam, vel, ws, st);
       HIPCHK(hipEventRecord(e0, st));
-      chain_sort(p, dev, st);
+      chain_sort(p, dev, st, 0);
       HIPCHK(hipEventRecord(e1, st));
       int rc = elapsed(&sort_ms);
       if (rc) return rc;
@@ -606,7 +612,7 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
   }
   load_system(sys, p, pos, diam, vel, ws, st);
   SysDev* dev = at<SysDev>(ws, p.off_desc);
-  chain_single(p, dev, st, blk);
+  chain_single(p, dev, st, blk, 0);
   launch_finalize(single_args(dev, p.d), 1, st);
   HIPCHK(hipGetLastError());
   if (!p.morse && !lpa_env() && p.n >= kLanesMinAtoms && tuning_enabled() && allow_tune) {
@@ -691,17 +697,16 @@ static void enqueue_md_step(const Plan& p, SysDev* dev, hipStream_t st, int blk)
   const DKernels* K = dkernels(p.d);
   KArgs a = single_args(dev, p.d);
   K->step(p.mix, p.lpa, p.morse, a, p.ntiles, st);
-  chain_single(p, dev, st, blk);
-  launch_finalize(a, 1, st);
+  chain_single(p, dev, st, blk, 1);
 }
 
 static void enqueue_fire_iter(const Plan& p, SysDev* dev, hipStream_t st, int blk) {
   const DKernels* K = dkernels(p.d);
   KArgs a = single_args(dev, p.d);
-  launch_fire_ctrl(a, 1, st);
+  a.fin = p.ntiles <= kFireFused ? 2 : 1;
+  if (a.fin == 1) launch_fire_ctrl(a, 1, st);
   K->fire_update(p.mix, a, p.ntiles, st);
-  chain_single(p, dev, st, blk);
-  launch_finalize(a, 1, st);
+  chain_single(p, dev, st, blk, a.fin);
   K->force(p.mix, p.lpa, p.morse, a, p.ntiles, 1, st);
 }
 
@@ -1013,11 +1018,10 @@ static int md_run(const hdmd_system* sys, double* pos, double* vel, const double
       HIPCHK(hipEventRecord(ev[4 * k], st));
       K->step(p.mix, p.lpa, p.morse, a, p.ntiles, st);
       HIPCHK(hipEventRecord(ev[4 * k + 1], st));
-      chain_sort(p, dev, st);
+      chain_sort(p, dev, st, 1);
       HIPCHK(hipEventRecord(ev[4 * k + 2], st));
       build_single(p, dev, st, blk);
       HIPCHK(hipEventRecord(ev[4 * k + 3], st));
-      launch_finalize(a, 1, st);
     }
     HIPCHK(hipGetLastError());
   } else {
@@ -1481,6 +1485,7 @@ static KArgs batch_args(HostBatch* B, int d, int part = 0) {
   a.tab = B->dtab;
   a.cls = d;
   a.part = part;
+  a.fin = 0;
   return a;
 }
 
@@ -1491,7 +1496,7 @@ static void enqueue_batch_iter(HostBatch* B, const std::vector<int>& grids, hipS
   auto ga = [&](int d) { return grids[2 + 3 * (d - kMinD)]; };
   auto gc = [&](int d) { return grids[3 + 3 * (d - kMinD)]; };
   KArgs a0 = batch_args(B, 0);  // class 0: the tiles of every class
-  const int ga_all = grids[grids.size() - 4], gc_all = grids[grids.size() - 3];
+  const int ga_all = grids[grids.size() - 3];
   const int gb_all = grids[grids.size() - 2];
   if (B->has_fire) {
     launch_fire_ctrl(a0, gsys, st);
@@ -1506,7 +1511,7 @@ static void enqueue_batch_iter(HostBatch* B, const std::vector<int>& grids, hipS
   launch_scan1(a0, gchunk, st);
   launch_scan2(a0, gsys, st);
   launch_scatter(a0, ga_all, st);
-  launch_cellsort_all(a0, gc_all, st);
+  launch_place_all(a0, ga_all, st);
   // list builds: one launch per stencil radius present (a launch serves the
   // systems of its own radius and passes over the others' subcells)
   auto class_builds = [&](int d) {
@@ -1676,7 +1681,6 @@ int hdmd_batch_run(void* table_ws, int32_t iterations, void* stream) {
   grids.push_back(B->has_fire ? 1 : 0);
   grids.push_back(B->has_md ? 1 : 0);
   grids.push_back(pow2_grid(B->n_atom_all, 4096));  // all-class launches
-  grids.push_back(pow2_grid(B->n_cell_all, 8192));
   // one list-build launch over every class (0: one launch per class and variant)
   grids.push_back(std::getenv("HDMD_BUILD_PER_CLASS")
                       ? 0
