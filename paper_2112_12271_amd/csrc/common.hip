@@ -151,6 +151,7 @@ __global__ __launch_bounds__(kTile) void k_scatter(KArgs a) {
 
 // Finalisation of the systems of a batch (and of a system's first build).
 __global__ __launch_bounds__(64) void k_finalize(KArgs a) {
+  if (a.tab && blockIdx.x == 0 && threadIdx.x == 0) a.tab->build_waves = 0;
   for (int t = blockIdx.x;; t += gridDim.x) {
     SysDev* s;
     if (!fetch_sys(a, t, s)) break;

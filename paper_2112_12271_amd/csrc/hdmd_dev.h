@@ -96,7 +96,7 @@ struct SysDev {
   int32_t npad, ncell, ncells;
   int32_t width, nchunks, ntiles;
   int32_t mode, nwaves;
-  int32_t wrap;   // 1: n_cell <= 2 on subcells of side >= r_l,max
+  int32_t wrap;   // 1: the list build's circle form
   int32_t bmode;  // form of the list build (BuildMode)
   int32_t reach;  // stencil radius in subcells: 1 (side >= r_l,max), 2 (half-size subcells)
   int32_t lpa;    // lanes per atom of the force kernels (1, 2 or 4)
@@ -158,7 +158,8 @@ struct SysDev {
 
 // Tile tables of a batch: one list per dimension class (index d).
 struct Table {
-  int32_t max_slots, pad;
+  int32_t max_slots;
+  int32_t build_waves;  // waves of the list builds under way, unsplit (the binning adds them up)
   // index d: dimension class d; index 0: all classes (atom tiles of class d
   // follow those of class d-1 in one array, so class 0 covers them all; the
   // cell tiles of class 0 are an array of their own that lists the n_cell >= 3

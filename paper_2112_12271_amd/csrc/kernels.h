@@ -768,7 +768,7 @@ __global__ __launch_bounds__(256) void k_place(KArgs a) {
 // d = 4, N = 65536, 6.6 per subcell (sparse form): 0.43 -> 0.16 ms.
 //
 // Systems of n_cell <= 2, where several images of a pair can be in reach
-// along an axis, take k_build_wrap below.
+// along an axis, and small systems take k_build_wrap below.
 // ---------------------------------------------------------------------------
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef _Float16 hv4 __attribute__((ext_vector_type(4)));
@@ -1523,8 +1523,8 @@ __global__ __launch_bounds__(64 * G, 4) void k_build_mf(KArgs a) {
 
 // ---------------------------------------------------------------------------
 // Verlet-list build of systems of n_cell <= 2 (a list radius of a third of
-// the box or more): every atom is a candidate of every other, and the pair
-// test runs on the matrix cores too.  Along each axis the atom is put on the
+// the box or more) and of small systems: every atom is a candidate of every
+// other, and the pair test runs on the matrix cores too.  Along each axis the atom is put on the
 // circle, e = (cos, sin)(2 pi x / L): the chord between two atoms does not
 // exceed the arc, so a pair within its radius r_ij = a_i + a_j has
 //   sum_k |e_i - e_j|_k^2 <= (2 pi r_ij / L)^2
@@ -1538,9 +1538,11 @@ __global__ __launch_bounds__(64 * G, 4) void k_build_mf(KArgs a) {
 // (The chord test keeps about twice the pairs of the list in d = 8; it takes
 // no row cull, no shifts and no wrapped differences.)  2 d + 2 <= 16 (d <=
 // 7): records of 16 slots and 16x16x16 products; above: 24 slots, 16x16x32.
-// A wave takes 64 home atoms as four blocks of columns held in registers and
-// streams all atoms past them, 128 at a time: 32 matrix instructions and 128
-// sign-bit shifts per 8192 pair tests, and the exact tests of the survivors.
+// A wave takes 16 HB home atoms (HB = 4: a tile) as HB blocks of columns held
+// in registers and streams all atoms past them, 128 at a time: for a tile 32
+// matrix instructions and 128 sign-bit shifts per 8192 pair tests, and the
+// exact tests of the survivors.  The survivors of a row come in the order of
+// the candidates whatever HB is, so every HB gives the same rows.
 // d = 8, N = 131072 (mean row 200): 2.5 ms, where packed int16 tests of the
 // 45 % of the pairs that a row cull left took 7.6.
 // ---------------------------------------------------------------------------
@@ -1550,17 +1552,16 @@ struct WrapLds {
   int pad[kShellRow - 128 - sizeof(SurvivorLds<unsigned>) / 4];  // shell_order takes it all
 };
 
-// The 64 home atoms of one tile.
-template <int D>
-__device__ __forceinline__ void build_wrap_tile(SysDev* sys, int tile, WrapLds* m) {
+// Home atoms hb .. hb + 16 HB - 1.
+template <int D, int HB>
+__device__ __forceinline__ void build_wrap_tile(SysDev* sys, int hb, WrapLds* m) {
   typedef WrapRec<D> R;
   typedef typename std::conditional<R::LW == 2, hv4, hv8>::type Op;
   cSys* s = (cSys*)sys;
   const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
   const int n = s->n, npad = s->npad, W = s->width;
-  const int hb = tile * 64;
   if (hb >= n) return;
-  const int hcnt = min(64, n - hb);
+  const int hcnt = min(16 * HB, n - hb);
   const double* __restrict__ xb = s->x[s->rx];
   const int* __restrict__ rec = s->qc16;
   const double L = s->L, hL = s->hL, cut = s->cutoff, skin = s->skin;
@@ -1578,9 +1579,9 @@ __device__ __forceinline__ void build_wrap_tile(SysDev* sys, int tile, WrapLds* 
       return __builtin_bit_cast(Op, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
     }
   };
-  Op H[4];
+  Op H[HB];
 #pragma unroll
-  for (int b = 0; b < 4; b++) {
+  for (int b = 0; b < HB; b++) {
     // home slots from the atom's record: signs flipped, 1 and t exchanged
     Op h = operand(hb + 16 * b, hcnt - 16 * b);
     constexpr int GS = R::LW * 2;             // slots per lane group
@@ -1614,37 +1615,46 @@ __device__ __forceinline__ void build_wrap_tile(SysDev* sys, int tile, WrapLds* 
         append(lane, false, pass, h, i, shell_entry(s, j, r2, si, sj), len0, len1);
       });
     };
+    // the next 64 candidates' operands are on their way while these are used
+    Op X[4], Y[4];
+    auto fetch = [&](int a0, Op(&Z)[4]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int b = 0; b < 4; b++) {
+        const int a = a0 + 16 * b;
+        Z[b] = operand(c0 + min(a, ce), ce - a);
+      }
+    };
+    fetch(0, X);
     for (int c = 0; c < ce; c += 128) {
-      unsigned w[4] = {0u, 0u, 0u, 0u};
+      unsigned w[HB];
+#pragma unroll
+      for (int h = 0; h < HB; h++) w[h] = 0u;
 #pragma unroll
       for (int half = 0; half < 2; half++) {
-        Op X[4];
+        fetch(c + 64 * half + 64, half ? X : Y);
 #pragma unroll
         for (int b = 0; b < 4; b++) {
-          const int a = c + 64 * half + 16 * b;
-          X[b] = operand(c0 + min(a, ce), ce - a);
-        }
+          const Op& x = half ? Y[b] : X[b];
+          fv4 e[HB];
 #pragma unroll
-        for (int b = 0; b < 4; b++) {
-          fv4 e[4];
-#pragma unroll
-          for (int h = 0; h < 4; h++) {
+          for (int h = 0; h < HB; h++) {
             const fv4 zero = {};
-            if constexpr (R::LW == 2) e[h] = __builtin_amdgcn_mfma_f32_16x16x16f16(X[b], H[h], zero, 0, 0, 0);
-            else e[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(X[b], H[h], zero, 0, 0, 0);
+            if constexpr (R::LW == 2) e[h] = __builtin_amdgcn_mfma_f32_16x16x16f16(x, H[h], zero, 0, 0, 0);
+            else e[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, H[h], zero, 0, 0, 0);
           }
 #pragma unroll
-          for (int h = 0; h < 4; h++)
+          for (int h = 0; h < HB; h++)
 #pragma unroll
             for (int v = 0; v < 4; v++)
               w[h] = __builtin_amdgcn_alignbit(w[h], __float_as_uint(e[h][v]), 31u);
-          __builtin_amdgcn_sched_barrier(0);  // one block's results at a time
+          if (HB > 1) __builtin_amdgcn_sched_barrier(0);  // one block's results at a time
         }
       }
 #pragma unroll 1
-      for (int h = 0; h < 4; h++) {
+      for (int h = 0; h < HB; h++) {
         const int hs = 16 * h + col;
-        const unsigned wh = h < 2 ? (h == 0 ? w[0] : w[1]) : (h == 2 ? w[2] : w[3]);
+        unsigned wh = w[0];
+        if constexpr (HB == 4) wh = h < 2 ? (h == 0 ? w[0] : w[1]) : (h == 2 ? w[2] : w[3]);
         sv.push(hs < hcnt ? wh : 0u, (unsigned)(((c >> 7) << 8) | (hs << 2) | g));
         bool full = false;
         while (sv.nw >= 64 && !full) full = !sv.expand(lane);
@@ -1666,19 +1676,20 @@ __device__ __forceinline__ void build_wrap_tile(SysDev* sys, int tile, WrapLds* 
   }
 }
 
-template <int D>
+// One system: a tile per workgroup, or (HB = 1) a quarter of one.
+template <int D, int HB>
 __global__ __launch_bounds__(64, 4) void k_build_wrap(KArgs a) {
   __shared__ WrapLds lds;
   for (int t = blockIdx.x;; t += gridDim.x) {
     SysDev* s;
     int tile;
-    if (!fetch_atom_tile_u(a, t, s, tile)) break;
+    if (!fetch_atom_tile_u(a, t * HB / 4, s, tile)) break;
     cSys* c = (cSys*)s;
     if (!rebuilding(a, c) | (c->wrap == 0)) {
       if (a.single) break;  // one system: the same for every tile
       continue;
     }
-    build_wrap_tile<D>(s, tile, &lds);
+    build_wrap_tile<D, HB>(s, tile * 64 + (HB == 4 ? 0 : (t & 3) * 16), &lds);
   }
 }
 

@@ -67,7 +67,7 @@ struct Plan {
   int d = 0, dr = 0, dq = 0;
   int n = 0, npad = 0, ncell = 0, ncells = 0, nchunks = 0;
   int ntiles = 0, nwaves = 0, width = 0;
-  bool wrap = false;  // n_cell <= 2 on subcells of side >= r_l,max
+  bool wrap = false;  // the list build's circle form (circle_form)
   bool mix = false, morse = false;
   // reach: stencil radius in subcells (1: side >= r_l,max, 3^d stencil; 2:
   // half-size subcells, 5^d stencil); key_wrap/key_occ: the autotuner's key,
@@ -136,6 +136,24 @@ static int occ_bucket(int64_t n, int64_t ncells) {
 }
 
 // the autotuner's grid for a key: 0 (not tuned yet), 1 or 2 (reach)
+// Systems whose list is built in the circle form (every atom a candidate of
+// every other): those of n_cell <= 2, where the linked subcells do not cover
+// several images, and small ones.  A small system's build lasts as long as
+// one wave's walk: over its 3^d linked subcells, or over n / 128 groups of
+// candidates, which come in memory order and are fetched ahead.  Measured in
+// a batch of 24 minimisations (d 3 to 6, 256 to 8192 atoms, whole run): no
+// small system 53.7 ms, n <= 32 * 3^d or 64 * 3^d 48.5, 128 * 3^d 40.9, all
+// n <= 8192 42.6 (d = 3, N = 8192 alone: 10.9 ms by linked subcells, 11.5 by
+// all atoms).  d >= 8 keeps the linked subcells: its circle records are
+// longer.  HDMD_CIRCLE=0 leaves the form to n_cell <= 2.
+constexpr int64_t kCircleAtoms = 8192;
+static bool circle_form(int d, int64_t n, int reach, int ncell) {
+  if (reach != 1) return false;
+  if (ncell <= 2) return true;
+  const char* e = std::getenv("HDMD_CIRCLE");
+  return d <= 7 && n <= std::min(kCircleAtoms, 128 * ipow(3, d)) && !(e && e[0] == '0');
+}
+
 static int tuned_reach(int d, int wrap, int occ);
 // lanes per atom of the force kernels for a system (the autotuner's, or 1),
 // keyed by the row-length bucket
@@ -182,7 +200,7 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   // the system may take, so its layout does not depend on the choice
   const int ncf = choose_ncell(*s, p.rlmax);
   const int64_t cells_full = ipow(ncf, p.d);
-  p.key_wrap = ncf <= 2;
+  p.key_wrap = ncf <= 2 ? 1 : (circle_form(p.d, p.n, 1, ncf) ? 2 : 0);
   p.key_occ = occ_bucket(p.n, cells_full);
   int64_t cells_alloc = cells_full;
   p.reach = 1;
@@ -213,7 +231,7 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   p.ntiles = p.npad / kTile;
   p.nwaves = p.npad / kWave;
   p.width = s->max_neighbors;
-  p.wrap = p.reach == 1 && p.ncell <= 2;
+  p.wrap = circle_form(p.d, p.n, p.reach, p.ncell);
   p.mix = s->precision == HDMD_MIXED;
   p.row_key = row_bucket(*s, p.rlmax);
   p.lpa = lanes_for(s, p.d, p.row_key);
@@ -451,7 +469,10 @@ static void chain_sort(const Plan& p, SysDev* dev, hipStream_t st, int fin) {
 
 static void build_single(const Plan& p, SysDev* dev, hipStream_t st, int blk) {
   const DKernels* K = dkernels(p.d);
-  if (p.wrap) K->build_wrap(single_args(dev, p.d), p.ntiles, st);
+  // the circle form takes quarters of tiles while they are all at work at
+  // once, four waves per SIMD (d = 6, N = 8192: 155 us by tiles, 53 by quarters)
+  const bool split = p.ntiles <= 1024;
+  if (p.wrap) K->build_wrap(split, single_args(dev, p.d), split ? 4 * p.ntiles : p.ntiles, st);
   else K->build(p.reach, build_mode(p.reach, p.n, p.ncells), blk, single_args(dev, p.d), p.ncells, st);
 }
 
@@ -544,7 +565,7 @@ static int tune_build(const hdmd_system* sys, const Plan& pf, const double* pos,
       p.ncell = choose_ncell(*sys, pf.rlmax);
       p.ncells = (int)ipow(p.ncell, p.d);
           p.nchunks = (p.ncells + kChunk - 1) / kChunk;
-      p.wrap = p.ncell <= 2;
+      p.wrap = circle_form(p.d, p.n, 1, p.ncell);
     }
     SysDev* dev = at<SysDev>(ws, p.off_desc);
     float sort_ms = 0.f;
@@ -558,7 +579,7 @@ static int tune_build(const hdmd_system* sys, const Plan& pf, const double* pos,
     }
     float best = 1e30f;
     for (int cand : {1, 2, 4}) {
-      if (p.wrap && cand > 1) break;  // n_cell <= 2: one form
+      if (p.wrap && cand > 1) break;  // the circle form: one variant
       build_single(p, dev, st, cand);  // warm-up
       HIPCHK(hipEventRecord(e0, st));
       build_single(p, dev, st, cand);
@@ -1521,7 +1542,7 @@ static void enqueue_batch_iter(HostBatch* B, const std::vector<int>& grids, hipS
       K->build(1, BUILD_DENSE, 1, batch_args(B, d, 1), gc(d), st);
     }
     if (B->has_half[d]) K->build(2, BUILD_DENSE, 1, batch_args(B, d, 1), gc(d), st);
-    if (B->has_wrap[d]) K->build_wrap(batch_args(B, d), ga(d), st);
+    if (B->has_wrap[d]) K->build_wrap(false, batch_args(B, d), ga(d), st);
   };
   if (gb_all > 0) {
     bool half = false;

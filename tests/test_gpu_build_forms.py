@@ -17,6 +17,12 @@ pytestmark = pytest.mark.gpu
 CUT, SKIN = 1.0, 0.25
 
 
+@pytest.fixture(autouse=True)
+def linked_subcells(monkeypatch):
+    """These systems are small: the circle form only where n_cell <= 2."""
+    monkeypatch.setenv("HDMD_CIRCLE", "0")
+
+
 def _check(orc, x, sig, L, nc, d, width=256):
     ref = orc.nlist_brute(x, sig, L, CUT, SKIN)
     s = H.System(d=d, n=len(x), box_l=L, potential=H.HDMD_HARMONIC, cutoff=CUT, skin=SKIN,
