@@ -108,7 +108,7 @@ void l_swap_settle(SysDev* s, hipStream_t st, long long* ctl, const int32_t* off
                    int32_t* off_out, int64_t n_att, const int32_t* pairs, const double* u, double T,
                    const int32_t* slot_of, const double* de, const unsigned long long* conf,
                    int32_t* acc, double* diam) {
-  k_swap_settle<D><<<1, 1024, 0, st>>>(s, ctl, off_in, off_out, n_att, pairs, u, T, slot_of, de,
+  k_swap_settle<D><<<1, kSwapBatch, 0, st>>>(s, ctl, off_in, off_out, n_att, pairs, u, T, slot_of, de,
                                        conf, acc, diam);
 }
 const DKernels table = {l_load, l_unload, l_same_state, l_disp_restart, l_bin, l_place, l_build, l_build_wrap, l_force, l_step,

@@ -1772,8 +1772,12 @@ __device__ inline void sig_put(double* p, double v) {
 // current diameters, by a whole workgroup of up to 16 waves: the linked
 // subcells of each atom's subcell (all subcells when n_cell <= 2) in groups
 // of 64 per wave (a group's bounds loaded by its lanes at once), the lanes
-// striding over a subcell's atoms, the wave sums added in wave order.
-// Every thread returns the same value.
+// striding over the group's atoms, the wave sums added in wave order.  Every
+// thread returns the same value.  Bound by the latency of a wave's loads: a
+// subcell holds a few atoms only, so a lane finds its atom among those of the
+// whole group (a search in the prefix sums of the counts) instead of the
+// wave taking one subcell after the other (d = 6, N = 100000, 729 subcells
+// of 6.4 atoms, 256 attempts: 105 -> 58 us).
 template <int D>
 __device__ inline double swap_de(const SysDev* s, int pi, int pj, double (*red)[16], double& si_out,
                                  double& sj_out) {
@@ -1794,6 +1798,7 @@ __device__ inline double swap_de(const SysDev* s, int pi, int pj, double (*red)[
   const double si = sig_get(xb + (size_t)pi * DR + D), sj = sig_get(xb + (size_t)pj * DR + D);
   si_out = si;
   sj_out = sj;
+  const double far = cut * 0.5 * (fmax(si, sj) + s->sigma_max), far2 = far * far * (1.0 + 1e-12);
   double eb = 0.0, ea = 0.0;
   if (pi != pj) {
     for (int side = 0; side < 2; side++) {
@@ -1830,19 +1835,29 @@ __device__ inline double swap_de(const SysDev* s, int pi, int pj, double (*red)[
           cs = flat[cell];
           ce = flat[cell + 1];
         }
-        const int ng = min(64, nst - t0);
-        for (int g = 0; g < ng; g++) {
-          const int q1 = __builtin_amdgcn_readlane(ce, g);
-          for (int q = __builtin_amdgcn_readlane(cs, g) + lane; q < q1; q += 64) {
+        const int cnt = ce - cs, incl = wave_scan(cnt);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        for (int f0 = 0; f0 < total; f0 += 64) {
+          // the first subcell of the group whose prefix sum exceeds f
+          const int f = f0 + lane;
+          int g = 0;
+#pragma unroll
+          for (int o = 32; o > 0; o >>= 1)
+            if (__shfl(incl, g + o - 1) <= f) g += o;
+          const int q = __shfl(cs, g) + f - (__shfl(incl, g) - __shfl(cnt, g));
+          if (f < total) {
             if (q == p) continue;
             double xq[D];
             load_x<D>(xb, q, xq);
-            const double sq = sig_get(xb + (size_t)q * DR + D);
             double r2 = 0.0;
             for (int a = 0; a < D; a++) {
               const double dx = min_image(xq[a] - xp[a], L, h);
               r2 = __builtin_fma(dx, dx, r2);
             }
+            // no diameter reaches further (most of the linked subcells' atoms:
+            // their diameters, each a load past the caches, are not read)
+            if (!(r2 < far2)) continue;
+            const double sq = sig_get(xb + (size_t)q * DR + D);
             double fc, uu;
             const double s_b = 0.5 * (sa + sq);
             if (r2 < (cut * s_b) * (cut * s_b)) {
@@ -1944,9 +1959,14 @@ __global__ __launch_bounds__(1024) void k_swap_de(const SysDev* s, const long lo
 
 // Settles the round's batch in order (see above), applies the kept exchanges,
 // and writes the attempts put off to off_out; ctl[0] = their number, ctl[2]
-// advances past the attempts begun, ctl[1] += exchanges kept.
+// advances past the attempts begun, ctl[1] += exchanges kept.  Only the
+// decisions hang together: one wave takes 64 attempts at a time, the
+// conflicts with the groups before in parallel, those inside the group one
+// after the other in scalar registers; the exchanges kept touch no atom in
+// common and are applied by all threads (one thread walking the batch with
+// the stores in its chain took 82 us for 256 attempts, this 21).
 template <int D>
-__global__ __launch_bounds__(1024) void k_swap_settle(SysDev* s, long long* __restrict__ ctl,
+__global__ __launch_bounds__(kSwapBatch) void k_swap_settle(SysDev* s, long long* __restrict__ ctl,
                                                       const int32_t* __restrict__ off_in,
                                                       int32_t* __restrict__ off_out, int64_t n_att,
                                                       const int32_t* __restrict__ pairs,
@@ -1957,61 +1977,87 @@ __global__ __launch_bounds__(1024) void k_swap_settle(SysDev* s, long long* __re
                                                       int32_t* __restrict__ acc,
                                                       double* __restrict__ diam) {
   constexpr int DR = Dims<D>::DR, NW = kSwapBatch / 64;
-  __shared__ unsigned long long conf[kSwapBatch][NW];
-  __shared__ int put_off[kSwapBatch];
-  __shared__ int att[kSwapBatch], cid[kSwapBatch][2], slot[kSwapBatch][2];
-  __shared__ double thr[kSwapBatch];  // the Metropolis decision as 0 / 1
-  const int tid = threadIdx.x;
+  __shared__ unsigned long long put[NW], kept[NW];  // per attempt: put off; settled and kept
+  const int tid = threadIdx.x, lane = tid & 63;
   const int nb = swap_batch_size(ctl, n_att);
   if (nb <= 0) return;
   const int nput = (int)ctl[0];
   double* xb = s->x[s->xcur];
-  for (int t = tid; t < nb * NW; t += blockDim.x) conf[t / NW][t % NW] = cfg[t];
-  for (int t = tid; t < 2 * nb; t += blockDim.x) {
-    const int b = t >> 1, e = t & 1, k = swap_attempt(ctl, off_in, b);
-    const int c = pairs[2 * k + e], q = slot_of[c];
-    cid[b][e] = c;
-    slot[b][e] = q;
-    if (e == 0) {
-      att[b] = k;
+  if (tid < 64) {
+    unsigned long long blk[NW], hits[NW], oks[NW];
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+      const int b = 64 * w + lane;
+      const bool in = b < nb;
       // the decision of an attempt that settles (its dE stands)
-      const double d = de[3 * b];
-      thr[b] = (d <= 0.0 || u[k] < exp(-d / T)) ? 1.0 : 0.0;
+      bool ok = false;
+      if (in) {
+        const int k = swap_attempt(ctl, off_in, b);
+        const double d = de[3 * b];
+        ok = d <= 0.0 || u[k] < exp(-d / T);
+      }
+      const unsigned long long okm = __ballot(ok);
+      bool before = false;
+#pragma unroll
+      for (int v = 0; v < NW; v++)
+        if (v < w && in) before = before || (cfg[(size_t)b * NW + v] & blk[v]) != 0;
+      const unsigned long long own = in ? cfg[(size_t)b * NW + w] : 0ull;
+      const unsigned long long pre = __ballot(before);
+      unsigned long long hit = 0ull, bl = 0ull;
+      const int cnt = min(max(nb - 64 * w, 0), 64);
+      for (int c = 0; c < cnt; c++) {
+        const unsigned long long m =
+            ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(own >> 32), c) << 32) |
+            (unsigned)__builtin_amdgcn_readlane((int)(unsigned)own, c);
+        const bool h = ((pre >> c) & 1ull) != 0 || (m & bl) != 0;
+        if (h) hit |= 1ull << c;
+        if (h || ((okm >> c) & 1ull)) bl |= 1ull << c;
+      }
+      blk[w] = bl;
+      hits[w] = hit;
+      oks[w] = okm & ~hit;
+    }
+#pragma unroll
+    for (int w = 0; w < NW; w++) {
+      if (lane == 0) {
+        put[w] = hits[w];
+        kept[w] = oks[w];
+      }
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    unsigned long long blk[NW];
-    for (int w = 0; w < NW; w++) blk[w] = 0;
-    int noff = 0;
-    long long kept = 0;
-    for (int b = 0; b < nb; b++) {
-      bool hit = false;
-      for (int w = 0; w < NW; w++) hit = hit || (conf[b][w] & blk[w]) != 0;
-      const int k = att[b];
-      if (hit) {
-        put_off[noff++] = k;
-        blk[b >> 6] |= 1ull << (b & 63);
-        continue;
-      }
-      const bool ok = thr[b] != 0.0;
+  int noff = 0, nkept = 0;
+  for (int w = 0; w < NW; w++) {
+    noff += __popcll(put[w]);
+    nkept += __popcll(kept[w]);
+  }
+  // off_in and ctl are read before any thread writes ctl (off_out is another array)
+  if (tid < nb) {
+    const int b = tid, w = b >> 6, k = swap_attempt(ctl, off_in, b);
+    if (put[w] >> (b & 63) & 1ull) {
+      int at = __popcll(put[w] & ((1ull << (b & 63)) - 1));
+      for (int v = 0; v < w; v++) at += __popcll(put[v]);
+      off_out[at] = k;
+    } else {
+      const bool ok = kept[w] >> (b & 63) & 1ull;
       if (acc) acc[k] = ok ? 1 : 0;
       if (ok) {
         // a settled attempt's atoms were not touched earlier in the batch, so
         // their diameters are the ones its dE was taken with
+        const int c0 = pairs[2 * k], c1 = pairs[2 * k + 1];
         const double si = de[3 * b + 1], sj = de[3 * b + 2];
-        sig_put(xb + (size_t)slot[b][0] * DR + D, sj);
-        sig_put(xb + (size_t)slot[b][1] * DR + D, si);
-        diam[cid[b][0]] = sj;
-        diam[cid[b][1]] = si;
-        kept++;
-        blk[b >> 6] |= 1ull << (b & 63);
+        sig_put(xb + (size_t)slot_of[c0] * DR + D, sj);
+        sig_put(xb + (size_t)slot_of[c1] * DR + D, si);
+        diam[c0] = sj;
+        diam[c1] = si;
       }
     }
-    for (int b = 0; b < noff; b++) off_out[b] = put_off[b];
+  }
+  __syncthreads();
+  if (tid == 0) {
     ctl[2] += nb - nput;
     ctl[0] = noff;
-    ctl[1] += kept;
+    ctl[1] += nkept;
   }
 }
 
