@@ -97,7 +97,7 @@ typedef struct {
    * at least 5) and the 5^d stencil; HDMD_ERR_ARG when L < 5 r_l,max/2.
    * HDMD_SUBCELLS_AUTO (0): the autotuner times both grids (where the half
    * grid applies and has at most max(64, 4n) subcells) on the first list
-   * build of each key (d, n_cell <= 2, log2 of the atoms per subcell) in the
+   * build of each key (d, form, log2 of the atoms per subcell) in the
    * process and keeps the faster for every later call with that key.  The
    * lists are the same on either grid; the atom order, and so the rounding
    * of the force sums, follows the grid. */
@@ -158,7 +158,7 @@ int hdmd_cells_per_axis(const hdmd_system* sys);
 /* The kernel configuration calls on sys use now.  List build (Sec. II.C):
  * *reach 1 (subcells of side >= r_l,max, 3^d stencil) or 2 (half-size
  * subcells, 5^d stencil), *cells_per_axis of that grid, and *variant 1, 2 or
- * 4: waves sharing a subcell (n_cell <= 2: 1).  Every variant builds the same
+ * 4: waves sharing a subcell (circle form: 1).  Every variant builds the same
  * lists, and the environment variable HDMD_BUILD_BLK forces one (reported as given;
  * other values take the nearest of 1, 2 and 4).  Forces (Sec. II.B
  * getforce): *lanes_per_atom 1, 2 or 4 lanes sharing an atom's row; the

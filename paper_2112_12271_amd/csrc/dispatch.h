@@ -17,11 +17,11 @@ struct DKernels {
   void (*bin)(const KArgs& a, int grid, hipStream_t st);
   // grid: workgroups of four tiles, and one for the finalisation
   void (*place)(bool mix, const KArgs& a, int grid, hipStream_t st);
-  // list build of the systems of n_cell >= 3 on one stencil radius (reach 1:
+  // list build by linked subcells on one stencil radius (reach 1:
   // subcells of side >= r_l,max, 3^d stencil; 2: half-size subcells, 5^d
   // stencil) and of one form (BuildMode), with G = 1, 2 or 4 waves per subcell
   void (*build)(int reach, int mode, int G, const KArgs& a, int grid, hipStream_t st);
-  // list build of the systems of n_cell <= 2, over atom tiles (split: quarters
+  // list build in the circle form, over atom tiles (split: quarters
   // of tiles)
   void (*build_wrap)(bool split, const KArgs& a, int grid, hipStream_t st);
   // the force kernels serve the systems of one precision form (mix) and one

@@ -17,7 +17,7 @@
 //   xref      positions at the last build [d][npad] FP64 (rebuild trigger).
 //   qc16      the list build's record of each atom: the f16 slots of its offset
 //             from the subcell centre quantised in units of L_sc/250 (32
-//             bytes), or, for n_cell <= 2, of its place on the circle along
+//             bytes), or, for the circle form, of its place on the circle along
 //             each axis (32 bytes; 48 for d >= 8).
 //   nl, nlen  Verlet rows in ELL form, column-major nl[k*npad + i], i.e. entry
 //             k of every row is contiguous so a wave reads it coalesced.  With
@@ -162,11 +162,11 @@ struct Table {
   int32_t build_waves;  // waves of the list builds under way, unsplit (the binning adds them up)
   // index d: dimension class d; index 0: all classes (atom tiles of class d
   // follow those of class d-1 in one array, so class 0 covers them all; the
-  // cell tiles of class 0 are an array of their own that lists the n_cell >= 3
+  // cell tiles of class 0 are an array of their own that lists the linked
   // subcells of every class before the wrap ones)
   int32_t n_atom[kMaxD + 1];
   int32_t n_cell[kMaxD + 1];
-  int32_t n_cell_nowrap[kMaxD + 1];  // cell tiles of systems with n_cell >= 3 come first
+  int32_t n_cell_nowrap[kMaxD + 1];  // cell tiles of systems built by linked subcells come first
   int32_t n_chunk;
   int32_t n_sys;
   int2* atom_tiles[kMaxD + 1];  // (slot, tile)
@@ -177,8 +177,8 @@ struct Table {
 };
 
 // Kernel arguments: either one system (tile = blockIdx) or a batch table.
-// part selects a sub-range of the cell tiles: 0 all, 1 systems with
-// n_cell >= 3, 2 systems with n_cell <= 2 (crowded subcells).
+// part selects a sub-range of the cell tiles: 0 all, 1 systems
+// built by linked subcells, 2 systems of the circle form.
 // fin (a system alone): the placement kernel also finalises the iteration; 2:
 // a FIRE iteration whose update takes the control's decision itself.
 struct KArgs {

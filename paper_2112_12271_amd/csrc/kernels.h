@@ -469,7 +469,7 @@ __device__ inline void place_tile(SysDev* s, int tile) {
     if (md) dout[(size_t)k * npad + dst] = din[(size_t)k * npad + src];
   }
   if (s->wrap) {
-    // slots on the circle (list build of n_cell <= 2)
+    // slots on the circle (the circle form of the list build)
     wrap_record<D>(s, x, sg, s->qc16 + (size_t)dst * WrapRec<D>::WORDS);
   } else {
     // the candidate slots of the matrix-core build, from the offsets to the
@@ -732,7 +732,7 @@ __global__ __launch_bounds__(256) void k_place(KArgs a) {
 // ---------------------------------------------------------------------------
 // Verlet-list build over the linked subcells (Sec. II.C, Fig. 1)
 //
-// Systems of n_cell >= 3 (and half-size subcells, at least 5 per axis): the
+// Linked subcells (n_cell >= 3, and half-size subcells, at least 5 per axis): the
 // matrix-core build.  Every atom's offset from its subcell centre is
 // quantised to q = y/Delta (Delta = L_sc/250, |q| <= 125), so an atom of the
 // subcell o away sits at q_j + 250 o.  A pair is within its list radius

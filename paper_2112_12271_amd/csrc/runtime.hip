@@ -532,12 +532,10 @@ static void load_system(const hdmd_system* sys, const Plan& p, const double* pos
 
 // The autotuner, on the first build of a key: for each grid the system may
 // take (an autotuned system whose half-size grid applies: both; otherwise its
-// own), loads the system, times the binning and subcell sort, then each
+// own), loads the system, times the binning and placement, then each
 // list-build variant (every variant gives the same list), and records the
 // best variant of each grid timed and, for an autotuned system, the grid of
-// the lower sum.  Half-size subcells are timed with the candidate-lane
-// variants only: the home-lane build stages each of the 5^d linked subcells,
-// most of them nearly empty.
+// the lower sum.
 static int tune_build(const hdmd_system* sys, const Plan& pf, const double* pos,
                       const double* diam, const double* vel, void* ws, hipStream_t st) {
   hipEvent_t e0, e1;
@@ -1342,7 +1340,7 @@ struct HostBatch {
   Table* dtab = nullptr;
   int2* d_atom = nullptr;
   int2* d_cell = nullptr;
-  int2* d_cell_all = nullptr;  // every class: all n_cell >= 3 subcells, then all wrap ones
+  int2* d_cell_all = nullptr;  // every class: all linked subcells, then those of the circle form
   int2* d_chunk = nullptr;
   int32_t* d_syslist = nullptr;
   int32_t* d_state = nullptr;
@@ -1434,7 +1432,7 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
       if (S.mode == MODE_MD) B->kinds_md[d] |= kind;
       else B->kinds_fire[d] |= kind;
     }
-    // cell tiles: systems with n_cell >= 3 first, then those of n_cell <= 2
+    // cell tiles: systems built by linked subcells first, then those of the circle form
     for (int pass = 0; pass < 2; pass++) {
       for (int s = 0; s < B->max_slots; s++) {
         const SlotInfo& S = B->slots[s];
@@ -1470,9 +1468,9 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
     t.cell_tiles[d] = B->d_cell + c_off[d];
   }
   t.n_atom[0] = (int32_t)atom_base;  // class 0: every class
-  // class 0 lists its cell tiles in an array of its own, the n_cell >= 3
+  // class 0 lists its cell tiles in an array of its own, the linked
   // subcells of every class before the others (the list build of a batch
-  // goes over the former only; it takes n_cell <= 2 systems by atom tiles)
+  // goes over the former only; it takes the circle form by atom tiles)
   std::vector<int2> cell_all;
   cell_all.reserve(cell.size());
   for (int pass = 0; pass < 2; pass++)
