@@ -1,7 +1,8 @@
 """Distance shells of the Verlet rows: forces right after a build (shell 0
 alone) and along runs whose displacement grows through the shells, against the
 oracle, with rows at the edges of the in-place ordering (32 rows of 64 entries
-down to one of 2048, and rows too long for it), a skin of zero, one lane and
+down to one of 2048, and rows too long for it; also of the export's, whose
+rows past 512 entries take another sort), a skin of zero, one lane and
 several per atom."""
 import os
 
@@ -24,7 +25,7 @@ def _ball(n, d, r, L, seed):
     return np.where(x >= L / 2, x - L, x)
 
 
-@pytest.mark.parametrize("n", [2, 64, 65, 66, 129, 257, 513, 1025, 2049, 2050, 2600])
+@pytest.mark.parametrize("n", [2, 64, 65, 66, 129, 257, 512, 513, 514, 1025, 2049, 2050, 2600])
 def test_rows_of_every_ordering_width(orc, n):
     """All atoms within the list radius of each other: rows of n - 1 entries,
     in every shell."""
