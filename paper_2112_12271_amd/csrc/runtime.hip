@@ -641,7 +641,17 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
       std::lock_guard<std::mutex> g(g_tune_mu);
       timed = g_lanes.count({p.d, mix, p.row_key}) > 0;
     }
+    bool usable = false;
     if (!timed) {
+      // only a usable list: the force kernels pass over a system whose rows
+      // overflowed (or whose input was refused), and timing their empty
+      // launches would settle the key for the process
+      SysDev h;
+      const int rc = read_desc(dev, &h, st);
+      if (rc) return rc;
+      usable = h.err == 0 && h.status == SLOT_RUNNING;
+    }
+    if (usable) {
       // the force kernel with 1, 2 and 4 lanes per atom on the list just built;
       // more lanes only where one lane takes at least 12 us and they save 10 %
       // (d = 4, N = 65536: 16.5 and 11.7 us, an MD step 30 and 25 us)
