@@ -73,12 +73,11 @@ __global__ __launch_bounds__(256) void k_scan1(KArgs a) {
     }
     const int nc = s->ncells;
     const int c0 = ch * kChunk + tid * 4;
-    int v[4], local = 0, mx = 0;
+    int v[4], local = 0;
 #pragma unroll
     for (int u = 0; u < 4; u++) {
       v[u] = (c0 + u < nc) ? s->cell_count[c0 + u] : 0;
       local += v[u];
-      mx = max(mx, v[u]);
     }
     sh[tid] = local;
     __syncthreads();
@@ -95,8 +94,6 @@ __global__ __launch_bounds__(256) void k_scan1(KArgs a) {
       run += v[u];
     }
     if (tid == 255) s->chunk_sum[ch] = sh[255];
-    mx = wave_max_i(mx);
-    if ((tid & 63) == 0 && mx > 0) atomicMax(&s->max_cell, mx);
     __syncthreads();
   }
 }

@@ -140,7 +140,7 @@ struct SysDev {
   // ---- dynamic, written by the kernels
   int32_t xcur, pcur, force_rebuild, err;
   unsigned long long maxdisp2;  // bit pattern of a non-negative double
-  int32_t max_row, max_cell, status, fstatus;
+  int32_t max_row, status, fstatus;
   int64_t step, builds, iters;
   double ke, pe;
   double fdt, falpha, fmax, c_keep, c_mix;

@@ -205,7 +205,6 @@ template <int D>
 __device__ inline void bin_tile(SysDev* s, int tile) {
   const int lane = threadIdx.x & 63;
   if (tile == 0 && lane == 0) {
-    s->max_cell = 0;
     s->rx = s->xcur;
     s->rp = s->pcur;
   }
@@ -265,21 +264,18 @@ __device__ inline void scatter_atom(SysDev* s, int i, int c, int r) {
 
 // Exclusive prefix of the subcell occupancies by one workgroup of kBinBlock
 // threads, 1024 subcells per wave and pass (sixteen independent wave scans).
-// sh: 2 x kBinBlock / 64 words.
+// sh: kBinBlock / 64 words.
 __device__ inline void scan_cells(SysDev* s, int* sh) {
   constexpr int W = kBinBlock / 64, PER = 16;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, nc = s->ncells;
-  int carry = 0, mx = 0;
+  int carry = 0;
   for (int b = 0; b < nc; b += kBinBlock * PER) {
     const int c0 = b + w * 64 * PER + lane;
     int v[PER], x[PER];
 #pragma unroll
     for (int u = 0; u < PER; u++) v[u] = c0 + 64 * u < nc ? load_agent(s->cell_count + c0 + 64 * u) : 0;
 #pragma unroll
-    for (int u = 0; u < PER; u++) {
-      mx = max(mx, v[u]);
-      x[u] = v[u];
-    }
+    for (int u = 0; u < PER; u++) x[u] = v[u];
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
 #pragma unroll
@@ -310,14 +306,7 @@ __device__ inline void scan_cells(SysDev* s, int* sh) {
     __syncthreads();
   }
   for (int ch = tid; ch < s->nchunks; ch += kBinBlock) s->chunk_off[ch] = 0;
-  mx = wave_max_i(mx);
-  if (lane == 0) sh[W + w] = mx;
-  __syncthreads();
-  if (tid == 0) {
-    for (int q = 1; q < W; q++) mx = max(mx, sh[W + q]);
-    s->max_cell = mx;
-    s->max_row = 0;
-  }
+  if (tid == 0) s->max_row = 0;
 }
 
 // The binning of a system alone, and in its last workgroup to end (by
@@ -325,7 +314,7 @@ __device__ inline void scan_cells(SysDev* s, int* sh) {
 // (bin_scans, bin_scatters).
 template <int D>
 __global__ __launch_bounds__(kBinBlock) void k_bin(KArgs a) {
-  __shared__ int sh[2 * kBinBlock / 64];
+  __shared__ int sh[kBinBlock / 64];
   SysDev* s = a.single;
   const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const bool rb = running(s) && need_rebuild(s);
