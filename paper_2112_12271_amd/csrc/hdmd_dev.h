@@ -324,9 +324,16 @@ __device__ inline bool fetch_cell_tile_u(const KArgs& a, int t, SysDev*& s, int&
 // d = 3, N = 8192 36 us and N = 1000 17 us (bin, scans and scatter 20 and 4
 // launches).  Past 65536 subcells or 8192 atoms one workgroup takes longer
 // than the launches saved; k_scan1, k_scan2 and k_scatter run.
-__host__ __device__ constexpr bool bin_scans(int nchunks) { return nchunks <= 65536 / kChunk; }
-__host__ __device__ constexpr bool bin_scatters(int n, int nchunks) {
-  return n <= 8192 && bin_scans(nchunks);
+// A first build (fin = 0) has no such steps to save for: past kFirstTail atoms
+// it takes the launches of their own (d = 2, kernels: N = 8192 50 us by the
+// binning and 16 apart, N = 3456 32 and 15; N = 1000 15 and 17).  A whole
+// hdmd_build_nlist at N = 8192: d = 2 182 -> 156 us, d = 4 188 -> 159.
+constexpr int kFirstTail = 1024;
+__host__ __device__ constexpr bool bin_scans(int fin, int n, int nchunks) {
+  return nchunks <= 65536 / kChunk && (fin || n <= kFirstTail);
+}
+__host__ __device__ constexpr bool bin_scatters(int fin, int n, int nchunks) {
+  return n <= 8192 && bin_scans(fin, n, nchunks);
 }
 
 // Largest system (in tiles) whose FIRE update kernel takes the control's

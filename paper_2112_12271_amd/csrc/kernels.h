@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(KArgs a) {
   const int nt = s->ntiles, n = s->n;
   for (int t = blockIdx.x * (kBinBlock / 64) + w; t < nt; t += gridDim.x * (kBinBlock / 64))
     bin_tile<D>(s, t);
-  if (!bin_scans(s->nchunks)) return;
+  if (!bin_scans(a.fin, n, s->nchunks)) return;
   // every value the last workgroup reads of the others' went out past the
   // caches (additions, store_agent); it has arrived when the wave's count of
   // outstanding accesses is zero, so that no cache is written back here
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(kBinBlock) void k_bin(KArgs a) {
   __syncthreads();
   if (tid == 0) s->ticket = 0;
   scan_cells(s, sh);
-  if (!bin_scatters(n, s->nchunks)) return;
+  if (!bin_scatters(a.fin, n, s->nchunks)) return;
   __threadfence_block();
   __syncthreads();
   for (int b = tid; b < n; b += 4 * kBinBlock) {

@@ -459,11 +459,11 @@ static void chain_sort(const Plan& p, SysDev* dev, hipStream_t st, int fin) {
   a.fin = fin;
   constexpr int per_bin = kBinBlock / kTile;
   K->bin(a, std::min((p.ntiles + per_bin - 1) / per_bin, 256), st);
-  if (!bin_scans(p.nchunks)) {
+  if (!bin_scans(fin, p.n, p.nchunks)) {
     launch_scan1(a, p.nchunks, st);
     launch_scan2(a, 1, st);
   }
-  if (!bin_scatters(p.n, p.nchunks)) launch_scatter(a, std::min(p.ntiles, 1024), st);
+  if (!bin_scatters(fin, p.n, p.nchunks)) launch_scatter(a, std::min(p.ntiles, 1024), st);
   K->place(p.mix, a, std::min((p.ntiles + 3) / 4, 512) + 1, st);
 }
 
