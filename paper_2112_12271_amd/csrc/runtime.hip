@@ -68,6 +68,9 @@ struct Plan {
   int n = 0, npad = 0, ncell = 0, ncells = 0, nchunks = 0;
   int ntiles = 0, nwaves = 0, width = 0;
   bool wrap = false;  // the list build's circle form (circle_form)
+  // rows in distance shells; a list that is built to be exported, or for its
+  // row lengths (hdmd_build_nlist, hdmd_swap), has no use for them
+  bool shells = true;
   bool mix = false, morse = false;
   // reach: stencil radius in subcells (1: side >= r_l,max, 3^d stencil; 2:
   // half-size subcells, 5^d stencil); key_wrap/key_occ: the autotuner's key,
@@ -339,7 +342,7 @@ static SysDev make_desc(const hdmd_system* s, const Plan& p, void* ws) {
   // rounding of r
   h.ends = at<uint16_t>(ws, p.off_ends);
   h.nshell =
-      p.n < (1 << 28) && p.width < 65536 && s->skin >= 1e-6 * p.rlmax ? kShells : 1;
+      p.shells && p.n < (1 << 28) && p.width < 65536 && s->skin >= 1e-6 * p.rlmax ? kShells : 1;
   h.jmask = h.nshell == 1 ? 0x7fffffff : (1 << 28) - 1;
   h.sh_scale = h.nshell == 1 ? 0.0 : kShells / s->skin;
   h.sh_off = 1e-6 + h.sh_scale * s->box_l * 0x1p-29;
@@ -551,6 +554,7 @@ static int tune_build(const hdmd_system* sys, const Plan& pf, const double* pos,
   const int r0 = pf.nh_auto ? 1 : pf.reach, r1 = pf.nh_auto ? 2 : pf.reach;
   for (int reach = r0; reach <= r1; reach++) {
     Plan p = pf;
+    p.shells = true;  // the choice serves runs
     if (reach == 2) {
       // the same layout with the half-size grid
       p.reach = 2;
@@ -626,32 +630,31 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
     Plan q;
     rc = make_plan(sys, q);
     if (rc) return rc;
+    q.shells = p.shells;
     p = q;
     blk = lookup_blk(p, &known);
   }
+  // whether the lanes of the force kernels are yet to be timed for the key
+  const int mix = p.mix ? 1 : 0;
+  bool time_lanes = !p.morse && !lpa_env() && p.n >= kLanesMinAtoms && tuning_enabled() && allow_tune;
+  if (time_lanes) {
+    std::lock_guard<std::mutex> g(g_tune_mu);
+    time_lanes = g_lanes.count({p.d, mix, p.row_key}) == 0;
+  }
+  if (time_lanes) p.shells = true;
   load_system(sys, p, pos, diam, vel, ws, st);
   SysDev* dev = at<SysDev>(ws, p.off_desc);
   chain_single(p, dev, st, blk, 0);
   launch_finalize(single_args(dev, p.d), 1, st);
   HIPCHK(hipGetLastError());
-  if (!p.morse && !lpa_env() && p.n >= kLanesMinAtoms && tuning_enabled() && allow_tune) {
-    const int mix = p.mix ? 1 : 0;
-    bool timed = false;
-    {
-      std::lock_guard<std::mutex> g(g_tune_mu);
-      timed = g_lanes.count({p.d, mix, p.row_key}) > 0;
-    }
-    bool usable = false;
-    if (!timed) {
-      // only a usable list: the force kernels pass over a system whose rows
-      // overflowed (or whose input was refused), and timing their empty
-      // launches would settle the key for the process
-      SysDev h;
-      const int rc = read_desc(dev, &h, st);
-      if (rc) return rc;
-      usable = h.err == 0 && h.status == SLOT_RUNNING;
-    }
-    if (usable) {
+  if (time_lanes) {
+    // only a usable list: the force kernels pass over a system whose rows
+    // overflowed (or whose input was refused), and timing their empty
+    // launches would settle the key for the process
+    SysDev h;
+    const int rc = read_desc(dev, &h, st);
+    if (rc) return rc;
+    if (h.err == 0 && h.status == SLOT_RUNNING) {
       // the force kernel with 1, 2 and 4 lanes per atom on the list just built;
       // more lanes only where one lane takes at least 12 us and they save 10 %
       // (d = 4, N = 65536: 16.5 and 11.7 us, an MD step 30 and 25 us)
@@ -830,6 +833,7 @@ int hdmd_build_nlist(const hdmd_system* sys, const double* pos, const double* di
   int rc = make_plan(sys, p);
   if (rc) return rc;
   hipStream_t st = S(stream);
+  p.shells = false;
   rc = init_system(sys, p, pos, diam, nullptr, ws, ws_bytes, st, nullptr);
   if (rc) return rc;
   SysDev h;
@@ -1186,6 +1190,7 @@ static int swap_run(const hdmd_system* sys, const double* pos, double* diam, voi
   HIPCHK(hipMemcpyAsync(hc, w.ctl, sizeof(hc), hipMemcpyDeviceToHost, st));
   HIPCHK(hipStreamSynchronize(st));
   if (hc[3]) return fail(HDMD_ERR_ARG, "swap pair names an atom outside [0, n)");
+  p.shells = false;
   rc = init_system(sys, p, pos, diam, nullptr, ws, ws_bytes, st, nullptr);
   if (rc) return rc;
   SysDev* dev = at<SysDev>(ws, p.off_desc);
