@@ -21,9 +21,9 @@ struct DKernels {
   // subcells of side >= r_l,max, 3^d stencil; 2: half-size subcells, 5^d
   // stencil) and of one form (BuildMode), with G = 1, 2 or 4 waves per subcell
   void (*build)(int reach, int mode, int G, const KArgs& a, int grid, hipStream_t st);
-  // list build in the circle form, over atom tiles (split: quarters
-  // of tiles)
-  void (*build_wrap)(bool split, const KArgs& a, int grid, hipStream_t st);
+  // list build in the circle form, over atom tiles, `homes` atoms (4, 16 or
+  // kTile) per workgroup
+  void (*build_wrap)(int homes, const KArgs& a, int grid, hipStream_t st);
   // the force kernels serve the systems of one precision form (mix) and one
   // potential class (morse: the Morse form; otherwise WCA and harmonic)
   void (*force)(bool mix, int lpa, bool morse, const KArgs& a, int grid, int fire, hipStream_t st);

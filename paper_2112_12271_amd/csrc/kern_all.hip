@@ -191,8 +191,8 @@ __global__ __launch_bounds__(256, 4) void k_build_all(KArgs a) {
         switch (((cSys*)s)->d) {
 #define HDMD_CASE(DD)                                                                  \
   case DD:                                                                             \
-    if (sh) build_wrap_tile<DD, 1>(s, hb, reinterpret_cast<WrapLds*>(&lds[wv]));       \
-    else build_wrap_tile<DD, 4>(s, hb, reinterpret_cast<WrapLds*>(&lds[wv]));          \
+    if (sh) build_wrap_tile<DD, 1>(s, hb, 16, reinterpret_cast<WrapLds*>(&lds[wv]));       \
+    else build_wrap_tile<DD, 4>(s, hb, kTile, reinterpret_cast<WrapLds*>(&lds[wv]));          \
     break;
           HDMD_BUILD_D(HDMD_CASE)
 #undef HDMD_CASE

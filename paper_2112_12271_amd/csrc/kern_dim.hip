@@ -50,9 +50,9 @@ void l_build(int reach, int mode, int G, const KArgs& a, int grid, hipStream_t s
     else k_build_mf<D, 4, 1, BUILD_SPARSE><<<grid, 256, 0, st>>>(a);
   }
 }
-void l_build_wrap(bool split, const KArgs& a, int grid, hipStream_t st) {
-  if (split) k_build_wrap<D, 1><<<grid, 64, 0, st>>>(a);
-  else k_build_wrap<D, 4><<<grid, 64, 0, st>>>(a);
+void l_build_wrap(int homes, const KArgs& a, int grid, hipStream_t st) {
+  if (homes <= 16) k_build_wrap<D, 1><<<grid, 64, 0, st>>>(a, homes);
+  else k_build_wrap<D, 4><<<grid, 64, 0, st>>>(a, homes);
 }
 template <bool MIX, int LPA, bool MORSE = false>
 void force_lpa(const KArgs& a, int grid, int fire, hipStream_t st) {

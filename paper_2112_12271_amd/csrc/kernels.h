@@ -1541,16 +1541,16 @@ struct WrapLds {
   int pad[kShellRow - 128 - sizeof(SurvivorLds<unsigned>) / 4];  // shell_order takes it all
 };
 
-// Home atoms hb .. hb + 16 HB - 1.
+// Home atoms hb .. hb + homes - 1 (homes <= 16 HB).
 template <int D, int HB>
-__device__ __forceinline__ void build_wrap_tile(SysDev* sys, int hb, WrapLds* m) {
+__device__ __forceinline__ void build_wrap_tile(SysDev* sys, int hb, int homes, WrapLds* m) {
   typedef WrapRec<D> R;
   typedef typename std::conditional<R::LW == 2, hv4, hv8>::type Op;
   cSys* s = (cSys*)sys;
   const int lane = threadIdx.x & 63, g = lane >> 4, col = lane & 15;
   const int n = s->n, npad = s->npad, W = s->width;
   if (hb >= n) return;
-  const int hcnt = min(16 * HB, n - hb);
+  const int hcnt = min(homes, n - hb);
   const double* __restrict__ xb = s->x[s->rx];
   const int* __restrict__ rec = s->qc16;
   const double L = s->L, hL = s->hL, cut = s->cutoff, skin = s->skin;
@@ -1665,20 +1665,21 @@ __device__ __forceinline__ void build_wrap_tile(SysDev* sys, int hb, WrapLds* m)
   }
 }
 
-// One system: a tile per workgroup, or (HB = 1) a quarter of one.
+// One system: a tile per workgroup, or (HB = 1) `homes` atoms of one.
 template <int D, int HB>
-__global__ __launch_bounds__(64, 4) void k_build_wrap(KArgs a) {
+__global__ __launch_bounds__(64, 4) void k_build_wrap(KArgs a, int homes) {
   __shared__ WrapLds lds;
+  const int per = kTile / homes;  // workgroups per tile
   for (int t = blockIdx.x;; t += gridDim.x) {
     SysDev* s;
     int tile;
-    if (!fetch_atom_tile_u(a, t * HB / 4, s, tile)) break;
+    if (!fetch_atom_tile_u(a, t / per, s, tile)) break;
     cSys* c = (cSys*)s;
     if (!rebuilding(a, c) | (c->wrap == 0)) {
       if (a.single) break;  // one system: the same for every tile
       continue;
     }
-    build_wrap_tile<D, HB>(s, tile * 64 + (HB == 4 ? 0 : (t & 3) * 16), &lds);
+    build_wrap_tile<D, HB>(s, tile * kTile + t % per * homes, homes, &lds);
   }
 }
 

@@ -470,13 +470,29 @@ static void chain_sort(const Plan& p, SysDev* dev, hipStream_t st, int fin) {
   K->place(p.mix, a, std::min((p.ntiles + 3) / 4, 512) + 1, st);
 }
 
+// Home atoms per wave of a lone system's circle form (the rows do not depend on
+// it): a tile, or a quarter of one while those are all at work at once, four
+// waves per SIMD (d = 6, N = 8192: 155 us by tiles, 53 by quarters).  A wave's
+// time is then its survivors', one exact test after the other: where rows are
+// long (n_cell <= 2: each atom lists much of the box) or the waves few, a wave
+// takes four home atoms.  hdmd_build_nlist by quarters and by fours: n_cell =
+// 2, d = 3, N = 1000 291 and 147 us, N = 6000 1428 and 546, d = 6, N = 8192
+// 469 and 270; past that the repeated products count (d = 8, N = 16000 352
+// and 357).  n_cell >= 3, d = 7, N = 1000 155 and 133, d = 3, N = 1000 99 and
+// 98, N = 3456 113 and 121.
+static int circle_homes(const Plan& p) {
+  if (p.ntiles <= (p.ncell <= 2 ? 128 : 16)) return 4;
+  return p.ntiles <= 1024 ? 16 : kTile;
+}
+
 static void build_single(const Plan& p, SysDev* dev, hipStream_t st, int blk) {
   const DKernels* K = dkernels(p.d);
-  // the circle form takes quarters of tiles while they are all at work at
-  // once, four waves per SIMD (d = 6, N = 8192: 155 us by tiles, 53 by quarters)
-  const bool split = p.ntiles <= 1024;
-  if (p.wrap) K->build_wrap(split, single_args(dev, p.d), split ? 4 * p.ntiles : p.ntiles, st);
-  else K->build(p.reach, build_mode(p.reach, p.n, p.ncells), blk, single_args(dev, p.d), p.ncells, st);
+  if (p.wrap) {
+    const int homes = circle_homes(p);
+    K->build_wrap(homes, single_args(dev, p.d), p.ntiles * (kTile / homes), st);
+  } else {
+    K->build(p.reach, build_mode(p.reach, p.n, p.ncells), blk, single_args(dev, p.d), p.ncells, st);
+  }
 }
 
 static void chain_single(const Plan& p, SysDev* dev, hipStream_t st, int blk, int fin) {
@@ -1566,7 +1582,7 @@ static void enqueue_batch_iter(HostBatch* B, const std::vector<int>& grids, hipS
       K->build(1, BUILD_DENSE, 1, batch_args(B, d, 1), gc(d), st);
     }
     if (B->has_half[d]) K->build(2, BUILD_DENSE, 1, batch_args(B, d, 1), gc(d), st);
-    if (B->has_wrap[d]) K->build_wrap(false, batch_args(B, d), ga(d), st);
+    if (B->has_wrap[d]) K->build_wrap(kTile, batch_args(B, d), ga(d), st);
   };
   if (gb_all > 0) {
     bool half = false;
