@@ -200,7 +200,13 @@ __device__ inline void store_agent(int* p, int v) {
 // rank.  The wave adds to a subcell's count once for all its atoms there: in
 // the order of the last build most of a wave's atoms share a few subcells, and
 // one addition each made the counts the bottleneck (d = 8, N = 131072, 256
-// subcells: 300 us of same-address additions).
+// subcells: 300 us of same-address additions).  It gathers the subcells of
+// kBinGather lanes that way; the atoms left over, of waves whose atoms are
+// scattered over many subcells (a first build in the caller's order, few atoms
+// per subcell), are added one by one: gathering all 64 took 7 us of a first
+// build of N = 1152 (k_bin 10.6 us; 3.2 without).  Eight were too few for runs
+// (d = 4, N = 65536, 6.6 atoms per subcell: 12.99 ms, 12.94 with sixteen).
+constexpr int kBinGather = 16;
 template <int D>
 __device__ inline void bin_tile(SysDev* s, int tile) {
   const int lane = threadIdx.x & 63;
@@ -226,9 +232,9 @@ __device__ inline void bin_tile(SysDev* s, int tile) {
     }
     c = flat_cell<D>(s, x);
   }
-  int rk = 0, lead = lane, cnt = 0;
+  int rk = 0, lead = lane, cnt = 1;
   unsigned long long todo = __ballot(vi);
-  while (todo) {
+  for (int g = 0; g < kBinGather && todo; g++) {
     const int l = __builtin_ctzll(todo);
     const unsigned long long m = __ballot(c == __builtin_amdgcn_readlane(c, l));
     if (m >> lane & 1) {
