@@ -1671,11 +1671,11 @@ __device__ __forceinline__ void build_wrap_tile(SysDev* sys, int hb, int homes, 
   }
 }
 
-// One system: a tile per workgroup, or (HB = 1) `homes` atoms of one.
+// One system: a tile per workgroup, or (HB = 1) `few` (4 or 16) atoms of one.
 template <int D, int HB>
-__global__ __launch_bounds__(64, 4) void k_build_wrap(KArgs a, int homes) {
+__global__ __launch_bounds__(64, 4) void k_build_wrap(KArgs a, int few) {
   __shared__ WrapLds lds;
-  const int per = kTile / homes;  // workgroups per tile
+  const int homes = HB == 1 ? few : 16 * HB, per = kTile / homes;  // workgroups per tile
   for (int t = blockIdx.x;; t += gridDim.x) {
     SysDev* s;
     int tile;
