@@ -41,10 +41,6 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
   for (; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-__global__ void k_set_status(SysDev* s, int32_t status) {
-  if (threadIdx.x == 0) s->status = status;
-}
-
 // Snapshot of every slot's state and iteration / step count.
 __global__ void k_poll(const Table* t, int32_t* state, int64_t* iters) {
   int slot = blockIdx.x * blockDim.x + threadIdx.x;
@@ -357,9 +353,6 @@ void launch_export(const SysDev* s, int n, int64_t* row_ptr, int32_t* cols, hipS
   if (phase == 0) k_export_lens<<<(n + 255) / 256, 256, 0, st>>>(s, row_ptr);
   else if (phase == 1) k_export_scan<<<1, 1024, 0, st>>>(n, row_ptr);
   else k_export_fill<<<n, 256, 0, st>>>(s, row_ptr, cols);
-}
-void launch_set_status(SysDev* s, int32_t status, hipStream_t st) {
-  k_set_status<<<1, 64, 0, st>>>(s, status);
 }
 void launch_poll(const Table* t, int max_slots, int32_t* state, int64_t* iters, hipStream_t st) {
   k_poll<<<(max_slots + 255) / 256, 256, 0, st>>>(t, state, iters);

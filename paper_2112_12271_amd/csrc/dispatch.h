@@ -68,7 +68,6 @@ void launch_slot_of(const SysDev* s, int n, int32_t* slot_of, hipStream_t st);
 void launch_swap_init(int64_t n_att, const int32_t* pairs, int n, long long* ctl, hipStream_t st);
 void launch_export(const SysDev* s, int n, int64_t* row_ptr, int32_t* cols, hipStream_t st,
                    int phase);
-void launch_set_status(SysDev* s, int32_t status, hipStream_t st);
 void launch_poll(const Table* t, int max_slots, int32_t* state, int64_t* iters, hipStream_t st);
 
 }  // namespace hdmd

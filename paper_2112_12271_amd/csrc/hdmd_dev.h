@@ -60,7 +60,6 @@ __host__ __device__ inline int build_mode(int reach, int64_t n, int64_t ncells) 
   return reach == 2 || n > 16 * ncells ? BUILD_DENSE : BUILD_SPARSE;
 }
 
-
 enum Mode : int32_t { MODE_NONE = 0, MODE_FIRE = 1, MODE_MD = 2, MODE_STATIC = 3 };
 enum Slot : int32_t { SLOT_EMPTY = 0, SLOT_RUNNING = 1, SLOT_DONE = 2 };
 enum Err : int32_t {
@@ -160,13 +159,11 @@ struct SysDev {
 struct Table {
   int32_t max_slots;
   int32_t build_waves;  // waves of the list builds under way, unsplit (the binning adds them up)
-  // index d: dimension class d; index 0: all classes (atom tiles of class d
-  // follow those of class d-1 in one array, so class 0 covers them all; the
-  // cell tiles of class 0 are an array of their own that lists the linked
-  // subcells of every class before the wrap ones)
+  // index d: dimension class d; index 0: all classes (the tiles of class d
+  // follow those of class d-1 in one array, so class 0 covers them all).  Cell
+  // tiles: the subcells of the systems built by linked subcells
   int32_t n_atom[kMaxD + 1];
   int32_t n_cell[kMaxD + 1];
-  int32_t n_cell_nowrap[kMaxD + 1];  // cell tiles of systems built by linked subcells come first
   int32_t n_chunk;
   int32_t n_sys;
   int2* atom_tiles[kMaxD + 1];  // (slot, tile)
@@ -177,15 +174,12 @@ struct Table {
 };
 
 // Kernel arguments: either one system (tile = blockIdx) or a batch table.
-// part selects a sub-range of the cell tiles: 0 all, 1 systems
-// built by linked subcells, 2 systems of the circle form.
 // fin (a system alone): the placement kernel also finalises the iteration; 2:
 // a FIRE iteration whose update takes the control's decision itself.
 struct KArgs {
   SysDev* single;
   Table* tab;
   int32_t cls;
-  int32_t part;
   int32_t fin;
 };
 
@@ -212,22 +206,6 @@ __device__ inline bool fetch_atom_tile(const KArgs& a, int t, SysDev*& s, int& t
   int2 e = a.tab->atom_tiles[a.cls][t];
   s = a.tab->sys[e.x];
   tile = e.y;
-  return true;
-}
-
-__device__ inline bool fetch_cell_tile(const KArgs& a, int t, SysDev*& s, int& cell) {
-  if (a.single) {
-    s = a.single;
-    cell = t;
-    return t < s->ncells;
-  }
-  int lo = 0, hi = a.tab->n_cell[a.cls];
-  if (a.part == 1) hi = a.tab->n_cell_nowrap[a.cls];
-  else if (a.part == 2) lo = a.tab->n_cell_nowrap[a.cls];
-  if (t >= hi - lo) return false;
-  int2 e = a.tab->cell_tiles[a.cls][lo + t];
-  s = a.tab->sys[e.x];
-  cell = e.y;
   return true;
 }
 
@@ -306,11 +284,8 @@ __device__ inline bool fetch_cell_tile_u(const KArgs& a, int t, SysDev*& s, int&
     return t < ((cSys*)a.single)->ncells;
   }
   cTable* tab = (cTable*)a.tab;
-  int lo = 0, hi = tab->n_cell[a.cls];
-  if (a.part == 1) hi = tab->n_cell_nowrap[a.cls];
-  else if (a.part == 2) lo = tab->n_cell_nowrap[a.cls];
-  if (t >= hi - lo) return false;
-  cint2* e = (cint2*)tab->cell_tiles[a.cls] + lo + t;
+  if (t >= tab->n_cell[a.cls]) return false;
+  cint2* e = (cint2*)tab->cell_tiles[a.cls] + t;
   s = tab->sys[e->x];
   cell = e->y;
   return true;

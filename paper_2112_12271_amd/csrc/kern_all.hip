@@ -145,7 +145,7 @@ __global__ __launch_bounds__(256, 4) void k_build_all(KArgs a) {
   static_assert(sizeof(WrapLds) <= sizeof(BuildLds<RAD>), "one LDS area serves both builds");
   cTable* tab = (cTable*)a.tab;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int nnw = tab->n_cell_nowrap[0];
+  const int nnw = tab->n_cell[0];
   cint2* tiles = (cint2*)tab->cell_tiles[0];
   // this wave's tiles are strided by the waves of the launch
   const int g = gridDim.x * 4, me = xcd_tile(blockIdx.x, gridDim.x) * 4 + wv;

@@ -2476,7 +2476,7 @@ __global__ __launch_bounds__(kTile * LPA) void k_step(KArgs a) {
     const bool first = s->step == 0, close = s->step >= s->nsteps;
     const bool rec = s->thermo && s->thermo_every > 0 && s->step % s->thermo_every == 0;
     const double dt = s->dt, hdt = 0.5 * dt;
-      Own<D, MIX> me;
+    Own<D, MIX> me;
     load_own<D, MIX>(s, ii, me);
     VT F[D];
     double e, w, z;

@@ -138,7 +138,6 @@ static int occ_bucket(int64_t n, int64_t ncells) {
   return b;
 }
 
-// the autotuner's grid for a key: 0 (not tuned yet), 1 or 2 (reach)
 // Systems whose list is built in the circle form (every atom a candidate of
 // every other): those of n_cell <= 2, where the linked subcells do not cover
 // several images, and small ones.  A small system's build lasts as long as
@@ -157,6 +156,7 @@ static bool circle_form(int d, int64_t n, int reach, int ncell) {
   return d <= 7 && n <= std::min(kCircleAtoms, 128 * ipow(3, d)) && !(e && e[0] == '0');
 }
 
+// the autotuner's grid for a key: 0 (not tuned yet), 1 or 2 (reach)
 static int tuned_reach(int d, int wrap, int occ);
 // lanes per atom of the force kernels for a system (the autotuner's, or 1),
 // keyed by the row-length bucket
@@ -403,8 +403,6 @@ static int lookup_blk(const Plan& p, bool* known) {
   return it->second.blk[p.reach];
 }
 
-
-
 // Lanes per atom of the force kernels (1, 2 or 4 lanes share an atom's row;
 // their partial sums meet in a tree that depends on the count, so the choice
 // fixes the rounding of the forces): chosen by the autotuner per (d,
@@ -444,7 +442,6 @@ static KArgs single_args(SysDev* dev, int d) {
   a.single = dev;
   a.tab = nullptr;
   a.cls = d;
-  a.part = 0;
   a.fin = 0;
   return a;
 }
@@ -582,7 +579,7 @@ static int tune_build(const hdmd_system* sys, const Plan& pf, const double* pos,
       p.reach = 1;
       p.ncell = choose_ncell(*sys, pf.rlmax);
       p.ncells = (int)ipow(p.ncell, p.d);
-          p.nchunks = (p.ncells + kChunk - 1) / kChunk;
+      p.nchunks = (p.ncells + kChunk - 1) / kChunk;
       p.wrap = circle_form(p.d, p.n, 1, p.ncell);
     }
     SysDev* dev = at<SysDev>(ws, p.off_desc);
@@ -788,7 +785,6 @@ static int run_chunk(void* ws, int kind, EnqueueFn fn, int chunk, const Plan& p,
   return HDMD_OK;
 }
 
-
 }  // namespace hdmd
 
 using namespace hdmd;
@@ -907,7 +903,6 @@ static int forces_run(const hdmd_system* sys, Plan& p, const double* pos, const 
   if (rc) return rc;
   return err_to_status(h.err, "hdmd_forces");
 }
-
 
 // Device memory of hdmd_forces_noalloc: a scratch array the library holds on
 // every device it runs on (until the process ends) in place of a caller's
@@ -1362,16 +1357,15 @@ struct SlotInfo {
   SysDev* dev = nullptr;
   void* ws = nullptr;
   int mode = 0;
-  int blk = 64;
 };
 
 struct HostBatch {
   int max_slots = 0;
+  // (cap_cell counts every system's subcells, of either form)
   int64_t cap_atom = 0, cap_cell = 0, cap_chunk = 0;
   Table* dtab = nullptr;
   int2* d_atom = nullptr;
   int2* d_cell = nullptr;
-  int2* d_cell_all = nullptr;  // every class: all linked subcells, then those of the circle form
   int2* d_chunk = nullptr;
   int32_t* d_syslist = nullptr;
   int32_t* d_state = nullptr;
@@ -1379,9 +1373,9 @@ struct HostBatch {
   std::vector<SlotInfo> slots;
   bool dirty = true;
   // current composition
-  int n_atom[kMaxD + 1] = {0}, n_cell[kMaxD + 1] = {0}, n_nowrap[kMaxD + 1] = {0};
+  int n_atom[kMaxD + 1] = {0}, n_cell[kMaxD + 1] = {0};
   int n_chunk = 0, n_sys = 0;
-  int n_atom_all = 0, n_cell_all = 0, n_nowrap_all = 0;
+  int n_atom_all = 0, n_cell_all = 0;
   bool has_fire = false, has_md = false, has_wrap[kMaxD + 1] = {false},
        has_nowrap[kMaxD + 1] = {false}, mix[kMaxD + 1] = {false},
        has_half[kMaxD + 1] = {false};  // systems on half-size subcells
@@ -1395,7 +1389,7 @@ static std::mutex g_batch_mu;
 static std::unordered_map<void*, HostBatch*> g_batches;
 
 struct BatchLayout {
-  size_t off_tab, off_atom, off_cell, off_cell_all, off_chunk, off_sys, off_state, off_iters, bytes;
+  size_t off_tab, off_atom, off_cell, off_chunk, off_sys, off_state, off_iters, bytes;
 };
 
 static BatchLayout batch_layout(int max_slots, int64_t cap_atom, int64_t cap_cell,
@@ -1410,7 +1404,6 @@ static BatchLayout batch_layout(int max_slots, int64_t cap_atom, int64_t cap_cel
   L.off_tab = take(sizeof(Table));
   L.off_atom = take((size_t)cap_atom * sizeof(int2));
   L.off_cell = take((size_t)cap_cell * sizeof(int2));
-  L.off_cell_all = take((size_t)cap_cell * sizeof(int2));
   L.off_chunk = take((size_t)cap_chunk * sizeof(int2));
   L.off_sys = take((size_t)max_slots * 4);
   L.off_state = take((size_t)max_slots * 4);
@@ -1441,13 +1434,12 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
   t.max_slots = B->max_slots;
   std::memset(B->n_atom, 0, sizeof(B->n_atom));
   std::memset(B->n_cell, 0, sizeof(B->n_cell));
-  std::memset(B->n_nowrap, 0, sizeof(B->n_nowrap));
   B->has_fire = B->has_md = false;
   for (int d = 0; d <= kMaxD; d++) {
     B->has_wrap[d] = B->has_nowrap[d] = B->mix[d] = B->has_half[d] = false;
     B->kinds_md[d] = B->kinds_fire[d] = 0;
   }
-  int64_t atom_base = 0, cell_base = 0;
+  int64_t atom_base = 0, cell_base = 0, cells = 0;
   int64_t a_off[kMaxD + 1], c_off[kMaxD + 1];
   for (int d = kMinD; d <= kMaxD; d++) {
     a_off[d] = atom_base;
@@ -1463,16 +1455,19 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
       if (S.mode == MODE_MD) B->kinds_md[d] |= kind;
       else B->kinds_fire[d] |= kind;
     }
-    // cell tiles: systems built by linked subcells first, then those of the circle form
-    for (int pass = 0; pass < 2; pass++) {
-      for (int s = 0; s < B->max_slots; s++) {
-        const SlotInfo& S = B->slots[s];
-        if (!S.used || S.p.d != d || (int)S.p.wrap != pass) continue;
-        for (int k = 0; k < S.p.ncells; k++) cell.push_back(make_int2(s, k));
-        B->n_cell[d] += S.p.ncells;
-        if (pass == 0) B->n_nowrap[d] += S.p.ncells, B->has_nowrap[d] = true;
-        else B->has_wrap[d] = true;
+    // cell tiles: the systems built by linked subcells (the circle form goes by
+    // atom tiles)
+    for (int s = 0; s < B->max_slots; s++) {
+      const SlotInfo& S = B->slots[s];
+      if (!S.used || S.p.d != d) continue;
+      cells += S.p.ncells;
+      if (S.p.wrap) {
+        B->has_wrap[d] = true;
+        continue;
       }
+      for (int k = 0; k < S.p.ncells; k++) cell.push_back(make_int2(s, k));
+      B->n_cell[d] += S.p.ncells;
+      B->has_nowrap[d] = true;
     }
     atom_base += B->n_atom[d];
     cell_base += B->n_cell[d];
@@ -1486,7 +1481,7 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
     if (S.mode == MODE_FIRE) B->has_fire = true;
     if (S.mode == MODE_MD) B->has_md = true;
   }
-  if ((int64_t)atom.size() > B->cap_atom || (int64_t)cell.size() > B->cap_cell ||
+  if ((int64_t)atom.size() > B->cap_atom || cells > B->cap_cell ||
       (int64_t)chunk.size() > B->cap_chunk)
     return fail(HDMD_ERR_WORKSPACE, "batch table capacity exceeded (max_atoms / max_cells)");
   B->n_chunk = (int)chunk.size();
@@ -1494,28 +1489,13 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
   for (int d = kMinD; d <= kMaxD; d++) {
     t.n_atom[d] = B->n_atom[d];
     t.n_cell[d] = B->n_cell[d];
-    t.n_cell_nowrap[d] = B->n_nowrap[d];
     t.atom_tiles[d] = B->d_atom + a_off[d];
     t.cell_tiles[d] = B->d_cell + c_off[d];
   }
   t.n_atom[0] = (int32_t)atom_base;  // class 0: every class
-  // class 0 lists its cell tiles in an array of its own, the linked
-  // subcells of every class before the others (the list build of a batch
-  // goes over the former only; it takes the circle form by atom tiles)
-  std::vector<int2> cell_all;
-  cell_all.reserve(cell.size());
-  for (int pass = 0; pass < 2; pass++)
-    for (int d = kMinD; d <= kMaxD; d++) {
-      const int64_t lo = c_off[d] + (pass ? B->n_nowrap[d] : 0);
-      const int64_t hi = c_off[d] + (pass ? B->n_cell[d] : B->n_nowrap[d]);
-      cell_all.insert(cell_all.end(), cell.begin() + lo, cell.begin() + hi);
-    }
-  B->n_nowrap_all = 0;
-  for (int d = kMinD; d <= kMaxD; d++) B->n_nowrap_all += B->n_nowrap[d];
   t.n_cell[0] = (int32_t)cell_base;
-  t.n_cell_nowrap[0] = B->n_nowrap_all;
   t.atom_tiles[0] = B->d_atom;
-  t.cell_tiles[0] = B->d_cell_all;
+  t.cell_tiles[0] = B->d_cell;
   B->n_atom_all = (int)atom_base;
   B->n_cell_all = (int)cell_base;
   t.n_chunk = B->n_chunk;
@@ -1524,8 +1504,6 @@ static int upload_tables(HostBatch* B, hipStream_t st) {
   t.sys_list = B->d_syslist;
   if (!atom.empty()) HIPCHK(hipMemcpyAsync(B->d_atom, atom.data(), atom.size() * sizeof(int2), hipMemcpyHostToDevice, st));
   if (!cell.empty()) HIPCHK(hipMemcpyAsync(B->d_cell, cell.data(), cell.size() * sizeof(int2), hipMemcpyHostToDevice, st));
-  if (!cell_all.empty())
-    HIPCHK(hipMemcpyAsync(B->d_cell_all, cell_all.data(), cell_all.size() * sizeof(int2), hipMemcpyHostToDevice, st));
   if (!chunk.empty()) HIPCHK(hipMemcpyAsync(B->d_chunk, chunk.data(), chunk.size() * sizeof(int2), hipMemcpyHostToDevice, st));
   if (!sys.empty()) HIPCHK(hipMemcpyAsync(B->d_syslist, sys.data(), sys.size() * 4, hipMemcpyHostToDevice, st));
   HIPCHK(hipMemcpyAsync(B->dtab, &t, sizeof(Table), hipMemcpyHostToDevice, st));
@@ -1540,12 +1518,11 @@ static inline int pow2_grid(int n, int cap) {
   return g;
 }
 
-static KArgs batch_args(HostBatch* B, int d, int part = 0) {
+static KArgs batch_args(HostBatch* B, int d) {
   KArgs a;
   a.single = nullptr;
   a.tab = B->dtab;
   a.cls = d;
-  a.part = part;
   a.fin = 0;
   return a;
 }
@@ -1578,10 +1555,10 @@ static void enqueue_batch_iter(HostBatch* B, const std::vector<int>& grids, hipS
   auto class_builds = [&](int d) {
     const DKernels* K = dkernels(d);
     if (B->has_nowrap[d]) {
-      K->build(1, BUILD_SPARSE, 1, batch_args(B, d, 1), gc(d), st);
-      K->build(1, BUILD_DENSE, 1, batch_args(B, d, 1), gc(d), st);
+      K->build(1, BUILD_SPARSE, 1, batch_args(B, d), gc(d), st);
+      K->build(1, BUILD_DENSE, 1, batch_args(B, d), gc(d), st);
     }
-    if (B->has_half[d]) K->build(2, BUILD_DENSE, 1, batch_args(B, d, 1), gc(d), st);
+    if (B->has_half[d]) K->build(2, BUILD_DENSE, 1, batch_args(B, d), gc(d), st);
     if (B->has_wrap[d]) K->build_wrap(kTile, batch_args(B, d), ga(d), st);
   };
   if (gb_all > 0) {
@@ -1636,7 +1613,6 @@ int hdmd_batch_init(void* table_ws, size_t table_bytes, int32_t max_slots, int64
   B->dtab = at<Table>(table_ws, L.off_tab);
   B->d_atom = at<int2>(table_ws, L.off_atom);
   B->d_cell = at<int2>(table_ws, L.off_cell);
-  B->d_cell_all = at<int2>(table_ws, L.off_cell_all);
   B->d_chunk = at<int2>(table_ws, L.off_chunk);
   B->d_syslist = at<int32_t>(table_ws, L.off_sys);
   B->d_state = at<int32_t>(table_ws, L.off_state);
@@ -1699,7 +1675,6 @@ static int batch_add(void* table_ws, int32_t slot, const hdmd_system* sys, const
   S_.dev = dev;
   S_.ws = ws;
   S_.mode = fp ? MODE_FIRE : MODE_MD;
-  S_.blk = blk;
   B->dirty = true;
   return HDMD_OK;
 }
@@ -1745,7 +1720,7 @@ int hdmd_batch_run(void* table_ws, int32_t iterations, void* stream) {
   // one list-build launch over every class (0: one launch per class and variant)
   grids.push_back(std::getenv("HDMD_BUILD_PER_CLASS")
                       ? 0
-                      : pow2_grid((B->n_nowrap_all + 3) / 4 + (B->n_atom_all + 3) / 4, 8192));
+                      : pow2_grid((B->n_cell_all + 3) / 4 + (B->n_atom_all + 3) / 4, 8192));
   grids.push_back(iterations);
   if (!graphs_enabled()) {
     for (int k = 0; k < iterations; k++) enqueue_batch_iter(B, grids, st);
