@@ -159,8 +159,8 @@ int hdmd_cells_per_axis(const hdmd_system* sys);
  * *reach 1 (subcells of side >= r_l,max, 3^d stencil) or 2 (half-size
  * subcells, 5^d stencil), *cells_per_axis of that grid, and *variant 1, 2 or
  * 4: waves sharing a subcell (circle form: 1).  Every variant builds the same
- * lists, and the environment variable HDMD_BUILD_BLK forces one (reported as given;
- * other values take the nearest of 1, 2 and 4).  Forces (Sec. II.B
+ * lists, and the environment variable HDMD_BUILD_BLK forces one (other values
+ * take the nearest of 1, 2 and 4).  Forces (Sec. II.B
  * getforce): *lanes_per_atom 1, 2 or 4 lanes sharing an atom's row; the
  * autotuner times them on the first list built for each (d, precision form,
  * expected row length n V_d(r_l,max) / L^d in half-octaves), and every later system with

@@ -379,11 +379,12 @@ static int tuned_reach(int d, int wrap, int occ) {
   return it == g_tune.end() ? 0 : it->second.reach;
 }
 
+// the variant HDMD_BUILD_BLK forces, of those there are (the circle form has
+// one), or 1
 static int default_blk(const Plan& p) {
   const char* e = std::getenv("HDMD_BUILD_BLK");
-  if (e) return std::atoi(e);
-  (void)p;
-  return 1;
+  const int v = e && !p.wrap ? std::atoi(e) : 1;
+  return v <= 1 ? 1 : (v == 2 ? 2 : 4);
 }
 
 static int lookup_blk(const Plan& p, bool* known) {
