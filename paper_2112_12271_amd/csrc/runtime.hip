@@ -63,6 +63,9 @@ static SwapScratch swap_scratch(void* base) {
 // ---------------------------------------------------------------------------
 // geometry and workspace plan
 // ---------------------------------------------------------------------------
+// (d, precision form, expected row length, size)
+typedef std::tuple<int, int, int, int> LanesKey;
+
 struct Plan {
   int d = 0, dr = 0, dq = 0;
   int n = 0, npad = 0, ncell = 0, ncells = 0, nchunks = 0;
@@ -77,7 +80,8 @@ struct Plan {
   // taken from the grid of side >= r_l,max; nh_auto: half-size subcells per
   // axis the autotuner may take (0: none)
   int reach = 1, key_wrap = 0, key_occ = 0, nh_auto = 0;
-  int lpa = 1, row_key = 0;  // lanes per atom of the force kernels and their key
+  int lpa = 1;        // lanes per atom of the force kernels
+  LanesKey lanes_key;  // and their key
   double rlmax = 0;
   size_t off_desc = 0, off_x[2] = {0, 0}, off_q[2] = {0, 0}, off_v[2] = {0, 0},
          off_oid[2] = {0, 0}, off_f = 0, off_xref = 0, off_disp[2] = {0, 0}, off_qc16 = 0, off_ends = 0,
@@ -158,17 +162,22 @@ static bool circle_form(int d, int64_t n, int reach, int ncell) {
 
 // the autotuner's grid for a key: 0 (not tuned yet), 1 or 2 (reach)
 static int tuned_reach(int d, int wrap, int occ);
-// lanes per atom of the force kernels for a system (the autotuner's, or 1),
-// keyed by the row-length bucket
-static int lanes_for(const hdmd_system* s, int d, int rowkey);
+// lanes per atom of the force kernels for a system (the autotuner's, or 1)
+static int lanes_for(const hdmd_system* s, const LanesKey& key);
 
 // The force kernels' key: half-octaves of the expected row length, the atoms
 // in a ball of the largest list radius at the mean number density, n V_d(r)
-// / L^d (rows, not the subcell occupancy, decide how many lanes pay).
-static int row_bucket(const hdmd_system& s, double rlmax) {
+// / L^d, and octaves of n: long rows pay for more lanes while the waves of one
+// lane per atom leave SIMDs without work (MD step loops with 1, 2 and 4 lanes,
+// us per step: d = 6, rows of 75, N = 30000 134, 121, 118, N = 262144 645,
+// 733, 770; d = 4, rows of 33, N = 65536 89, 85, 86, N = 200000 263, 312,
+// 332).
+static LanesKey lanes_key(const hdmd_system& s, double rlmax) {
   const double vd = std::pow(M_PI, 0.5 * s.d) / std::tgamma(0.5 * s.d + 1.0) * std::pow(rlmax, s.d);
   const double rows = (double)s.n * vd / std::pow(s.box_l, s.d);
-  return (int)std::lround(2.0 * std::log2(std::max(rows, 1.0)));
+  return LanesKey(s.d, s.precision == HDMD_MIXED ? 1 : 0,
+                  (int)std::lround(2.0 * std::log2(std::max(rows, 1.0))),
+                  (int)std::floor(std::log2((double)s.n)));
 }
 
 static int make_plan(const hdmd_system* s, Plan& p) {
@@ -236,8 +245,8 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   p.width = s->max_neighbors;
   p.wrap = circle_form(p.d, p.n, p.reach, p.ncell);
   p.mix = s->precision == HDMD_MIXED;
-  p.row_key = row_bucket(*s, p.rlmax);
-  p.lpa = lanes_for(s, p.d, p.row_key);
+  p.lanes_key = lanes_key(*s, p.rlmax);
+  p.lpa = lanes_for(s, p.lanes_key);
   p.morse = s->potential == HDMD_MORSE;
   const size_t np = (size_t)p.npad, vsz = p.mix ? 4 : 8;
   size_t o = 0;
@@ -365,8 +374,8 @@ struct Tuned {
 };
 static std::mutex g_tune_mu;
 static std::map<std::tuple<int, int, int>, Tuned> g_tune;
-// lanes per atom of the force kernels per (d, precision form, row bucket)
-static std::map<std::tuple<int, int, int>, int> g_lanes;
+// lanes per atom of the force kernels
+static std::map<LanesKey, int> g_lanes;
 
 static bool tuning_enabled() {
   const char* e = std::getenv("HDMD_AUTOTUNE");
@@ -406,9 +415,8 @@ static int lookup_blk(const Plan& p, bool* known) {
 
 // Lanes per atom of the force kernels (1, 2 or 4 lanes share an atom's row;
 // their partial sums meet in a tree that depends on the count, so the choice
-// fixes the rounding of the forces): chosen by the autotuner per (d,
-// precision form, row bucket) and kept for every later system with that key,
-// alone or in a batch.  Morse systems take one lane.  HDMD_LPA overrides.
+// fixes the rounding of the forces): chosen by the autotuner per lanes_key and
+// kept for every later system with that key, alone or in a batch.  Morse systems take one lane.  HDMD_LPA overrides.
 static int lpa_env() {
   const char* e = std::getenv("HDMD_LPA");
   if (!e) return 0;
@@ -421,12 +429,12 @@ static int lpa_env() {
 // its own per class, on every iteration.
 constexpr int64_t kLanesMinAtoms = 16384;
 
-static int lanes_for(const hdmd_system* s, int d, int rowkey) {
+static int lanes_for(const hdmd_system* s, const LanesKey& key) {
   if (s->potential == HDMD_MORSE) return 1;
   if (const int e = lpa_env()) return e;
   if (s->n < kLanesMinAtoms) return 1;
   std::lock_guard<std::mutex> g(g_tune_mu);
-  auto it = g_lanes.find({d, s->precision == HDMD_MIXED ? 1 : 0, rowkey});
+  auto it = g_lanes.find(key);
   return it == g_lanes.end() ? 1 : it->second;
 }
 
@@ -649,11 +657,10 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
     blk = lookup_blk(p, &known);
   }
   // whether the lanes of the force kernels are yet to be timed for the key
-  const int mix = p.mix ? 1 : 0;
   bool time_lanes = !p.morse && !lpa_env() && p.n >= kLanesMinAtoms && tuning_enabled() && allow_tune;
   if (time_lanes) {
     std::lock_guard<std::mutex> g(g_tune_mu);
-    time_lanes = g_lanes.count({p.d, mix, p.row_key}) == 0;
+    time_lanes = g_lanes.count(p.lanes_key) == 0;
   }
   if (time_lanes) p.shells = true;
   load_system(sys, p, pos, diam, vel, ws, st);
@@ -669,11 +676,17 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
     const int rc = read_desc(dev, &h, st);
     if (rc) return rc;
     if (h.err == 0 && h.status == SLOT_RUNNING) {
-      // the force kernel with 1, 2 and 4 lanes per atom on the list just built;
-      // more lanes only where one lane takes at least 12 us and they save 10 %
-      // (d = 4, N = 65536: 16.5 and 11.7 us, an MD step 30 and 25 us)
-      // (below that, launch overheads and the batches' one all-class launch
-      // for one-lane systems count for more)
+      // the step kernel with 1, 2 and 4 lanes per atom on the list just built,
+      // as the closing step of a run of none (no kick, no drift: the positions
+      // and velocities stay); more lanes only where one lane takes at least 12
+      // us and they save 10 % (below that, launch overheads and the batches'
+      // one all-class launch for one-lane systems count for more).  The step
+      // kernel, not the force kernel: its loads and stores per atom go by one
+      // lane in two or four.  Timed here with 1, 2 and 4 lanes, and the runs
+      // that follow, us per step: d = 4, N = 65536 18.8, 14.5, 17.6 and 166,
+      // 160, 162; N = 200000 35.0, 34.4, 46.4 and 251, 296, 315 (the force
+      // kernel gains 10 % from two lanes there); d = 8, N = 60000 67.8, 33.8,
+      // 39.3 and 249, 214, 237.
       hipEvent_t e0, e1;
       HIPCHK(hipEventCreate(&e0));
       HIPCHK(hipEventCreate(&e1));
@@ -683,15 +696,20 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
       int best_lpa = 1;
       // on the rows that a run walks half-way between two builds
       set_i32(dev, offsetof(SysDev, shells), kShells / 2, st);
+      set_i32(dev, offsetof(SysDev, mode), MODE_MD, st);
       for (int cand : {1, 2, 4}) {
         set_i32(dev, offsetof(SysDev, lpa), cand, st);
-        K->force(p.mix, cand, p.morse, a, p.ntiles, 0, st);  // warm-up
-        HIPCHK(hipEventRecord(e0, st));
-        K->force(p.mix, cand, p.morse, a, p.ntiles, 0, st);
-        HIPCHK(hipEventRecord(e1, st));
-        HIPCHK(hipEventSynchronize(e1));
-        float ms = 0;
-        HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+        K->step(p.mix, cand, p.morse, a, p.ntiles, st);  // warm-up
+        float ms = 1e30f;
+        for (int rep = 0; rep < 3; rep++) {  // the fastest: a hiccup decides nothing
+          HIPCHK(hipEventRecord(e0, st));
+          K->step(p.mix, cand, p.morse, a, p.ntiles, st);
+          HIPCHK(hipEventRecord(e1, st));
+          HIPCHK(hipEventSynchronize(e1));
+          float t = 0;
+          HIPCHK(hipEventElapsedTime(&t, e0, e1));
+          ms = std::min(ms, t);
+        }
         if (cand == 1) one = ms;
         if (ms < best) {
           best = ms;
@@ -703,10 +721,11 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
       if (one < 0.012f || best > 0.9f * one) best_lpa = 1;
       {
         std::lock_guard<std::mutex> g(g_tune_mu);
-        p.lpa = g_lanes.emplace(std::make_tuple(p.d, mix, p.row_key), best_lpa).first->second;
+        p.lpa = g_lanes.emplace(p.lanes_key, best_lpa).first->second;
       }
       set_i32(dev, offsetof(SysDev, lpa), p.lpa, st);
       set_i32(dev, offsetof(SysDev, shells), 1, st);
+      set_i32(dev, offsetof(SysDev, mode), MODE_STATIC, st);
     }
   }
   if (blk_out) *blk_out = blk;

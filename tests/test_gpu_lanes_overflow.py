@@ -1,6 +1,6 @@
 """The lanes per atom of the force kernels are chosen on a list that holds: a
 first build whose rows overflow (the usual way to a row width) leaves the
-choice to the next."""
+choice to the next; and on a list of about the system's own size."""
 import dataclasses
 
 import pytest
@@ -29,3 +29,23 @@ def test_an_overflowed_build_does_not_settle_the_lanes(prec):
     rc, _ = H.hdmd_build_nlist(s, x, sig, H.workspace(s))
     assert rc == H.HDMD_OK
     assert H.hdmd_build_config(s)[4] > 1
+
+
+def test_the_lanes_of_one_size_do_not_bind_another():
+    """Rows of the same length in a system eight times as large fill the SIMDs
+    with one lane per atom: its lanes are its own to time."""
+    rl = 1.6
+
+    def make(n):
+        L = (n * 3.14159 * rl * rl / 250.0) ** 0.5
+        x, sig = dev(inputs.uniform_positions(n, 2, L, 7)), dev(inputs.bidisperse(n, 1.0, 1.2, 8))
+        return H.System(d=2, n=n, box_l=L, potential=H.HDMD_HARMONIC, cutoff=1.0, skin=0.4, sigma_max=1.2,
+                        max_neighbors=400), x, sig
+
+    small, x, sig = make(18000)
+    assert H.hdmd_build_nlist(small, x, sig, H.workspace(small))[0] == H.HDMD_OK
+    assert H.hdmd_build_config(small)[4] > 1
+    large, x, sig = make(144000)
+    assert H.hdmd_build_config(large)[4] == 1
+    assert H.hdmd_build_nlist(large, x, sig, H.workspace(large))[0] == H.HDMD_OK
+    assert H.hdmd_build_config(large)[4] in (1, 2, 4)
