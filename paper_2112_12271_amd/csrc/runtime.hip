@@ -678,11 +678,13 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
     if (h.err == 0 && h.status == SLOT_RUNNING) {
       // the step kernel with 1, 2 and 4 lanes per atom on the list just built,
       // as the closing step of a run of none (no kick, no drift: the positions
-      // and velocities stay); more lanes only where one lane takes at least 12
+      // and velocities stay).  More lanes only where one lane takes at least 12
       // us and they save 10 % (below that, launch overheads and the batches'
-      // one all-class launch for one-lane systems count for more).  The step
-      // kernel, not the force kernel: its loads and stores per atom go by one
-      // lane in two or four.  Timed here with 1, 2 and 4 lanes, and the runs
+      // one all-class launch for one-lane systems count for more), four only
+      // where they save 15 % of two (a batch has waves enough: four systems of
+      // d = 6, N = 20000 take 35.9, 34.9 and 36.9 ms with 1, 2 and 4).  The
+      // step kernel, not the force kernel: its loads and stores per atom go by
+      // one lane in two or four.  Timed here with 1, 2 and 4 lanes, and the runs
       // that follow, us per step: d = 4, N = 65536 18.8, 14.5, 17.6 and 166,
       // 160, 162; N = 200000 35.0, 34.4, 46.4 and 251, 296, 315 (the force
       // kernel gains 10 % from two lanes there); d = 8, N = 60000 67.8, 33.8,
@@ -692,36 +694,33 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
       HIPCHK(hipEventCreate(&e1));
       const DKernels* K = dkernels(p.d);
       KArgs a = single_args(dev, p.d);
-      float best = 1e30f, one = 0.f;
-      int best_lpa = 1;
+      float t[3] = {1e30f, 1e30f, 1e30f};
       // on the rows that a run walks half-way between two builds
       set_i32(dev, offsetof(SysDev, shells), kShells / 2, st);
       set_i32(dev, offsetof(SysDev, mode), MODE_MD, st);
-      for (int cand : {1, 2, 4}) {
-        set_i32(dev, offsetof(SysDev, lpa), cand, st);
-        K->step(p.mix, cand, p.morse, a, p.ntiles, st);  // warm-up
-        float ms = 1e30f;
+      for (int k = 0; k < 3; k++) {
+        set_i32(dev, offsetof(SysDev, lpa), 1 << k, st);
+        K->step(p.mix, 1 << k, p.morse, a, p.ntiles, st);  // warm-up
         for (int rep = 0; rep < 3; rep++) {  // the fastest: a hiccup decides nothing
           HIPCHK(hipEventRecord(e0, st));
-          K->step(p.mix, cand, p.morse, a, p.ntiles, st);
+          K->step(p.mix, 1 << k, p.morse, a, p.ntiles, st);
           HIPCHK(hipEventRecord(e1, st));
           HIPCHK(hipEventSynchronize(e1));
-          float t = 0;
-          HIPCHK(hipEventElapsedTime(&t, e0, e1));
-          ms = std::min(ms, t);
+          float ms = 0;
+          HIPCHK(hipEventElapsedTime(&ms, e0, e1));
+          t[k] = std::min(t[k], ms);
         }
-        if (cand == 1) one = ms;
-        if (ms < best) {
-          best = ms;
-          best_lpa = cand;
-        }
+      }
+      int lpa = 1;
+      if (t[0] >= 0.012f) {
+        if (t[1] <= 0.9f * t[0]) lpa = 2;
+        if (t[2] <= 0.9f * t[0] && (lpa == 1 || t[2] <= 0.85f * t[1])) lpa = 4;
       }
       HIPCHK(hipEventDestroy(e0));
       HIPCHK(hipEventDestroy(e1));
-      if (one < 0.012f || best > 0.9f * one) best_lpa = 1;
       {
         std::lock_guard<std::mutex> g(g_tune_mu);
-        p.lpa = g_lanes.emplace(p.lanes_key, best_lpa).first->second;
+        p.lpa = g_lanes.emplace(p.lanes_key, lpa).first->second;
       }
       set_i32(dev, offsetof(SysDev, lpa), p.lpa, st);
       set_i32(dev, offsetof(SysDev, shells), 1, st);
