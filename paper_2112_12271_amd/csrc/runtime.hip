@@ -657,10 +657,13 @@ static int init_system(const hdmd_system* sys, Plan& p, const double* pos,
     blk = lookup_blk(p, &known);
   }
   // whether the lanes of the force kernels are yet to be timed for the key
+  // (another thread may have settled them since the plan was made)
   bool time_lanes = !p.morse && !lpa_env() && p.n >= kLanesMinAtoms && tuning_enabled() && allow_tune;
   if (time_lanes) {
     std::lock_guard<std::mutex> g(g_tune_mu);
-    time_lanes = g_lanes.count(p.lanes_key) == 0;
+    auto it = g_lanes.find(p.lanes_key);
+    time_lanes = it == g_lanes.end();
+    if (!time_lanes) p.lpa = it->second;
   }
   if (time_lanes) p.shells = true;
   load_system(sys, p, pos, diam, vel, ws, st);
