@@ -92,9 +92,9 @@ def kernel_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def committed_traffic(name: str):
-    """HBM bytes per launch from a committed rocprofv3 counter summary, if it
-    was taken on the current kernel source; otherwise None."""
+def committed_counter(name: str, key: str = "bytes_per_launch"):
+    """A figure of a committed rocprofv3 counter summary (HBM bytes per launch),
+    if it was taken on the current kernel source; otherwise None."""
     p = os.path.join(ROOT, "profiles", name)
     if not os.path.exists(p):
         return None
@@ -104,7 +104,7 @@ def committed_traffic(name: str):
         return None
     if d.get("kernel_hash") != kernel_hash():
         return None
-    return d.get("bytes_per_launch")
+    return d.get(key)
 
 
 def drift(th: np.ndarray, n: int, dt: float) -> tuple[float, float]:
@@ -593,27 +593,25 @@ def main():
     if "step_kernel_ms" in f:
         roof = {"bound": "hbm", "achieved": f["step_kernel_gbs"], "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": f["step_kernel_gbs"] / HBM_PEAK_GBS,
-                "traffic": committed_traffic("step_kernel_c3_traffic.json"),
+                "traffic": committed_counter("step_kernel_c3_traffic.json"),
                 "kernel": "k_step<6,fp64>", "bytes_per_launch": cfg.n * f["step_bytes_per_atom"],
                 "launch_ms": f["step_kernel_ms"]}
-    # the list build as a candidate rate against the vector ALU peak: every
-    # candidate pair of the subcell stencil (Sec. II.C) is priced at the
-    # vector prefilter's cost, ceil(d/2) packed int16 dot products and a
-    # compare, one VALU lane-operation each; the peak is 256 CUs x 4 SIMDs x
-    # 16 lanes x 2.4 GHz lane-operations per second.  (Row culling skips most
-    # candidates before any test, and the tests it does make run as f16
-    # matrix products, so this is a rate, not the kernel's own
-    # VALU use.)
+    # the list build against the vector ALU peak: the kernel's own vector
+    # instructions per build (committed counters of this kernel source, d = 6
+    # N = 262144 only; otherwise None), 64 lane-operations each, over its
+    # launch; the peak is 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane-operations
+    # per second.  candidates_per_s: candidate pairs of the subcell stencil
+    # (Sec. II.C) per second, most of them skipped by row culling
     roof_build = None
     if f.get("build_ms") and f.get("build_candidates"):
-        ops = (cfg.d + 1) // 2 + 1
-        ach = f["build_candidates"] * ops / (f["build_ms"] * 1e-3)
+        insts = committed_counter("build_kernel_c3_valu.json", "valu_insts_per_build") if cfg.n == 262144 else None
+        ach = insts * 64 / (f["build_ms"] * 1e-3) if insts else None
         roof_build = {"bound": "alu", "achieved": ach, "peak": VALU_LANE_OPS_PEAK,
-                      "unit": "lane-op/s", "frac": ach / VALU_LANE_OPS_PEAK,
+                      "unit": "lane-op/s", "frac": ach / VALU_LANE_OPS_PEAK if ach else None,
                       "kernel": build_kernel_name(cfg.d, f.get("build_variant", 1)),
                       "candidates_per_build": f["build_candidates"],
                       "candidates_per_s": f["build_candidates"] / (f["build_ms"] * 1e-3),
-                      "launch_ms": f["build_ms"], "lane_ops_per_candidate": ops}
+                      "launch_ms": f["build_ms"]}
     cpu = None
     if not args.no_cpu_baseline and not args.no_md:
         spb = f.get("long_run", f)["steps_per_build"]

@@ -759,8 +759,9 @@ __global__ __launch_bounds__(256) void k_place(KArgs a) {
 // as ready operands and word-wise listing replaced per-row conversions,
 // operand transposes and a listing walk per home atom (4.4e8 instead of
 // 9.3e8 vector instructions per build): d = 6, N = 262144, 64 atoms per
-// subcell: 2.14 -> 1.30 ms; d = 6, N = 1e5, 24 per subcell: 1.03 -> 0.70;
-// d = 4, N = 65536, 6.6 per subcell (sparse form): 0.43 -> 0.16 ms.
+// subcell: 2.14 -> 1.30 ms.  With the rows ordered by shell (below): 1.50; d =
+// 6, N = 1e5, 24 per subcell: 1.03 -> 0.56; d = 4, N = 65536, 6.6 per subcell
+// (sparse form): 0.43 -> 0.17 ms.
 //
 // Systems of n_cell <= 2, where several images of a pair can be in reach
 // along an axis, and small systems take k_build_wrap below.
@@ -958,7 +959,7 @@ __device__ __forceinline__ void shell_order(P s, int i0, int cnt, int mylen, int
   mylen = lane < cnt ? min(mylen, s->width) : 0;
   const int mx = __builtin_amdgcn_readfirstlane(wave_max_i(mylen));
   if (mx > kShellRow) {
-    const int l2 = mylen * 0x10001;
+    const int l2 = (int)((unsigned)mylen * 0x10001u);  // (a row may have 65535 entries)
     if (lane < cnt) ends[lane] = vi4{l2, l2, l2, l2};
     return;
   }
@@ -1533,12 +1534,13 @@ __global__ __launch_bounds__(64 * G, 4) void k_build_mf(KArgs a) {
 // (The chord test keeps about twice the pairs of the list in d = 8; it takes
 // no row cull, no shifts and no wrapped differences.)  2 d + 2 <= 16 (d <=
 // 7): records of 16 slots and 16x16x16 products; above: 24 slots, 16x16x32.
-// A wave takes 16 HB home atoms (HB = 4: a tile) as HB blocks of columns held
-// in registers and streams all atoms past them, 128 at a time: for a tile 32
+// A wave takes up to 16 HB home atoms (HB = 4: a tile; HB = 1: 16 or, in lone
+// systems of few or long rows, 4) as HB blocks of columns held in registers
+// and streams all atoms past them, 128 at a time: for a tile 32
 // matrix instructions and 128 sign-bit shifts per 8192 pair tests, and the
 // exact tests of the survivors.  The survivors of a row come in the order of
 // the candidates whatever HB is, so every HB gives the same rows.
-// d = 8, N = 131072 (mean row 200): 2.5 ms, where packed int16 tests of the
+// d = 8, N = 131072 (mean row 200): 2.4 ms, where packed int16 tests of the
 // 45 % of the pairs that a row cull left took 7.6.
 // ---------------------------------------------------------------------------
 struct WrapLds {

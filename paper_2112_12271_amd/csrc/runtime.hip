@@ -149,9 +149,12 @@ static int occ_bucket(int64_t n, int64_t ncells) {
 // candidates, which come in memory order and are fetched ahead.  Measured in
 // a batch of 24 minimisations (d 3 to 6, 256 to 8192 atoms, whole run): no
 // small system 53.7 ms, n <= 32 * 3^d or 64 * 3^d 48.5, 128 * 3^d 40.9, all
-// n <= 8192 42.6 (d = 3, N = 8192 alone: 10.9 ms by linked subcells, 11.5 by
-// all atoms).  d >= 8 keeps the linked subcells: its circle records are
-// longer.  HDMD_CIRCLE=0 leaves the form to n_cell <= 2.
+// n <= 8192 42.6.  Alone, 100 MD steps by all atoms and by linked subcells: d =
+// 3, N = 1000 2.30 and 2.35 ms, N = 3400 2.57 and 2.56; d = 4, N = 1000 2.83
+// and 3.16, N = 8192 3.79 and 3.57 (the one case where it loses); d = 5, N =
+// 8192 4.36 and 5.06; d = 6, N = 8192 4.84 and 8.57.  d >= 8 keeps the linked
+// subcells: its circle records are longer.  HDMD_CIRCLE=0 leaves the form to
+// n_cell <= 2.
 constexpr int64_t kCircleAtoms = 8192;
 static bool circle_form(int d, int64_t n, int reach, int ncell) {
   if (reach != 1) return false;
@@ -424,9 +427,12 @@ static int lpa_env() {
   return v >= 4 ? 4 : (v >= 2 ? 2 : 1);
 }
 
-// Systems below this size take one lane per atom without timing: their force
-// kernels are short, and in a batch every other lane count costs a launch of
-// its own per class, on every iteration.
+// Systems below this size take one lane per atom without timing: in a batch
+// every other lane count costs a launch of its own per class, on every
+// iteration (24 uneven FIRE requests, 256 to 8192 atoms: 41.4, 46.1 and 44.5 ms
+// with 1, 2 and 4 lanes), and a system takes the same count in a batch as
+// alone, where two or four would pay (100 MD steps, 1, 2 and 4 lanes: d = 3, N
+// = 1000 2.30, 2.04, 2.01 ms; d = 6, N = 8192 4.84, 4.03, 3.73).
 constexpr int64_t kLanesMinAtoms = 16384;
 
 static int lanes_for(const hdmd_system* s, const LanesKey& key) {
@@ -1198,7 +1204,7 @@ int hdmd_van_hove(const hdmd_system* sys, void* ws, size_t ws_bytes, int32_t nbi
 namespace hdmd {
 
 // SWAP Monte Carlo with its scratch at `scr` (kSwapScratchBytes of device
-// memory): one rounds of a batch each (dE of every attempt, then the
+// memory): rounds of one batch each (dE of every attempt, then the
 // settlement in order), enqueued in runs of as many rounds as the attempts
 // left need at least, the counters read back after each run.
 static int swap_run(const hdmd_system* sys, const double* pos, double* diam, void* ws,
