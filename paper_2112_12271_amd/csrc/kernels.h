@@ -1535,7 +1535,7 @@ __global__ __launch_bounds__(64 * G, 4) void k_build_mf(KArgs a) {
 // no row cull, no shifts and no wrapped differences.)  2 d + 2 <= 16 (d <=
 // 7): records of 16 slots and 16x16x16 products; above: 24 slots, 16x16x32.
 // A wave takes up to 16 HB home atoms (HB = 4: a tile; HB = 1: 16 or, in lone
-// systems of few or long rows, 4) as HB blocks of columns held in registers
+// systems of long rows, 4) as HB blocks of columns held in registers
 // and streams all atoms past them, 128 at a time: for a tile 32
 // matrix instructions and 128 sign-bit shifts per 8192 pair tests, and the
 // exact tests of the survivors.  The survivors of a row come in the order of

@@ -83,6 +83,7 @@ struct Plan {
   int lpa = 1;        // lanes per atom of the force kernels
   LanesKey lanes_key;  // and their key
   double rlmax = 0;
+  double near_part = 0;  // V_d(r_l,max) / L^d: the part of the box within the list radius
   size_t off_desc = 0, off_x[2] = {0, 0}, off_q[2] = {0, 0}, off_v[2] = {0, 0},
          off_oid[2] = {0, 0}, off_f = 0, off_xref = 0, off_disp[2] = {0, 0}, off_qc16 = 0, off_ends = 0,
          off_cell_of = 0,
@@ -175,9 +176,8 @@ static int lanes_for(const hdmd_system* s, const LanesKey& key);
 // us per step: d = 6, rows of 75, N = 30000 134, 121, 118, N = 262144 645,
 // 733, 770; d = 4, rows of 33, N = 65536 89, 85, 86, N = 200000 263, 312,
 // 332).
-static LanesKey lanes_key(const hdmd_system& s, double rlmax) {
-  const double vd = std::pow(M_PI, 0.5 * s.d) / std::tgamma(0.5 * s.d + 1.0) * std::pow(rlmax, s.d);
-  const double rows = (double)s.n * vd / std::pow(s.box_l, s.d);
+static LanesKey lanes_key(const hdmd_system& s, double near_part) {
+  const double rows = (double)s.n * near_part;
   return LanesKey(s.d, s.precision == HDMD_MIXED ? 1 : 0,
                   (int)std::lround(2.0 * std::log2(std::max(rows, 1.0))),
                   (int)std::floor(std::log2((double)s.n)));
@@ -248,7 +248,9 @@ static int make_plan(const hdmd_system* s, Plan& p) {
   p.width = s->max_neighbors;
   p.wrap = circle_form(p.d, p.n, p.reach, p.ncell);
   p.mix = s->precision == HDMD_MIXED;
-  p.lanes_key = lanes_key(*s, p.rlmax);
+  p.near_part = std::pow(M_PI, 0.5 * s->d) / std::tgamma(0.5 * s->d + 1.0) * std::pow(p.rlmax, s->d) /
+                std::pow(s->box_l, s->d);
+  p.lanes_key = lanes_key(*s, p.near_part);
   p.lpa = lanes_for(s, p.lanes_key);
   p.morse = s->potential == HDMD_MORSE;
   const size_t np = (size_t)p.npad, vsz = p.mix ? 4 : 8;
@@ -484,16 +486,18 @@ static void chain_sort(const Plan& p, SysDev* dev, hipStream_t st, int fin) {
 
 // Home atoms per wave of a lone system's circle form (the rows do not depend on
 // it): a tile, or a quarter of one while those are all at work at once, four
-// waves per SIMD (d = 6, N = 8192: 155 us by tiles, 53 by quarters).  A wave's
-// time is then its survivors', one exact test after the other: where rows are
-// long (n_cell <= 2: each atom lists much of the box) or the waves few, a wave
-// takes four home atoms.  hdmd_build_nlist by quarters and by fours: n_cell =
-// 2, d = 3, N = 1000 291 and 147 us, N = 6000 1428 and 546, d = 6, N = 8192
-// 469 and 270; past that the repeated products count (d = 8, N = 16000 352
-// and 357).  n_cell >= 3, d = 7, N = 1000 155 and 133, d = 3, N = 1000 99 and
-// 98, N = 3456 113 and 121.
+// waves per SIMD (d = 6, N = 8192: 155 us by tiles, 53 by quarters).  A wave
+// tests n candidates per home block and then its survivors, one batch after
+// the other: where an atom lists a large part of the box, the survivors are
+// most of its time, and four home atoms per wave pay for testing with a quarter
+// of the columns.  They do from one eightieth of the box within the list
+// radius on (hdmd_build_nlist by quarters and by fours, us: fraction 0.49, d =
+// 3, N = 6000 1427 and 545; 0.072, d = 6, N = 8192 469 and 270; 0.022, d = 6, N
+// = 2000 118 and 111; 0.0126, d = 6, N = 3456 125 and 125; 0.0087, N = 5000 135
+// and 142; 0.003, d = 3, N = 3456 113 and 121); past 8192 atoms the waves are
+// many either way (0.0135, d = 8, N = 8192 225 and 189, N = 16000 352 and 357).
 static int circle_homes(const Plan& p) {
-  if (p.ntiles <= (p.ncell <= 2 ? 128 : 16)) return 4;
+  if (p.ntiles <= 128 && p.near_part >= 1.0 / 80.0) return 4;
   return p.ntiles <= 1024 ? 16 : kTile;
 }
 
@@ -790,7 +794,7 @@ static int run_chunk(void* ws, int kind, EnqueueFn fn, int chunk, const Plan& p,
     HIPCHK(hipGetLastError());
     return HDMD_OK;
   }
-  const int form = (int)p.wrap + 2 * p.reach + 8 * build_mode(p.reach, p.n, p.ncells);
+  const int form = (int)p.wrap + 2 * p.reach + 8 * build_mode(p.reach, p.n, p.ncells) + 16 * (p.wrap ? circle_homes(p) : 0);
   GraphKey key{ws,      kind,  chunk, p.d,     (int)p.mix + 2 * p.lpa, (int)p.morse, form,
                blk,     p.ntiles, p.ncells, p.nchunks};
   hipGraphExec_t exec = nullptr;

@@ -1,6 +1,7 @@
-"""A lone system's circle form takes four home atoms per wave up to 1024 atoms
-(8192 where n_cell <= 2) and sixteen past that: lists and forces on both sides
-of either line, with last groups that are not full."""
+"""A lone system's circle form takes four home atoms per wave where at least an
+eightieth of the box lies within the list radius, up to 8192 atoms, and sixteen
+otherwise: lists and forces on both sides of either line, with last groups that
+are not full."""
 import numpy as np
 import pytest
 
@@ -14,7 +15,7 @@ CUT, SKIN = 1.0, 0.25
 
 @pytest.mark.parametrize("d,n,nc", [
     (3, 3, 2), (4, 65, 2), (3, 1022, 2), (8, 1027, 2), (6, 8192, 2), (6, 8193, 2),
-    (3, 1021, 5), (3, 1024, 5), (5, 1025, 3), (7, 1023, 3), (2, 6, 4),
+    (3, 1021, 5), (3, 1024, 5), (5, 1025, 3), (7, 1023, 3), (2, 6, 4), (6, 900, 2.7), (6, 901, 2.75),
 ])
 def test_lists_and_forces(orc, d, n, nc):
     L = nc * (CUT * 1.4 + SKIN) * 1.01
