@@ -593,8 +593,8 @@ def main():
     if "step_kernel_ms" in f:
         roof = {"bound": "hbm", "achieved": f["step_kernel_gbs"], "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": f["step_kernel_gbs"] / HBM_PEAK_GBS,
-                "traffic": committed_counter("step_kernel_c3_traffic.json"),
-                "kernel": "k_step<6,fp64>", "bytes_per_launch": cfg.n * f["step_bytes_per_atom"],
+                "traffic": committed_counter("step_kernel_c3_traffic.json") if cfg.n == 262144 else None,
+                "kernel": "k_step<%d,fp64>" % cfg.d, "bytes_per_launch": cfg.n * f["step_bytes_per_atom"],
                 "launch_ms": f["step_kernel_ms"]}
     # the list build against the vector ALU peak: the kernel's own vector
     # instructions per build (committed counters of this kernel source, d = 6
