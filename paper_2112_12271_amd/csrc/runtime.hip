@@ -80,7 +80,7 @@ struct Plan {
   // taken from the grid of side >= r_l,max; nh_auto: half-size subcells per
   // axis the autotuner may take (0: none)
   int reach = 1, key_wrap = 0, key_occ = 0, nh_auto = 0;
-  int lpa = 1;        // lanes per atom of the force kernels
+  int lpa = 1;         // lanes per atom of the force kernels
   LanesKey lanes_key;  // and their key
   double rlmax = 0;
   double near_part = 0;  // V_d(r_l,max) / L^d: the part of the box within the list radius
@@ -172,8 +172,8 @@ static int lanes_for(const hdmd_system* s, const LanesKey& key);
 // The force kernels' key: half-octaves of the expected row length, the atoms
 // in a ball of the largest list radius at the mean number density, n V_d(r)
 // / L^d, and octaves of n: long rows pay for more lanes while the waves of one
-// lane per atom leave SIMDs without work (MD step loops with 1, 2 and 4 lanes,
-// us per step: d = 6, rows of 75, N = 30000 134, 121, 118, N = 262144 645,
+// lane per atom leave SIMDs without work (MD calls of 20 or 40 steps, 1, 2 and
+// 4 lanes, us per step: d = 6, rows of 75, N = 30000 134, 121, 118, N = 262144 645,
 // 733, 770; d = 4, rows of 33, N = 65536 89, 85, 86, N = 200000 263, 312,
 // 332).
 static LanesKey lanes_key(const hdmd_system& s, double near_part) {
@@ -421,7 +421,8 @@ static int lookup_blk(const Plan& p, bool* known) {
 // Lanes per atom of the force kernels (1, 2 or 4 lanes share an atom's row;
 // their partial sums meet in a tree that depends on the count, so the choice
 // fixes the rounding of the forces): chosen by the autotuner per lanes_key and
-// kept for every later system with that key, alone or in a batch.  Morse systems take one lane.  HDMD_LPA overrides.
+// kept for every later system with that key, alone or in a batch.  Morse
+// systems take one lane.  HDMD_LPA overrides.
 static int lpa_env() {
   const char* e = std::getenv("HDMD_LPA");
   if (!e) return 0;
@@ -794,7 +795,8 @@ static int run_chunk(void* ws, int kind, EnqueueFn fn, int chunk, const Plan& p,
     HIPCHK(hipGetLastError());
     return HDMD_OK;
   }
-  const int form = (int)p.wrap + 2 * p.reach + 8 * build_mode(p.reach, p.n, p.ncells) + 16 * (p.wrap ? circle_homes(p) : 0);
+  const int form = (int)p.wrap + 2 * p.reach + 8 * build_mode(p.reach, p.n, p.ncells) +
+                   16 * (p.wrap ? circle_homes(p) : 0);
   GraphKey key{ws,      kind,  chunk, p.d,     (int)p.mix + 2 * p.lpa, (int)p.morse, form,
                blk,     p.ntiles, p.ncells, p.nchunks};
   hipGraphExec_t exec = nullptr;
